@@ -60,6 +60,13 @@ int chi0_ws_debug_loss_grad(chi0_ws *ws, int32_t n, const double *omega, const f
  * steps recorded (0 if none).  Either pointer may be NULL. */
 int chi0_debug_lz_passes(const chi0_ctx *ctx, int32_t *passes, double *b_pre, int32_t cap);
 
+/* C [M][N] = A [M][K] B [K][N] (host, row-major) by the panel GEMM that the
+ * dense transforms of `precision` use (CHI0_PREC_BF16X3), with at most
+ * `work_bytes` of panels for B (so that small sizes also go in chunks of
+ * columns).  Needs a device context, no system.  Synchronous. */
+int chi0_debug_panel_gemm(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N, int32_t K, const double *A,
+                          const double *B, int64_t work_bytes, double *C);
+
 /* Host eigen-decomposition of a Hermitian n x n matrix (row-major interleaved
  * complex): eigenvalues descending in w[n], eigenvectors as columns of V. */
 int chi0_debug_eigh(int32_t n, const double *A, double *w, double *V);

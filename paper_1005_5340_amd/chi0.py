@@ -156,6 +156,9 @@ def lib():
     L.chi0_ws_debug_loss_grad.restype = C.c_int
     L.chi0_debug_lz_passes.argtypes = [C.c_void_p, _i32p, _dp, C.c_int32]
     L.chi0_debug_lz_passes.restype = C.c_int
+    L.chi0_debug_panel_gemm.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _dp, _dp,
+                                        C.c_int64, _dp]
+    L.chi0_debug_panel_gemm.restype = C.c_int
     L.chi0_debug_eigh.argtypes = [C.c_int32, _dp, _dp, _dp]
     L.chi0_debug_eigh.restype = C.c_int
     L.chi0_lanczos_opts_default.argtypes = [C.POINTER(LanczosOpts)]
@@ -449,6 +452,15 @@ class Context:
         b = np.zeros((max(n, 1), n_drive))
         self._L.chi0_debug_lz_passes(self._h, _ptr(p, _i32p), _ptr(b), n)
         return p[:n], b[:n]
+
+    def debug_panel_gemm(self, A, B, precision: int, work_bytes: int = 1 << 30) -> np.ndarray:
+        """Test hook: A @ B by the panel GEMM of the dense transforms (chi0_debug_panel_gemm)."""
+        A, B = _f64(A), _f64(B)
+        (M, K), N = A.shape, B.shape[1]
+        out = np.zeros((M, N))
+        self._check(self._L.chi0_debug_panel_gemm(self._h, int(precision), M, N, K, _ptr(A), _ptr(B),
+                                                  int(work_bytes), _ptr(out)))
+        return out
 
     def set_graphs(self, enable: bool):
         """Replay repeated chi0_apply calls from a HIP graph (chi0_set_graphs)."""

@@ -114,13 +114,15 @@ struct OpWork {
     double *gemm_scratch = nullptr;
     size_t gemm_scratch_n = 0;
     float *Tt32 = nullptr, *at32 = nullptr, *Ut32 = nullptr;
-    uint16_t *Bhi = nullptr, *Blo = nullptr;   // split-BF16 planes of the dense GEMMs' B operand
+    void *panel = nullptr;   // panels of the dense GEMMs' B operand
+    size_t panel_bytes = 0;
     void release() {
         lpbuf.release();
         buf.release();
         nc_cap = lp_cap = 0;
         Tt32 = at32 = Ut32 = nullptr;
-        Bhi = Blo = nullptr;
+        panel = nullptr;
+        panel_bytes = 0;
     }
 };
 constexpr int kLanes = 4;            // most slot lanes of the solver, one stream each
@@ -179,7 +181,7 @@ struct chi0_ctx {
     }
     // low-precision operator: operand copies (set_system)
     float *Xo32 = nullptr, *Xv32 = nullptr, *Xvt32 = nullptr;
-    uint16_t *Xv_hi = nullptr, *Xv_lo = nullptr, *Xvt_hi = nullptr, *Xvt_lo = nullptr;
+    PanelDev Xv_bf, Xvt_bf;   // BF16 panels: rows = atomic orbitals (b3), rows = virtual states (b2)
 
     // partial reorthogonalisation with kernel timing on: per step, whether the
     // pass ran and the b_j (one per drive) that the device decision used
@@ -270,6 +272,17 @@ static int dalloc(chi0_ctx *c, DevBuf &buf, T **p, int64_t n) {
         int r_ = (x);               \
         if (r_ != CHI0_OK) return r_; \
     } while (0)
+
+// BF16 panels of an operand with `rows` rows and K reduction entries.
+static int panel_alloc(chi0_ctx *c, DevBuf &buf, PanelDev &p, int rows, int K) {
+    p.ld = (int)round_up(rows, PANEL_LD);
+    p.nkb = (int)round_up((K + 7) / 8, PANEL_KB);
+    p.plane = (int64_t)p.nkb * p.ld;
+    double *d = nullptr;
+    CHK(dalloc(c, buf, &d, p.plane * PANEL_BF * 2));
+    p.data = d;
+    return CHI0_OK;
+}
 
 // ============================================================ static scratch
 // Workspace of chi0_apply_noalloc: a fixed array in device memory, one copy
@@ -657,16 +670,14 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
         CHK(dalloc(c, sb, &c->Xo32, (int64_t)xo.size()));
         CHK(dalloc(c, sb, &c->Xv32, (int64_t)xv.size()));
         CHK(dalloc(c, sb, &c->Xvt32, (int64_t)xvt.size()));
-        CHK(dalloc(c, sb, &c->Xv_hi, (int64_t)xv.size()));
-        CHK(dalloc(c, sb, &c->Xv_lo, (int64_t)xv.size()));
-        CHK(dalloc(c, sb, &c->Xvt_hi, (int64_t)xvt.size()));
-        CHK(dalloc(c, sb, &c->Xvt_lo, (int64_t)xvt.size()));
+        CHK(panel_alloc(c, sb, c->Xvt_bf, Nv, N));
+        CHK(panel_alloc(c, sb, c->Xv_bf, N, Nv));
         HIPCHK(c, hipDeviceSynchronize());
         launch_to_f32(nullptr, c->Xo, c->Xo32, (int64_t)xo.size());
         launch_to_f32(nullptr, c->Xv, c->Xv32, (int64_t)xv.size());
         launch_to_f32(nullptr, c->Xvt, c->Xvt32, (int64_t)xvt.size());
-        launch_split_bf16(nullptr, c->Xv, c->Xv_hi, c->Xv_lo, (int64_t)xv.size());
-        launch_split_bf16(nullptr, c->Xvt, c->Xvt_hi, c->Xvt_lo, (int64_t)xvt.size());
+        launch_panel_bf16(nullptr, c->Xv, N, Nv, c->Nv_pad, &c->Xvt_bf);
+        launch_panel_bf16(nullptr, c->Xvt, Nv, N, c->N_pad, &c->Xv_bf);
         HIPCHK(c, hipGetLastError());
         HIPCHK(c, hipDeviceSynchronize());
     }
@@ -746,6 +757,10 @@ static int ensure_ws(chi0_ctx *c, OpWork &o, int nc) {
     return CHI0_OK;
 }
 
+// Most bytes of B panels held at once: a transform over more columns goes in
+// chunks of columns.
+constexpr int64_t kPanelBytes = 256LL << 20;
+
 static int ensure_lp(chi0_ctx *c, OpWork &o) {
     if (o.lp_cap >= o.nc_cap && o.Tt32) return CHI0_OK;
     for (hipStream_t ls : c->lane_stream)
@@ -758,12 +773,14 @@ static int ensure_lp(chi0_ctx *c, OpWork &o) {
     CHK(dalloc(c, o.lpbuf, &o.Tt32, (int64_t)c->N_pad * mcol));
     CHK(dalloc(c, o.lpbuf, &o.Ut32, (int64_t)c->N_pad * mcol));
     CHK(dalloc(c, o.lpbuf, &o.at32, (int64_t)c->Nv_pad * mcol));
-    // two uint16 planes of max(N_pad, Nv_pad) x mcol: as many bytes as one FP32 copy
-    const int64_t kmax = std::max(c->N_pad, c->Nv_pad);
-    double *planes = nullptr;
-    CHK(dalloc(c, o.lpbuf, &planes, (kmax * mcol + 3) / 4 * 2));
-    o.Bhi = reinterpret_cast<uint16_t *>(planes);
-    o.Blo = o.Bhi + (kmax * mcol + 3) / 4 * 4;
+    // B panels of the dense transforms: every column at once up to kPanelBytes
+    const int64_t nkb = std::max(c->Xvt_bf.nkb, c->Xv_bf.nkb);
+    const int64_t full = nkb * round_up(mcol, PANEL_LD) * 16 * PANEL_BF;
+    const int64_t least = nkb * PANEL_LD * 16 * PANEL_BF;
+    o.panel_bytes = (size_t)std::max(least, std::min(full, kPanelBytes));
+    double *pd = nullptr;
+    CHK(dalloc(c, o.lpbuf, &pd, (int64_t)(o.panel_bytes / 8)));
+    o.panel = pd;
     HIPCHK(c, hipDeviceSynchronize());
     o.lp_cap = o.nc_cap;
     return CHI0_OK;
@@ -807,12 +824,12 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
                          o.at32, (int)mcol, o.Ut32, (int)mcol, fl, by + 4.0 * w.N * w.Nv, nullptr,
                          o.gemm_scratch, sb, tu);
         } else {   // split BF16 x 3: three BF16 products per multiply-add
-            launch_bgemm3(t, s, "virt_transform_lorentz_bf16x3", c->Nv_pad, ncol, c->N_pad, c->Xvt_hi,
-                          c->Xvt_lo, c->N_pad, o.Tt32, (int)mcol, o.Bhi, o.Blo, o.at32, (int)mcol, 3.0 * fl,
-                          by + 4.0 * w.N * w.Nv, &la, o.gemm_scratch, sb);
-            launch_bgemm3(t, s, "virt_back_bf16x3", c->N_pad, ncol, c->Nv_pad, c->Xv_hi, c->Xv_lo,
-                          c->Nv_pad, o.at32, (int)mcol, o.Bhi, o.Blo, o.Ut32, (int)mcol, 3.0 * fl,
-                          by + 4.0 * w.N * w.Nv, nullptr, o.gemm_scratch, sb);
+            launch_panel_gemm_bf16x3(t, s, "virt_transform_lorentz_bf16x3", c->Nv_pad, ncol, c->N, c->Xvt_bf,
+                                     o.Tt32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb, o.at32, (int)mcol,
+                                     3.0 * fl, by + 4.0 * w.N * w.Nv, &la);
+            launch_panel_gemm_bf16x3(t, s, "virt_back_bf16x3", c->N_pad, ncol, c->Nv, c->Xv_bf, o.at32, mcol, o.panel,
+                                     o.panel_bytes, o.gemm_scratch, sb, o.Ut32, (int)mcol, 3.0 * fl,
+                                     by + 4.0 * w.N * w.Nv, nullptr);
         }
         launch_occ_back_f32(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo32, c->No_pad, c->No16, o.Ut32, o.W, nc, w);
     }
@@ -2055,6 +2072,48 @@ extern "C" int chi0_ws_debug_loss_grad(chi0_ws *w, int32_t n, const double *omeg
     HIPCHK(c, hipMemcpyAsync(grads, w->grads, (size_t)w->n_params * 4, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     HIPCHK(c, hipGetLastError());
+    return CHI0_OK;
+}
+
+extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, int32_t N, int32_t K,
+                                     const double *A, const double *B, int64_t work_bytes, double *C) {
+    if (!c) return CHI0_EINVAL;
+    if (c->device < 0) return fail(c, CHI0_ENOSYS, "no device context");
+    if (M < 1 || N < 1 || K < 1 || !A || !B || !C) return fail(c, CHI0_EINVAL, "bad sizes or NULL");
+    if (precision != CHI0_PREC_BF16X3) return fail(c, CHI0_EINVAL, "no panel GEMM for this precision");
+    HIPCHK(c, hipSetDevice(c->device));
+    struct Scope {
+        DevBuf buf;
+        ~Scope() { buf.release(); }
+    } ws;
+    const int64_t mk = (int64_t)M * K, kn = (int64_t)K * N, mn = (int64_t)M * N;
+    std::vector<double> at((size_t)mk);
+    std::vector<float> b32((size_t)kn), c32((size_t)mn);
+    for (int i = 0; i < M; ++i)
+        for (int k = 0; k < K; ++k) at[(size_t)k * M + i] = A[(size_t)i * K + k];
+    for (int64_t i = 0; i < kn; ++i) b32[i] = (float)B[i];
+    double *a_d = nullptr, *work = nullptr, *scratch = nullptr;
+    float *b_d = nullptr, *c_d = nullptr;
+    PanelDev p;
+    CHK(panel_alloc(c, ws.buf, p, M, K));
+    const int64_t least = (int64_t)p.nkb * PANEL_LD * 16 * PANEL_BF;
+    work_bytes = std::max(work_bytes, least);
+    const size_t scratch_n = (size_t)2048 * 64 * 64;
+    CHK(dalloc(c, ws.buf, &a_d, mk));
+    CHK(dalloc(c, ws.buf, &work, work_bytes / 8));
+    CHK(dalloc(c, ws.buf, &scratch, (int64_t)scratch_n));
+    CHK(dalloc(c, ws.buf, &b_d, kn));
+    CHK(dalloc(c, ws.buf, &c_d, mn));
+    HIPCHK(c, hipMemcpy(a_d, at.data(), mk * 8, hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpy(b_d, b32.data(), kn * 4, hipMemcpyHostToDevice));
+    launch_panel_bf16(c->stream, a_d, K, M, M, &p);
+    HIPCHK(c, hipDeviceSynchronize());   // the copies above are on the default stream
+    launch_panel_gemm_bf16x3(nullptr, c->stream, "panel", M, N, K, p, b_d, N, work, (size_t)(work_bytes / 8 * 8),
+                             scratch, scratch_n * sizeof(double), c_d, N, 0.0, 0.0, nullptr);
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipMemcpy(c32.data(), c_d, mn * 4, hipMemcpyDeviceToHost));
+    for (int64_t i = 0; i < mn; ++i) C[i] = c32[i];
     return CHI0_OK;
 }
 

@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <map>
 #include <string>
 
@@ -140,13 +141,30 @@ void launch_sgemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int 
                   const float *A, int lda, const float *B, int ldb, float *C, int ldc,
                   double flops, double bytes, const LorentzArgs *la, void *scratch,
                   size_t scratch_bytes, GemmTuner *tu = nullptr);
-// Bhi/Blo: workspace of K * N uint16 each, filled with B's split (k-blocks of 8).
-void launch_bgemm3(Tracer *t, hipStream_t s, const char *name, int M, int N, int K,
-                   const uint16_t *Ahi, const uint16_t *Alo, int lda, const float *B, int ldb,
-                   uint16_t *Bhi, uint16_t *Blo, float *C, int ldc, double flops, double bytes,
-                   const LorentzArgs *la, void *scratch, size_t scratch_bytes);
+// An operand of the panel GEMMs (kernels_panel.hip): planes of 16-byte k-blocks,
+// block kb of row r at uint4 number kb * ld + r of a plane of `plane` uint4s.
+struct PanelDev {
+    void *data = nullptr;
+    int ld = 0;          // rows, rounded up to PANEL_LD
+    int nkb = 0;         // k-blocks, rounded up to PANEL_KB
+    int64_t plane = 0;   // uint4s per plane, nkb * ld
+};
+constexpr int PANEL_LD = 128;   // rows of an operand: whole GEMM tiles
+constexpr int PANEL_KB = 4;     // k-blocks of an operand: whole GEMM stages
+constexpr int PANEL_BF = 2;     // BF16 planes kept of the orbital matrices
+// planes of X [K][ldx] (N columns = the operand's rows); p->nkb, ld, plane set
+void launch_panel_bf16(hipStream_t s, const double *X, int K, int N, int64_t ldx, PanelDev *p);
+// C = A B in split BF16 x 3, B [K][ldb] FP32; `work` takes B's panels, as many
+// columns at a time as fit (at least PANEL_LD; all of N where N is small enough
+// for split-K, whose partial sums go to `scratch`).
+void launch_panel_gemm_bf16x3(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const PanelDev &A,
+                              const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
+                              size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
+                              const LorentzArgs *la);
+// C = sum of S FP32 slices of M x N (+ the frequency factor if la)
+void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, const float *part,
+                              float *C, int ldc, const LorentzArgs *la);
 void launch_to_f32(hipStream_t s, const double *x, float *y, int64_t n);
-void launch_split_bf16(hipStream_t s, const double *x, uint16_t *hi, uint16_t *lo, int64_t n);
 
 // (e) skinny K z for a few columns (HBM-streaming GEMV).
 void launch_kmatvec_skinny(Tracer *t, hipStream_t s, int P_pad, const double *K,

@@ -1,0 +1,326 @@
+// Dense matrix-core products over k-block panels: the virtual-orbital
+// transforms (Sec. 4.2, Table t:flops steps 3 and 4) wherever their operands
+// are cut into pieces of a narrow type.
+//
+// Panel layout.  An operand with R rows (columns of B) and K reduction
+// entries is stored in 16-byte blocks of consecutive k (8 of BF16): block
+// kb of row r is uint4 number kb * ld + r of its plane, ld >= R.  That is
+// what one lane of a 32x32 MFMA supplies (lane l: row l % 32, k-block l / 32
+// of the instruction's two), so a tile is a set of contiguous runs in global
+// memory, goes straight to LDS (16 bytes per lane, consecutive lanes to
+// consecutive addresses) and is read back without bank conflicts and without
+// padding.  A and B use the same k order inside a block, so the order itself
+// does not matter.  D of a 32x32 MFMA: element r of lane l is row
+// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+#include "common.h"
+
+#include <type_traits>
+
+namespace chi0 {
+
+// 128x128 tiles from which those are used: about one per CU; fewer leave CUs idle and the
+// 64x64 tiles, with split-K, fill the chip
+constexpr int PANEL_BIG = 200;
+
+typedef float flt16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+#define CHI0_GLOBAL __attribute__((address_space(1)))
+#define CHI0_LDS __attribute__((address_space(3)))
+
+// Workgroup id -> tile id, each of the 8 XCDs on one contiguous range of tiles.
+__device__ __forceinline__ int panel_xcd(int wid, int n) {
+    const int q = n / 8, r = n % 8;
+    const int x = wid % 8, local = wid / 8;
+    return x * q + (x < r ? x : r) + local;
+}
+
+__device__ __forceinline__ uint16_t panel_bf(float x) {   // round to nearest even
+    const uint32_t u = __float_as_uint(x);
+    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+__device__ __forceinline__ float panel_unbf(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
+// C [M][ldc] (FP32) = A B, A and B as PL planes of BF16 (hi, then the
+// rounded remainders): PL = 2 sums lo hi + hi lo + hi hi.
+//
+// A workgroup computes a BM x BN tile with WM x WN wavefronts of 32x32 MFMA
+// tiles.  KB k-blocks of both operands make one stage; two stages of LDS are
+// filled in turn by direct-to-LDS loads.  The fragments of a step are read
+// while the MFMAs of the step before run, also across the stage boundary:
+// the last step's fragments are in registers when the workgroup meets at the
+// barrier, so the loads that refill the freed stage and the first fragment
+// reads of the next one are issued ahead of the last step's MFMAs and a load
+// has a whole stage of MFMAs to land.  blockIdx.y selects a k range of
+// nkb_split k-blocks (at least one stage), whose raw sums go to a C slice of
+// their own.
+//
+// Bound by the matrix cores' sustained rate: 128x128 tiles execute 1.0-1.1
+// PFLOP/s of BF16 (a library product of 8192^3 reaches 1.05 on this card).
+// The 64x64-tile kernel with 16x16x32 MFMAs and operands staged through
+// registers that this replaces was bound by its LDS reads (a 16-byte fragment
+// per 1.5 MFMAs; here one per 1.5 MFMAs of twice the work) and ran at 0.54:
+// 400-atom transforms of 32 vectors (3200 x 128000 x 5200) 23.6 and 22.3 ms
+// before, 12.7 and 12.2 ms now; 200 atoms, 24 vectors 705 and 663 -> 516 and
+// 408 us.
+template <int PL, int BM, int BN, int WM, int WN, int KB, bool LORENTZ>
+__global__ __launch_bounds__(WM * WN * 64)
+void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const uint4 *__restrict__ A, int lda,
+                  int64_t apl, const uint4 *__restrict__ B, int ldb, int64_t bpl, float *__restrict__ C, int ldc,
+                  int col0, LorentzArgs la) {
+    constexpr int NT = WM * WN * 64;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int SA = KB * BM, SB = KB * BN, KS = KB / 2;
+    static_assert(SA % NT == 0 && SB % NT == 0 && KB % 2 == 0, "whole 16-byte chunks per thread");
+    __shared__ uint4 s0[PL * (SA + SB)], s1[PL * (SA + SB)];
+    const int tile = panel_xcd(blockIdx.x, ntm * ntn);
+    const int m0 = (tile % ntm) * BM, n0 = (tile / ntm) * BN;
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wv % WM, wn = wv / WM, lr = lane & 31, lk = lane >> 5;
+    const int kb0 = blockIdx.y * nkb_split, KT = min(nkb_split, nkb - kb0) / KB;
+    A += (int64_t)kb0 * lda + m0;
+    B += (int64_t)kb0 * ldb + n0;
+    C += (int64_t)blockIdx.y * M * ldc;
+
+    auto load = [&](uint4 *dst, int kt) {
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) {
+#pragma unroll
+            for (int c = 0; c < SA / NT; ++c) {
+                const int ch = c * NT + t;
+                const uint4 *g = A + pl * apl + (int64_t)(kt * KB + ch / BM) * lda + ch % BM;
+                __builtin_amdgcn_global_load_lds((const CHI0_GLOBAL void *)g,
+                                                 (CHI0_LDS void *)(dst + pl * SA + c * NT + wv * 64), 16, 0, 0);
+            }
+#pragma unroll
+            for (int c = 0; c < SB / NT; ++c) {
+                const int ch = c * NT + t;
+                const uint4 *g = B + pl * bpl + (int64_t)(kt * KB + ch / BN) * ldb + ch % BN;
+                __builtin_amdgcn_global_load_lds((const CHI0_GLOBAL void *)g,
+                                                 (CHI0_LDS void *)(dst + PL * SA + pl * SB + c * NT + wv * 64), 16,
+                                                 0, 0);
+            }
+        }
+    };
+    flt16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    uint4 fa[2][PL][TM], fb[2][PL][TN];   // fragments of two steps
+    auto read = [&](int w, const uint4 *src, int ks) {
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                fb[w][pl][j] = src[PL * SA + pl * SB + (2 * ks + lk) * BN + wn * (BN / WN) + j * 32 + lr];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                fa[w][pl][i] = src[pl * SA + (2 * ks + lk) * BM + wm * (BM / WM) + i * 32 + lr];
+        }
+    };
+    auto mma = [&](int w) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                auto mm = [&](int x, int y) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[w][x][i]),
+                                                                        __builtin_bit_cast(bf16x8, fb[w][y][j]),
+                                                                        acc[i][j], 0, 0, 0);
+                };
+                mm(1, 0);
+                mm(0, 1);
+                mm(0, 0);
+            }
+    };
+    // every wavefront's loads have landed and every fragment read is done
+    auto meet = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+    };
+    // Stage kt in `cur`, its first step's fragments already in set W0.  Past the
+    // last stage the fragment read of `nxt` takes what LDS holds and is not used.
+    auto stage = [&](auto W0, uint4 *cur, const uint4 *nxt, int kt) {
+        constexpr int w0 = decltype(W0)::value;
+#pragma unroll
+        for (int ks = 0; ks + 1 < KS; ++ks) {
+            read((w0 + ks + 1) & 1, cur, ks + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma((w0 + ks) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        meet();
+        if (kt + 2 < KT) load(cur, kt + 2);
+        read((w0 + KS) & 1, nxt, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mma((w0 + KS - 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(s0, 0);
+    meet();
+    if (KT > 1) load(s1, 1);
+    read(0, s0, 0);
+    int kt = 0;
+    for (; kt + 2 <= KT; kt += 2) {
+        stage(std::integral_constant<int, 0>{}, s0, s1, kt);
+        stage(std::integral_constant<int, KS & 1>{}, s1, s0, kt + 1);
+    }
+    if (kt < KT) stage(std::integral_constant<int, 0>{}, s0, s1, kt);
+
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn * (BN / WN) + j * 32 + lr;
+        const bool ok = col < N;
+        int E = 0, par = 0;
+        double w = 0.0;
+        if (LORENTZ) {
+            const int cc = ok ? col0 + col : 0;
+            E = cc / la.ncp;
+            const int jj = cc - E * la.ncp;
+            par = jj & 1;
+            w = la.omega[jj >> 1];
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = m0 + wm * (BM / WM) + i * 32 + 8 * (r / 4) + 4 * lk + r % 4;
+                float v = acc[i][j][r];
+                if (LORENTZ) {
+                    const float other = __shfl_xor(v, 1);
+                    const double D = la.Dlt[(int64_t)E * la.nv_pad + (row < M ? row : 0)];
+                    const double d1 = w - D, d2 = w + D, e = la.eps;
+                    const double dm = par ? d2 : d1;   // the Re / Im pair shares the two reciprocals
+                    const double sm = 1.0 / (dm * dm + e * e), so = __shfl_xor(sm, 1);
+                    const double f1 = par ? so : sm, f2 = par ? sm : so;
+                    const double Lr = la.occ * (d1 * f1 - d2 * f2);
+                    const double Li = la.occ * (-e * f1 + e * f2);
+                    const double re = par ? other : v, im = par ? v : other;
+                    v = (float)(par ? (re * Li + im * Lr) : (re * Lr - im * Li));
+                }
+                if (ok && row < M) __builtin_nontemporal_store(v, &C[(int64_t)row * ldc + col]);
+            }
+    }
+}
+
+// X [K][ldx] -> PL planes of BF16 panels, columns n < N (zero for k >= K and
+// up to ld): plane 0 holds bf16(x), each further one bf16 of what the planes
+// before leave.  Thread (kb, n) reads the 8 rows of its block in column n
+// (coalesced over n) and writes 16 bytes per plane.
+template <int PL, class T>
+__global__ __launch_bounds__(256)
+void k_panel_split(const T *__restrict__ X, int K, int N, int64_t ldx, int nkb, int ld, uint4 *__restrict__ out,
+                   int64_t plane) {
+    const int64_t total = (int64_t)nkb * ld;
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
+        const int kb = (int)(idx / ld), n = (int)(idx % ld);
+        float x[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int k = kb * 8 + c;
+            x[c] = (n < N && k < K) ? (float)X[(int64_t)k * ldx + n] : 0.f;
+        }
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) {
+            uint32_t w[4];
+#pragma unroll
+            for (int c = 0; c < 8; c += 2) {
+                const uint16_t h0 = panel_bf(x[c]), h1 = panel_bf(x[c + 1]);
+                x[c] -= panel_unbf(h0);
+                x[c + 1] -= panel_unbf(h1);
+                w[c / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            }
+            out[pl * plane + idx] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_to_f32(const double *__restrict__ x, float *__restrict__ y, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        y[i] = (float)x[i];
+}
+
+template <int PL, class T>
+static void split_any(hipStream_t s, const T *X, int K, int N, int64_t ldx, int nkb, int ld, uint4 *out,
+                      int64_t plane) {
+    int64_t blocks = ((int64_t)nkb * ld + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    hipLaunchKernelGGL((k_panel_split<PL, T>), dim3((unsigned)blocks), dim3(256), 0, s, X, K, N, ldx, nkb, ld, out,
+                       plane);
+}
+
+void launch_panel_bf16(hipStream_t s, const double *X, int K, int N, int64_t ldx, PanelDev *p) {
+    split_any<PANEL_BF, double>(s, X, K, N, ldx, p->nkb, p->ld, reinterpret_cast<uint4 *>(p->data), p->plane);
+}
+
+template <int PL, int BM, int BN, bool LORENTZ>
+static void panel_launch(hipStream_t s, int M, int N, int S, int nkb_split, const PanelDev &A, const uint4 *B,
+                         int ldb, float *C, int ldc, int col0, const LorentzArgs &la) {
+    const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
+    hipLaunchKernelGGL((k_panel_gemm<PL, BM, BN, 2, 2, PANEL_KB, LORENTZ>), dim3(ntm * ntn, S), dim3(256), 0, s, M,
+                       N, ntm, ntn, A.nkb, nkb_split, reinterpret_cast<const uint4 *>(A.data), A.ld, A.plane, B, ldb,
+                       (int64_t)A.nkb * ldb, C, ldc, col0, la);
+}
+
+template <int PL>
+static void panel_gemm_any(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const PanelDev &A,
+                           const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
+                           size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
+                           const LorentzArgs *la) {
+    const int nkb = A.nkb, KT = nkb / PANEL_KB;
+    uint4 *bp = static_cast<uint4 *>(work);
+    const LorentzArgs none{};
+    const int64_t big = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+    const int64_t small = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+    int S = 1;   // k splits of the small tiles, each at least 4 stages
+    // columns whose B panels fit the workspace at once
+    const int64_t fit = (int64_t)(work_bytes / ((size_t)PL * nkb * 16)) / PANEL_LD * PANEL_LD;
+    if (scratch && big < PANEL_BIG && fit >= N)
+        while (S < 16 && small * S < 1024 && KT / (2 * S) >= 4 &&
+               (size_t)(2 * S) * M * (size_t)N * sizeof(float) <= scratch_bytes)
+            S *= 2;
+    const int kts = (KT + S - 1) / S;
+    S = (KT + kts - 1) / kts;
+    const int chunk = S > 1 ? N : (int)std::min<int64_t>(fit, round_up(N, PANEL_LD));
+    for (int c0 = 0; c0 < N; c0 += chunk) {
+        const int n = std::min(chunk, N - c0), ld = (int)round_up(n, PANEL_LD);
+        const double share = (double)n / N;
+        trace_begin(t, "bf16_split", s);
+        split_any<PL, float>(s, B + c0, K, n, ldb, nkb, ld, bp, (int64_t)nkb * ld);
+        trace_end(t, s, 0.0, (4.0 + 2.0 * PL) * (double)K * n);
+        trace_begin(t, name, s);
+        if (big >= PANEL_BIG) {
+            if (la) panel_launch<PL, 128, 128, true>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, *la);
+            else panel_launch<PL, 128, 128, false>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, none);
+        } else if (S == 1) {
+            if (la) panel_launch<PL, 64, 64, true>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, *la);
+            else panel_launch<PL, 64, 64, false>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, none);
+        } else {
+            panel_launch<PL, 64, 64, false>(s, M, n, S, kts * PANEL_KB, A, bp, ld, static_cast<float *>(scratch), n,
+                                            0, none);
+        }
+        trace_end(t, s, flops * share, bytes * share);
+        if (S > 1)
+            launch_splitk_reduce_f32(t, s, M, n, S, static_cast<const float *>(scratch), C, ldc, la);
+    }
+}
+
+void launch_panel_gemm_bf16x3(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const PanelDev &A,
+                              const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
+                              size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
+                              const LorentzArgs *la) {
+    panel_gemm_any<2>(t, s, name, M, N, K, A, B, ldb, work, work_bytes, scratch, scratch_bytes, C, ldc, flops, bytes,
+                      la);
+}
+
+void launch_to_f32(hipStream_t s, const double *x, float *y, int64_t n) {
+    int64_t blocks = (n + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    if (n > 0) hipLaunchKernelGGL(k_to_f32, dim3((unsigned)blocks), dim3(256), 0, s, x, y, n);
+}
+
+}  // namespace chi0
