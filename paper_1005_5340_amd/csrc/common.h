@@ -57,6 +57,46 @@ struct LorentzArgs {
     double occ;
 };
 
+// Value of the neighbouring lane (lane ^ 1): a DPP quad permutation, no LDS.
+__device__ __forceinline__ float lane_pair(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double lane_pair(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, true));
+}
+
+// L = n [1/(w - D + i eps) - 1/(w + D + i eps)] = 2 n D / q with
+// q = (w + i eps)^2 - D^2: one reciprocal, and no difference of two nearly
+// equal terms far from resonance.  Re q = (w - D)(w + D) - eps^2 keeps its
+// accuracy near resonance.  The reciprocal is the hardware estimate with two
+// Newton steps (to ~1 ulp).  The clamps only keep |q|^2 in range where L is
+// below 1e-59.
+//
+// The real (par = 0) and imaginary (par = 1) parts of a column pair sit in
+// neighbouring lanes: lane `par` holds own, its partner other, and
+// own * L becomes own Re L + other (par ? Im L : -Im L).
+struct Lorentz {
+    double w, e2, qi2, sqi, occ2;
+    __device__ __forceinline__ Lorentz(double omega, double eps, double occ, int par) {
+        w = fmin(fmax(omega, -1e60), 1e60);
+        const double e = fmin(eps, 1e60), qi = 2.0 * w * e;
+        e2 = e * e;
+        qi2 = qi * qi;
+        sqi = par ? -qi : qi;   // Im L = -f Im q
+        occ2 = 2.0 * occ;
+    }
+    __device__ __forceinline__ double apply(double D, double own, double other) const {
+        const double qr = fmax(__builtin_fma(w - D, w + D, -e2), -1e150);
+        const double den = __builtin_fma(qr, qr, qi2);
+        double r = __builtin_amdgcn_rcp(den);
+        r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
+        r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
+        const double f = occ2 * D * r;
+        return own * (f * qr) + other * (f * sqi);
+    }
+};
+
 // -------------------------------------------------------------- chi0 blocks
 struct BlockMapDev {
     // per atom-pair block k (n_blk of them)

@@ -196,15 +196,8 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
     for (int j = 0; j < TN; ++j) {
         const int col = n0 + wn * (BN / WN) + j * 16 + (lane & 15);
         const bool ok = col < N;
-        int E = 0, par = 0;
-        double w = 0.0;
-        if (LORENTZ) {
-            const int cc = ok ? col : 0;
-            E = cc / la.ncp;
-            const int jj = cc - E * la.ncp;
-            par = jj & 1;
-            w = la.omega[jj >> 1];
-        }
+        const int cc = ok ? col : 0, E = LORENTZ ? cc / la.ncp : 0, jj = LORENTZ ? cc - E * la.ncp : 0;
+        const Lorentz lz(LORENTZ ? la.omega[jj >> 1] : 0.0, la.eps, la.occ, jj & 1);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int rbase = m0 + wm * (BM / WM) + i * 16;
@@ -212,21 +205,7 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
             for (int r = 0; r < 4; ++r) {
                 const int row = rbase + Mma<T>::row(lane, r);
                 T v = acc[i][j][r];
-                if (LORENTZ) {
-                    // L = n [1/(w - D + i eps) - 1/(w + D + i eps)] (in FP64), applied
-                    // to the complex number held by this lane and its xor-1 partner;
-                    // the pair shares the two reciprocals (one computed by each lane).
-                    const T other = __shfl_xor(v, 1);
-                    const double D = la.Dlt[(int64_t)E * la.nv_pad + row];
-                    const double d1 = w - D, d2 = w + D, e = la.eps;
-                    const double dm = par ? d2 : d1;
-                    const double sm = 1.0 / (dm * dm + e * e), so = __shfl_xor(sm, 1);
-                    const double s1 = par ? so : sm, s2 = par ? sm : so;
-                    const double Lr = la.occ * (d1 * s1 - d2 * s2);
-                    const double Li = la.occ * (-e * s1 + e * s2);
-                    const double re = par ? (double)other : (double)v, im = par ? (double)v : (double)other;
-                    v = (T)(par ? (re * Li + im * Lr) : (re * Lr - im * Li));
-                }
+                if (LORENTZ) v = (T)lz.apply(la.Dlt[(int64_t)E * la.nv_pad + row], v, lane_pair(v));
                 // the output is read by the next kernel only: a streaming store
                 if (ok) __builtin_nontemporal_store(v, &C[(int64_t)row * ldc + col]);
             }
@@ -238,7 +217,7 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
 template <class T>
 __global__ __launch_bounds__(256)
 void k_splitk_reduce(int M, int N, int S, const T *__restrict__ part, int64_t slice,
-                     T *__restrict__ C, int ldc, int lorentz, LorentzArgs la) {
+                     T *__restrict__ C, int ldc, int factor, LorentzArgs la) {
     const int64_t npair = (int64_t)M * ((N + 1) / 2);
     for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < npair;
          idx += (int64_t)gridDim.x * 256) {
@@ -252,16 +231,11 @@ void k_splitk_reduce(int M, int N, int S, const T *__restrict__ part, int64_t sl
             re += (double)part[s2 * slice + op];
             if (two) im += (double)part[s2 * slice + op + 1];
         }
-        if (lorentz) {
+        if (factor) {
             const int E = col / la.ncp, jj = col - E * la.ncp;
-            const double w = la.omega[jj >> 1];
-            const double D = la.Dlt[(int64_t)E * la.nv_pad + row];
-            const double d1 = w - D, d2 = w + D, e = la.eps;
-            const double s1 = 1.0 / (d1 * d1 + e * e), s2 = 1.0 / (d2 * d2 + e * e);
-            const double Lr = la.occ * (d1 * s1 - d2 * s2), Li = la.occ * (-e * s1 + e * s2);
-            const double r2 = re * Lr - im * Li, i2 = re * Li + im * Lr;
-            re = r2;
-            im = i2;
+            const double D = la.Dlt[(int64_t)E * la.nv_pad + row], w = la.omega[jj >> 1], re0 = re;
+            re = Lorentz(w, la.eps, la.occ, 0).apply(D, re0, im);
+            im = Lorentz(w, la.eps, la.occ, 1).apply(D, im, re0);
         }
         C[o] = (T)re;
         if (two) C[o + 1] = (T)im;

@@ -18,9 +18,13 @@
 
 namespace chi0 {
 
-// 128x128 tiles from which those are used: about one per CU; fewer leave CUs idle and the
-// 64x64 tiles, with split-K, fill the chip
-constexpr int PANEL_BIG = 200;
+// Tiles of 128x128 from which those are used.  With half as many as CUs they
+// beat the 64x64 tiles, whose split-K then needs a reduction (chi0 in split
+// BF16, 64x64 against 128x128: 60 atoms, 12 vectors, 135 tiles 196 / 180 us;
+// 131 atoms, 5 vectors, 155 tiles 186 / 172 us; 200 atoms, 4 vectors 493 /
+// 442 us); below, the split fills the chip better (60 atoms, 4 vectors, 45
+// tiles 130 / 146 us; 100 atoms, 3 vectors, 68 tiles 139 / 154 us).
+constexpr int PANEL_BIG = 128;
 
 typedef float flt16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -61,8 +65,10 @@ __device__ __forceinline__ float panel_unbf(uint16_t h) { return __uint_as_float
 // registers that this replaces was bound by its LDS reads (a 16-byte fragment
 // per 1.5 MFMAs; here one per 1.5 MFMAs of twice the work) and ran at 0.54:
 // 400-atom transforms of 32 vectors (3200 x 128000 x 5200) 23.6 and 22.3 ms
-// before, 12.7 and 12.2 ms now; 200 atoms, 24 vectors 705 and 663 -> 516 and
-// 408 us.
+// before, 12.4 and 11.9 ms now; 200 atoms, 24 vectors 705 and 663 -> 480 and
+// 390 us.  The frequency factor costs 64 outputs per lane some 20 FP64
+// instructions each; with two divisions, LDS lane exchanges and loads between
+// the stores it was 20-25 us per launch of one round of tiles, now 8-15.
 template <int PL, int BM, int BN, int WM, int WN, int KB, bool LORENTZ>
 __global__ __launch_bounds__(WM * WN * 64)
 void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const uint4 *__restrict__ A, int lda,
@@ -175,35 +181,38 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
     for (int j = 0; j < TN; ++j) {
         const int col = n0 + wn * (BN / WN) + j * 32 + lr;
         const bool ok = col < N;
-        int E = 0, par = 0;
-        double w = 0.0;
-        if (LORENTZ) {
-            const int cc = ok ? col0 + col : 0;
-            E = cc / la.ncp;
-            const int jj = cc - E * la.ncp;
-            par = jj & 1;
-            w = la.omega[jj >> 1];
-        }
+        const int cc = ok ? col0 + col : 0, E = LORENTZ ? cc / la.ncp : 0, jj = LORENTZ ? cc - E * la.ncp : 0;
+        const Lorentz lz(LORENTZ ? la.omega[jj >> 1] : 0.0, la.eps, la.occ, jj & 1);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            // element 4 q + r: row row0 + 8 q + r, four consecutive rows (the frequency
+            // factor's M is a multiple of 64)
+            const int row0 = m0 + wm * (BM / WM) + i * 32 + 4 * lk;
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
+            if (LORENTZ) {
+                // the transition energies of the 16 rows first: loaded between the
+                // stores each would wait for a memory latency of its own
+                double2 D[8];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int row = row0 + 8 * q;
+                    const double2 *d = reinterpret_cast<const double2 *>(la.Dlt + (int64_t)E * la.nv_pad +
+                                                                         (row < M ? row : 0));
+                    D[2 * q] = d[0];
+                    D[2 * q + 1] = d[1];
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    v[r] = (float)lz.apply(r & 1 ? D[r / 2].y : D[r / 2].x, v[r], lane_pair(v[r]));
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm * (BM / WM) + i * 32 + 8 * (r / 4) + 4 * lk + r % 4;
-                float v = acc[i][j][r];
-                if (LORENTZ) {
-                    const float other = __shfl_xor(v, 1);
-                    const double D = la.Dlt[(int64_t)E * la.nv_pad + (row < M ? row : 0)];
-                    const double d1 = w - D, d2 = w + D, e = la.eps;
-                    const double dm = par ? d2 : d1;   // the Re / Im pair shares the two reciprocals
-                    const double sm = 1.0 / (dm * dm + e * e), so = __shfl_xor(sm, 1);
-                    const double f1 = par ? so : sm, f2 = par ? sm : so;
-                    const double Lr = la.occ * (d1 * f1 - d2 * f2);
-                    const double Li = la.occ * (-e * f1 + e * f2);
-                    const double re = par ? other : v, im = par ? v : other;
-                    v = (float)(par ? (re * Li + im * Lr) : (re * Lr - im * Li));
-                }
-                if (ok && row < M) __builtin_nontemporal_store(v, &C[(int64_t)row * ldc + col]);
+                const int row = row0 + 8 * (r / 4) + r % 4;
+                if (ok && row < M) __builtin_nontemporal_store(v[r], &C[(int64_t)row * ldc + col]);
             }
+        }
     }
 }
 
