@@ -52,7 +52,9 @@ extern "C" {
  * The vertex contractions, the frequency factor, K, Gram-Schmidt, the
  * Hessenberg problem and the true residual are always FP64.
  *   FP64    every transform on FP64 matrix cores.
- *   FP32    transforms on FP32 matrix cores, FP32 intermediates.
+ *   FP32    transforms on FP32 operands with FP32 accumulation, FP32 intermediates
+ *           (dense ones: each operand as three BF16 terms, which hold it whole,
+ *           six BF16 products).
  *   BF16X3  the two dense virtual-orbital transforms as split BF16 x 3 (each
  *           operand x = bf16 hi + bf16 lo, three BF16 products, FP32
  *           accumulation); the block-sparse occupied transforms in FP32. */

@@ -180,7 +180,7 @@ struct chi0_ctx {
         apply_seen = ApplyKey{};
     }
     // low-precision operator: operand copies (set_system)
-    float *Xo32 = nullptr, *Xv32 = nullptr, *Xvt32 = nullptr;
+    float *Xo32 = nullptr;
     PanelDev Xv_bf, Xvt_bf;   // BF16 panels: rows = atomic orbitals (b3), rows = virtual states (b2)
 
     // partial reorthogonalisation with kernel timing on: per step, whether the
@@ -668,14 +668,10 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
         HIPCHK(c, hipMemcpy(c->Dlt, dl.data(), dl.size() * 8, hipMemcpyHostToDevice));
         // operand copies of the low-precision operator
         CHK(dalloc(c, sb, &c->Xo32, (int64_t)xo.size()));
-        CHK(dalloc(c, sb, &c->Xv32, (int64_t)xv.size()));
-        CHK(dalloc(c, sb, &c->Xvt32, (int64_t)xvt.size()));
         CHK(panel_alloc(c, sb, c->Xvt_bf, Nv, N));
         CHK(panel_alloc(c, sb, c->Xv_bf, N, Nv));
         HIPCHK(c, hipDeviceSynchronize());
         launch_to_f32(nullptr, c->Xo, c->Xo32, (int64_t)xo.size());
-        launch_to_f32(nullptr, c->Xv, c->Xv32, (int64_t)xv.size());
-        launch_to_f32(nullptr, c->Xvt, c->Xvt32, (int64_t)xvt.size());
         launch_panel_bf16(nullptr, c->Xv, N, Nv, c->Nv_pad, &c->Xvt_bf);
         launch_panel_bf16(nullptr, c->Xvt, Nv, N, c->N_pad, &c->Xv_bf);
         HIPCHK(c, hipGetLastError());
@@ -816,21 +812,15 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
         LorentzArgs la{c->Dlt, omega, c->Nv_pad, nc, eps, c->occ};
         const size_t sb = o.gemm_scratch_n * sizeof(double);
         const double by = 4.0 * (w.N * w.No * nc + w.Nv * w.No * nc);
-        if (prec == CHI0_PREC_FP32) {
-            launch_sgemm(t, s, "virt_transform_lorentz_f32", c->Nv_pad, ncol, c->N_pad, c->Xvt32,
-                         c->N_pad, o.Tt32, (int)mcol, o.at32, (int)mcol, fl + 6.0 * w.No * w.Nv * nb,
-                         by + 4.0 * w.N * w.Nv, &la, o.gemm_scratch, sb, tu);
-            launch_sgemm(t, s, "virt_back_f32", c->N_pad, ncol, c->Nv_pad, c->Xv32, c->Nv_pad,
-                         o.at32, (int)mcol, o.Ut32, (int)mcol, fl, by + 4.0 * w.N * w.Nv, nullptr,
-                         o.gemm_scratch, sb, tu);
-        } else {   // split BF16 x 3: three BF16 products per multiply-add
-            launch_panel_gemm_bf16x3(t, s, "virt_transform_lorentz_bf16x3", c->Nv_pad, ncol, c->N, c->Xvt_bf,
-                                     o.Tt32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb, o.at32, (int)mcol,
-                                     3.0 * fl, by + 4.0 * w.N * w.Nv, &la);
-            launch_panel_gemm_bf16x3(t, s, "virt_back_bf16x3", c->N_pad, ncol, c->Nv, c->Xv_bf, o.at32, mcol, o.panel,
-                                     o.panel_bytes, o.gemm_scratch, sb, o.Ut32, (int)mcol, 3.0 * fl,
-                                     by + 4.0 * w.N * w.Nv, nullptr);
-        }
+        // FP32: six BF16 products per multiply-add, split BF16 x 3: three
+        const bool f32 = prec == CHI0_PREC_FP32;
+        const double fe = (f32 ? 1.0 : 3.0) * fl;   // the record's operations: FP32 ones, or the BF16 ones executed
+        launch_panel_gemm(t, s, f32 ? "virt_transform_lorentz_f32" : "virt_transform_lorentz_bf16x3", f32 ? 3 : 2,
+                          c->Nv_pad, ncol, c->N, c->Xvt_bf, o.Tt32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb,
+                          o.at32, (int)mcol, fe + (f32 ? 6.0 * w.No * w.Nv * nb : 0.0), by + 4.0 * w.N * w.Nv, &la);
+        launch_panel_gemm(t, s, f32 ? "virt_back_f32" : "virt_back_bf16x3", f32 ? 3 : 2, c->N_pad, ncol, c->Nv,
+                          c->Xv_bf, o.at32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb, o.Ut32, (int)mcol, fe,
+                          by + 4.0 * w.N * w.Nv, nullptr);
         launch_occ_back_f32(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo32, c->No_pad, c->No16, o.Ut32, o.W, nc, w);
     }
     launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod);
@@ -2080,7 +2070,8 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     if (!c) return CHI0_EINVAL;
     if (c->device < 0) return fail(c, CHI0_ENOSYS, "no device context");
     if (M < 1 || N < 1 || K < 1 || !A || !B || !C) return fail(c, CHI0_EINVAL, "bad sizes or NULL");
-    if (precision != CHI0_PREC_BF16X3) return fail(c, CHI0_EINVAL, "no panel GEMM for this precision");
+    if (precision != CHI0_PREC_FP32 && precision != CHI0_PREC_BF16X3)
+        return fail(c, CHI0_EINVAL, "no panel GEMM for this precision");
     HIPCHK(c, hipSetDevice(c->device));
     struct Scope {
         DevBuf buf;
@@ -2108,8 +2099,8 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     HIPCHK(c, hipMemcpy(b_d, b32.data(), kn * 4, hipMemcpyHostToDevice));
     launch_panel_bf16(c->stream, a_d, K, M, M, &p);
     HIPCHK(c, hipDeviceSynchronize());   // the copies above are on the default stream
-    launch_panel_gemm_bf16x3(nullptr, c->stream, "panel", M, N, K, p, b_d, N, work, (size_t)(work_bytes / 8 * 8),
-                             scratch, scratch_n * sizeof(double), c_d, N, 0.0, 0.0, nullptr);
+    launch_panel_gemm(nullptr, c->stream, "panel", precision == CHI0_PREC_FP32 ? 3 : 2, M, N, K, p, b_d, N, work,
+                      (size_t)(work_bytes / 8 * 8), scratch, scratch_n * sizeof(double), c_d, N, 0.0, 0.0, nullptr);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpy(c32.data(), c_d, mn * 4, hipMemcpyDeviceToHost));

@@ -170,17 +170,13 @@ void launch_dgemm_lorentz(Tracer *t, hipStream_t s, int M, int N, int K, int kpa
                           const double *Dlt, int nv_pad, const double *omega, double eps,
                           double occ, int ncp, double flops, double bytes, double *scratch,
                           size_t scratch_doubles, GemmTuner *tu = nullptr);
-// Low-precision operator: FP32 gathered transforms, FP32 or split-BF16x3 dense transforms.
+// Low-precision operator: FP32 gathered transforms, dense transforms on BF16 panels.
 void launch_occ_transform_f32(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
                               const float *Xo, int no_pad, const double *dV, float *Tt,
                               int nc, const WorkSizes &ws);
 void launch_occ_back_f32(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms, int max_rows,
                          const float *Xo, int no_pad, int no_sum, const float *Ut, double *W, int nc,
                          const WorkSizes &ws);
-void launch_sgemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K,
-                  const float *A, int lda, const float *B, int ldb, float *C, int ldc,
-                  double flops, double bytes, const LorentzArgs *la, void *scratch,
-                  size_t scratch_bytes, GemmTuner *tu = nullptr);
 // An operand of the panel GEMMs (kernels_panel.hip): planes of 16-byte k-blocks,
 // block kb of row r at uint4 number kb * ld + r of a plane of `plane` uint4s.
 struct PanelDev {
@@ -191,16 +187,15 @@ struct PanelDev {
 };
 constexpr int PANEL_LD = 128;   // rows of an operand: whole GEMM tiles
 constexpr int PANEL_KB = 4;     // k-blocks of an operand: whole GEMM stages
-constexpr int PANEL_BF = 2;     // BF16 planes kept of the orbital matrices
+constexpr int PANEL_BF = 3;     // BF16 planes kept of the orbital matrices
 // planes of X [K][ldx] (N columns = the operand's rows); p->nkb, ld, plane set
 void launch_panel_bf16(hipStream_t s, const double *X, int K, int N, int64_t ldx, PanelDev *p);
-// C = A B in split BF16 x 3, B [K][ldb] FP32; `work` takes B's panels, as many
-// columns at a time as fit (at least PANEL_LD; all of N where N is small enough
-// for split-K, whose partial sums go to `scratch`).
-void launch_panel_gemm_bf16x3(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const PanelDev &A,
-                              const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
-                              size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
-                              const LorentzArgs *la);
+// C = A B, B [K][ldb] FP32, with 2 (split BF16 x 3) or 3 (FP32) planes of
+// each operand; `work` takes B's panels, as many columns at a time as fit (at
+// least PANEL_LD), `scratch` (may be NULL) the partial sums of split-K.
+void launch_panel_gemm(Tracer *t, hipStream_t s, const char *name, int planes, int M, int N, int K,
+                       const PanelDev &A, const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
+                       size_t scratch_bytes, float *C, int ldc, double flops, double bytes, const LorentzArgs *la);
 // C = sum of S FP32 slices of M x N (+ the frequency factor if la)
 void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, const float *part,
                               float *C, int ldc, const LorentzArgs *la);

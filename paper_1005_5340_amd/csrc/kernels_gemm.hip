@@ -1,5 +1,6 @@
 // Matrix-core kernels of the orbital transforms (Sec. 4.2, Table t:flops steps
-// 2-5) and the kernel matrix-vector product (Sec. 4.1), for FP64 and FP32.
+// 2-5) and the kernel matrix-vector product (Sec. 4.1): the FP64 dense GEMMs
+// and the gathered occupied transforms in FP64 and FP32.
 //
 // A 16 x 16 output tile per K step of 4 on 64-lane wavefronts, lane l = 0..63:
 //   B (4 x 16):  lane l holds B[l / 16][l % 16]
@@ -25,8 +26,7 @@ typedef float flt4 __attribute__((ext_vector_type(4)));
 
 // NA A fragments per 16 x 16 tile and K step; a_row(l, r) is the tile row
 // that lane l supplies in fragment r.
-template <class T> struct Mma;
-template <> struct Mma<double> {
+struct Mma4 {
     typedef dbl4 acc;
     static constexpr int NA = 4;
     static __device__ __forceinline__ acc zero() { return acc{0.0, 0.0, 0.0, 0.0}; }
@@ -52,7 +52,7 @@ struct Mma16d {
     }
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
 };
-template <> struct Mma<float> {
+struct Mma16f {
     typedef flt4 acc;
     static constexpr int NA = 1;
     static __device__ __forceinline__ acc zero() { return acc{0.f, 0.f, 0.f, 0.f}; }
@@ -92,10 +92,10 @@ __device__ __forceinline__ int xcd_remap(int wid, int n) {
 // The tile shape (BM x BN, WM x WN wavefronts) changes only which workgroup
 // computes an element, never the order of its k accumulation, so every tile
 // variant gives bit-identical results and the autotuner may pick any of them.
-template <class T, int BM, int BN, int WM, int WN, bool LORENTZ, int BK = 16>
+template <int BM, int BN, int WM, int WN, bool LORENTZ, int BK = 16>
 __global__ __launch_bounds__(WM * WN * 64)
-void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
-             const T *__restrict__ B, int ldb, T *__restrict__ C, int ldc,
+void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
+             const double *__restrict__ B, int ldb, double *__restrict__ C, int ldc,
              int m_fastest, LorentzArgs la) {
     A += (int64_t)blockIdx.y * K;
     B += (int64_t)blockIdx.y * K * ldb;
@@ -107,8 +107,8 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
     constexpr int CB = BK * (BN / 4) / NT;   // 4-element B chunks per thread per tile
     static_assert(CA >= 1 && CB >= 1 && CA * NT == BM * (BK / 4) && CB * NT == BK * (BN / 4),
                   "tile shape must split into whole 4-element chunks per thread");
-    __shared__ T As[2][BK][BM + 1];
-    __shared__ T Bs[2][BK][BN];
+    __shared__ double As[2][BK][BM + 1];
+    __shared__ double Bs[2][BK][BN];
 
     const int ntm = M / BM, ntn = (N + BN - 1) / BN;
     const int tile = xcd_remap(blockIdx.x, ntm * ntn);
@@ -133,18 +133,18 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
         b_n[q] = (ch % (BN / 4)) * 4;
     }
 
-    T ra[CA][4], rb[CB][4];
+    double ra[CA][4], rb[CB][4];
     auto load = [&](int kt) {
 #pragma unroll
         for (int q = 0; q < CA; ++q) load4(A + (int64_t)(m0 + a_row[q]) * lda + kt * BK + a_k[q], ra[q]);
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
-            const T *bp = B + (int64_t)(kt * BK + b_k[q]) * ldb + n0 + b_n[q];
+            const double *bp = B + (int64_t)(kt * BK + b_k[q]) * ldb + n0 + b_n[q];
             if (n0 + b_n[q] + 3 < N) {
                 load4(bp, rb[q]);
             } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) rb[q][c] = (n0 + b_n[q] + c < N) ? bp[c] : T(0);
+                for (int c = 0; c < 4; ++c) rb[q][c] = (n0 + b_n[q] + c < N) ? bp[c] : 0.0;
             }
         }
     };
@@ -159,11 +159,11 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
             for (int c = 0; c < 4; ++c) Bs[buf][b_k[q]][b_n[q] + c] = rb[q][c];
     };
 
-    typename Mma<T>::acc acc[TM][TN];
+    Mma4::acc acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = Mma<T>::zero();
+        for (int j = 0; j < TN; ++j) acc[i][j] = Mma4::zero();
 
     const int KT = K / BK;
     load(0);
@@ -175,18 +175,18 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
 #pragma unroll
         for (int ks = 0; ks < BK / 4; ++ks) {
             const int kk = ks * 4 + lane / 16;
-            T af[TM][Mma<T>::NA], bf[TN];
+            double af[TM][Mma4::NA], bf[TN];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int r = 0; r < Mma<T>::NA; ++r)
-                    af[i][r] = As[cur][kk][wm * (BM / WM) + i * 16 + Mma<T>::a_row(lane, r)];
+                for (int r = 0; r < Mma4::NA; ++r)
+                    af[i][r] = As[cur][kk][wm * (BM / WM) + i * 16 + Mma4::a_row(lane, r)];
 #pragma unroll
             for (int j = 0; j < TN; ++j) bf[j] = Bs[cur][kk][wn * (BN / WN) + j * 16 + (lane & 15)];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = Mma<T>::op(af[i], bf[j], acc[i][j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] = Mma4::op(af[i], bf[j], acc[i][j]);
         }
         if (kt + 1 < KT) store(cur ^ 1);
         __syncthreads();
@@ -203,9 +203,9 @@ void k_dgemm(int M, int N, int K, const T *__restrict__ A, int lda,
             const int rbase = m0 + wm * (BM / WM) + i * 16;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = rbase + Mma<T>::row(lane, r);
-                T v = acc[i][j][r];
-                if (LORENTZ) v = (T)lz.apply(la.Dlt[(int64_t)E * la.nv_pad + row], v, lane_pair(v));
+                const int row = rbase + Mma4::row(lane, r);
+                double v = acc[i][j][r];
+                if (LORENTZ) v = lz.apply(la.Dlt[(int64_t)E * la.nv_pad + row], v, lane_pair(v));
                 // the output is read by the next kernel only: a streaming store
                 if (ok) __builtin_nontemporal_store(v, &C[(int64_t)row * ldc + col]);
             }
@@ -281,50 +281,50 @@ GemmTuner::~GemmTuner() {
         if (e) (void)hipEventDestroy(e);
 }
 
-template <class T, bool LZ>
-static void launch_variant(int v, hipStream_t s, dim3 grid_s, int M, int N, int K, const T *A, int lda,
-                           const T *B, int ldb, T *C, int ldc, int m_fastest, const LorentzArgs &la) {
+template <bool LZ>
+static void launch_variant(int v, hipStream_t s, dim3 grid_s, int M, int N, int K, const double *A, int lda,
+                           const double *B, int ldb, double *C, int ldc, int m_fastest, const LorentzArgs &la) {
     const int S = grid_s.y;
     auto tiles = [&](int bm, int bn) { return (unsigned)((M / bm) * ((N + bn - 1) / bn)); };
     switch (v) {
     case 1:
-        hipLaunchKernelGGL((k_dgemm<T, 64, 128, 2, 2, LZ>), dim3(tiles(64, 128), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<64, 128, 2, 2, LZ>), dim3(tiles(64, 128), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     case 2:
-        hipLaunchKernelGGL((k_dgemm<T, 128, 64, 2, 2, LZ>), dim3(tiles(128, 64), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<128, 64, 2, 2, LZ>), dim3(tiles(128, 64), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     case 3:
-        hipLaunchKernelGGL((k_dgemm<T, 128, 128, 2, 2, LZ>), dim3(tiles(128, 128), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<128, 128, 2, 2, LZ>), dim3(tiles(128, 128), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     case 4:
-        hipLaunchKernelGGL((k_dgemm<T, 64, 64, 2, 2, LZ, 32>), dim3(tiles(64, 64), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<64, 64, 2, 2, LZ, 32>), dim3(tiles(64, 64), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     case 5:
-        hipLaunchKernelGGL((k_dgemm<T, 64, 128, 2, 2, LZ, 32>), dim3(tiles(64, 128), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<64, 128, 2, 2, LZ, 32>), dim3(tiles(64, 128), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     default:
-        hipLaunchKernelGGL((k_dgemm<T, 64, 64, 2, 2, LZ>), dim3(tiles(64, 64), S), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_dgemm<64, 64, 2, 2, LZ>), dim3(tiles(64, 64), S), dim3(256), 0, s,
                            M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         break;
     }
 }
 
 // Variant for this call: the tuned one for its key, tuning first if the key is new.
-template <class T, bool LZ>
+template <bool LZ>
 static int pick_variant(GemmTuner *tu, hipStream_t s, const char *name, int S, int M, int N, int K,
-                        const T *A, int lda, const T *B, int ldb, T *C, int ldc, int m_fastest,
+                        const double *A, int lda, const double *B, int ldb, double *C, int ldc, int m_fastest,
                         const LorentzArgs &la) {
     if (!tu) return 0;
     if (tu->force >= 0 && tu->force < GEMM_VARIANTS)
         return (M % kVarBM[tu->force] == 0 && K % kVarBK[tu->force] == 0) ? tu->force : 0;
     if (!tu->enabled) return 0;
     const int nb = (int)std::floor(2.0 * std::log2((double)std::max(N, 1)));
-    const std::string key = std::string(name) + (sizeof(T) == 8 ? "" : "_f32") + " M=" + std::to_string(M) +
+    const std::string key = std::string(name) + " M=" + std::to_string(M) +
                             " K=" + std::to_string(K * S) + " S=" + std::to_string(S) + " N~2^" +
                             std::to_string(nb / 2) + (nb % 2 ? ".5" : "");
     auto it = tu->table.find(key);
@@ -335,12 +335,12 @@ static int pick_variant(GemmTuner *tu, hipStream_t s, const char *name, int S, i
     float best = 0.f;
     for (int v = 0; v < GEMM_VARIANTS; ++v) {
         if (M % kVarBM[v] != 0 || K % kVarBK[v] != 0) continue;
-        launch_variant<T, LZ>(v, s, dim3(1, S), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+        launch_variant<LZ>(v, s, dim3(1, S), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         // best of three timed launches: one launch's time varies by several per cent
         float tmin = 0.f;
         for (int rep = 0; rep < 3; ++rep) {
             (void)hipEventRecord(tu->ev[0], s);
-            launch_variant<T, LZ>(v, s, dim3(1, S), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+            launch_variant<LZ>(v, s, dim3(1, S), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
             (void)hipEventRecord(tu->ev[1], s);
             float ms = 0.f;
             if (hipEventSynchronize(tu->ev[1]) != hipSuccess ||
@@ -358,41 +358,40 @@ static int pick_variant(GemmTuner *tu, hipStream_t s, const char *name, int S, i
     return e.variant;
 }
 
-template <class T>
 static void gemm_any(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, int kpad,
-                     const T *A, int lda, const T *B, int ldb, T *C, int ldc,
+                     const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                      double flops, double bytes, bool lorentz, const LorentzArgs &la,
                      void *scratch, size_t scratch_bytes, GemmTuner *tu) {
     int ks = K;
-    const int S = scratch ? choose_splits(M, N, K, kpad, scratch_bytes / sizeof(T), &ks) : 1;
+    const int S = scratch ? choose_splits(M, N, K, kpad, scratch_bytes / sizeof(double), &ks) : 1;
     const int m_fastest = (M / 64) <= ((N + 63) / 64);
     if (S == 1) {
         if (lorentz) {
-            const int v = pick_variant<T, true>(tu, s, name, 1, M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+            const int v = pick_variant<true>(tu, s, name, 1, M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
             trace_begin(t, name, s);
-            launch_variant<T, true>(v, s, dim3(1, 1), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+            launch_variant<true>(v, s, dim3(1, 1), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         } else {
-            const int v = pick_variant<T, false>(tu, s, name, 1, M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+            const int v = pick_variant<false>(tu, s, name, 1, M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
             trace_begin(t, name, s);
-            launch_variant<T, false>(v, s, dim3(1, 1), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
+            launch_variant<false>(v, s, dim3(1, 1), M, N, K, A, lda, B, ldb, C, ldc, m_fastest, la);
         }
         trace_end(t, s, flops, bytes);
         return;
     }
     // partial products with ldc = N into scratch, then the reduction (+ epilogue)
-    T *part = static_cast<T *>(scratch);
-    const int v = pick_variant<T, false>(tu, s, name, S, M, N, ks, A, lda, B, ldb, part, N, m_fastest, la);
+    double *part = static_cast<double *>(scratch);
+    const int v = pick_variant<false>(tu, s, name, S, M, N, ks, A, lda, B, ldb, part, N, m_fastest, la);
     trace_begin(t, name, s);
-    launch_variant<T, false>(v, s, dim3(1, S), M, N, ks, A, lda, B, ldb, part, N, m_fastest, la);
+    launch_variant<false>(v, s, dim3(1, S), M, N, ks, A, lda, B, ldb, part, N, m_fastest, la);
     trace_end(t, s, flops, bytes);
-    reduce_splits<T>(t, s, M, N, S, part, C, ldc, lorentz, la);
+    reduce_splits<double>(t, s, M, N, S, part, C, ldc, lorentz, la);
 }
 
 void launch_dgemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, int kpad,
                   const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                   double flops, double bytes, double *scratch, size_t scratch_doubles, GemmTuner *tu) {
     LorentzArgs la{};
-    gemm_any<double>(t, s, name, M, N, K, kpad, A, lda, B, ldb, C, ldc, flops, bytes, false, la, scratch,
+    gemm_any(t, s, name, M, N, K, kpad, A, lda, B, ldb, C, ldc, flops, bytes, false, la, scratch,
                      scratch_doubles * sizeof(double), tu);
 }
 
@@ -402,7 +401,7 @@ void launch_dgemm_lorentz(Tracer *t, hipStream_t s, int M, int N, int K, int kpa
                           double occ, int ncp, double flops, double bytes, double *scratch,
                           size_t scratch_doubles, GemmTuner *tu) {
     LorentzArgs la{Dlt, omega, nv_pad, ncp, eps, occ};
-    gemm_any<double>(t, s, "virt_transform_lorentz", M, N, K, kpad, A, lda, B, ldb, C, ldc, flops, bytes,
+    gemm_any(t, s, "virt_transform_lorentz", M, N, K, kpad, A, lda, B, ldb, C, ldc, flops, bytes,
                      true, la, scratch, scratch_doubles * sizeof(double), tu);
 }
 
@@ -412,17 +411,9 @@ void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, con
     reduce_splits<float>(t, s, M, N, S, part, C, ldc, la != nullptr, la ? *la : none);
 }
 
-void launch_sgemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K,
-                  const float *A, int lda, const float *B, int ldb, float *C, int ldc,
-                  double flops, double bytes, const LorentzArgs *la, void *scratch,
-                  size_t scratch_bytes, GemmTuner *tu) {
-    LorentzArgs none{};
-    gemm_any<float>(t, s, name, M, N, K, K, A, lda, B, ldb, C, ldc, flops, bytes, la != nullptr,
-                    la ? *la : none, scratch, scratch_bytes, tu);
-}
-
-template <class T> struct OccMma { typedef Mma<T> type; };
+template <class T> struct OccMma;
 template <> struct OccMma<double> { typedef Mma16d type; };
+template <> struct OccMma<float> { typedef Mma16f type; };
 
 // ------------------------------------------------------- (b1) occupied transform
 // The gathered transforms multiply by one atom's orbitals b at a time, for every

@@ -27,7 +27,9 @@ namespace chi0 {
 constexpr int PANEL_BIG = 128;
 
 typedef float flt16 __attribute__((ext_vector_type(16)));
+typedef float flt2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 #define CHI0_GLOBAL __attribute__((address_space(1)))
 #define CHI0_LDS __attribute__((address_space(3)))
@@ -39,14 +41,30 @@ __device__ __forceinline__ int panel_xcd(int wid, int n) {
     return x * q + (x < r ? x : r) + local;
 }
 
-__device__ __forceinline__ uint16_t panel_bf(float x) {   // round to nearest even
-    const uint32_t u = __float_as_uint(x);
-    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+// One k-block of 8 values as PL planes: bf16(x), then one BF16 of what the
+// planes before leave (all to nearest even); x is overwritten.
+template <int PL>
+__device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+        uint32_t w[4];
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) {
+            const bf16x2 h = __builtin_convertvector((flt2{x[c], x[c + 1]}), bf16x2);
+            w[c / 2] = __builtin_bit_cast(uint32_t, h);
+            x[c] -= __uint_as_float(w[c / 2] << 16);
+            x[c + 1] -= __uint_as_float(w[c / 2] & 0xFFFF0000u);
+        }
+        out[pl] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
 }
-__device__ __forceinline__ float panel_unbf(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // C [M][ldc] (FP32) = A B, A and B as PL planes of BF16 (hi, then the
-// rounded remainders): PL = 2 sums lo hi + hi lo + hi hi.
+// rounded remainders).  PL = 2 (split BF16 x 3) sums lo hi + hi lo + hi hi,
+// which drops parts of 2^-17 of a product.  PL = 3 holds an FP32 value whole
+// (3 x 8 bits) and sums the six products of planes x + y <= 2, smallest
+// first: the rest is below 2^-25 of a product, under the rounding of the
+// FP32 accumulation.
 //
 // A workgroup computes a BM x BN tile with WM x WN wavefronts of 32x32 MFMA
 // tiles.  KB k-blocks of both operands make one stage; two stages of LDS are
@@ -69,11 +87,22 @@ __device__ __forceinline__ float panel_unbf(uint16_t h) { return __uint_as_float
 // 390 us.  The frequency factor costs 64 outputs per lane some 20 FP64
 // instructions each; with two divisions, LDS lane exchanges and loads between
 // the stores it was 20-25 us per launch of one round of tiles, now 8-15.
-template <int PL, int BM, int BN, int WM, int WN, int KB, bool LORENTZ>
+//
+// RAW takes B as it is, FP32 [K][ldb], and cuts it into planes on the way to
+// LDS: each thread loads the 8 values of one k-block of one column a stage
+// ahead and stores its planes before the workgroup meets.  Every row of tiles
+// cuts B again, so it is for few rows of tiles, where it saves a launch
+// (3-5 us of a 45-130 us chi0).
+//
+// PL = 3 replaces FP32 MFMA (157 TFLOP/s peak, 75-82 reached): chi0 in FP32
+// 131 atoms, 24 vectors 611 -> 479 us, 200 atoms, 24 vectors 3.31 -> 2.57 ms,
+// 400 atoms, 8 vectors 19.5 -> 14.0 ms; its error against 64 bits is a tenth
+// smaller (4.3e-7 -> 3.8e-7 of chi0 z).
+template <int PL, int BM, int BN, int WM, int WN, int KB, bool LORENTZ, bool RAW>
 __global__ __launch_bounds__(WM * WN * 64)
-void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const uint4 *__restrict__ A, int lda,
-                  int64_t apl, const uint4 *__restrict__ B, int ldb, int64_t bpl, float *__restrict__ C, int ldc,
-                  int col0, LorentzArgs la) {
+void k_panel_gemm(int M, int N, int K, int ntm, int ntn, int nkb, int nkb_split, const uint4 *__restrict__ A,
+                  int lda, int64_t apl, const void *__restrict__ Bv, int64_t ldb, int64_t bpl, float *__restrict__ C,
+                  int ldc, int col0, LorentzArgs la) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int SA = KB * BM, SB = KB * BN, KS = KB / 2;
@@ -85,7 +114,11 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
     const int wm = wv % WM, wn = wv / WM, lr = lane & 31, lk = lane >> 5;
     const int kb0 = blockIdx.y * nkb_split, KT = min(nkb_split, nkb - kb0) / KB;
     A += (int64_t)kb0 * lda + m0;
-    B += (int64_t)kb0 * ldb + n0;
+    const uint4 *B = static_cast<const uint4 *>(Bv) + (int64_t)kb0 * ldb + n0;
+    const float *Braw = static_cast<const float *>(Bv) + n0 + t % BN;   // RAW: this thread's column
+    static_assert(!RAW || SB == NT, "one k-block of B per thread");
+    const bool raw_ok = RAW && n0 + t % BN < N;
+    float rb[8];
     C += (int64_t)blockIdx.y * M * ldc;
 
     auto load = [&](uint4 *dst, int kt) {
@@ -99,7 +132,7 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
                                                  (CHI0_LDS void *)(dst + pl * SA + c * NT + wv * 64), 16, 0, 0);
             }
 #pragma unroll
-            for (int c = 0; c < SB / NT; ++c) {
+            for (int c = 0; c < (RAW ? 0 : SB / NT); ++c) {
                 const int ch = c * NT + t;
                 const uint4 *g = B + pl * bpl + (int64_t)(kt * KB + ch / BN) * ldb + ch % BN;
                 __builtin_amdgcn_global_load_lds((const CHI0_GLOBAL void *)g,
@@ -107,6 +140,17 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
                                                  0, 0);
             }
         }
+    };
+    auto load_raw = [&](int kt) {
+        const int k0 = (kb0 + kt * KB + t / BN) * 8;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) rb[c] = (raw_ok && k0 + c < K) ? Braw[(int64_t)(k0 + c) * ldb] : 0.f;
+    };
+    auto store_raw = [&](uint4 *dst) {
+        uint4 w[PL];
+        panel_cut<PL>(rb, w);
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) dst[PL * SA + pl * SB + t] = w[pl];
     };
     flt16 acc[TM][TN];
 #pragma unroll
@@ -138,6 +182,11 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
                                                                         __builtin_bit_cast(bf16x8, fb[w][y][j]),
                                                                         acc[i][j], 0, 0, 0);
                 };
+                if constexpr (PL == 3) {
+                    mm(2, 0);
+                    mm(0, 2);
+                    mm(1, 1);
+                }
                 mm(1, 0);
                 mm(0, 1);
                 mm(0, 0);
@@ -159,16 +208,27 @@ void k_panel_gemm(int M, int N, int ntm, int ntn, int nkb, int nkb_split, const 
             mma((w0 + ks) & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (RAW && kt + 1 < KT) store_raw(const_cast<uint4 *>(nxt));
         meet();
-        if (kt + 2 < KT) load(cur, kt + 2);
+        if (kt + 2 < KT) {
+            load(cur, kt + 2);
+            if (RAW) load_raw(kt + 2);
+        }
         read((w0 + KS) & 1, nxt, 0);
         __builtin_amdgcn_sched_barrier(0);
         mma((w0 + KS - 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
     };
     load(s0, 0);
+    if (RAW) {
+        load_raw(0);
+        store_raw(s0);
+    }
     meet();
-    if (KT > 1) load(s1, 1);
+    if (KT > 1) {
+        load(s1, 1);
+        if (RAW) load_raw(1);
+    }
     read(0, s0, 0);
     int kt = 0;
     for (; kt + 2 <= KT; kt += 2) {
@@ -233,18 +293,10 @@ void k_panel_split(const T *__restrict__ X, int K, int N, int64_t ldx, int nkb, 
             const int k = kb * 8 + c;
             x[c] = (n < N && k < K) ? (float)X[(int64_t)k * ldx + n] : 0.f;
         }
+        uint4 w[PL];
+        panel_cut<PL>(x, w);
 #pragma unroll
-        for (int pl = 0; pl < PL; ++pl) {
-            uint32_t w[4];
-#pragma unroll
-            for (int c = 0; c < 8; c += 2) {
-                const uint16_t h0 = panel_bf(x[c]), h1 = panel_bf(x[c + 1]);
-                x[c] -= panel_unbf(h0);
-                x[c + 1] -= panel_unbf(h1);
-                w[c / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            }
-            out[pl * plane + idx] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
+        for (int pl = 0; pl < PL; ++pl) out[pl * plane + idx] = w[pl];
     }
 }
 
@@ -266,13 +318,13 @@ void launch_panel_bf16(hipStream_t s, const double *X, int K, int N, int64_t ldx
     split_any<PANEL_BF, double>(s, X, K, N, ldx, p->nkb, p->ld, reinterpret_cast<uint4 *>(p->data), p->plane);
 }
 
-template <int PL, int BM, int BN, bool LORENTZ>
-static void panel_launch(hipStream_t s, int M, int N, int S, int nkb_split, const PanelDev &A, const uint4 *B,
-                         int ldb, float *C, int ldc, int col0, const LorentzArgs &la) {
+template <int PL, int BM, int BN, bool LORENTZ, bool RAW>
+static void panel_launch(hipStream_t s, int M, int N, int K, int S, int nkb_split, const PanelDev &A, const void *B,
+                         int64_t ldb, float *C, int ldc, int col0, const LorentzArgs &la) {
     const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
-    hipLaunchKernelGGL((k_panel_gemm<PL, BM, BN, 2, 2, PANEL_KB, LORENTZ>), dim3(ntm * ntn, S), dim3(256), 0, s, M,
-                       N, ntm, ntn, A.nkb, nkb_split, reinterpret_cast<const uint4 *>(A.data), A.ld, A.plane, B, ldb,
-                       (int64_t)A.nkb * ldb, C, ldc, col0, la);
+    hipLaunchKernelGGL((k_panel_gemm<PL, BM, BN, 2, 2, PL * BM <= 256 ? 4 : 2, LORENTZ, RAW>), dim3(ntm * ntn, S),
+                       dim3(256), 0, s, M, N, K, ntm, ntn, A.nkb, nkb_split, reinterpret_cast<const uint4 *>(A.data),
+                       A.ld, A.plane, B, ldb, (int64_t)A.nkb * ldb, C, ldc, col0, la);
 }
 
 template <int PL>
@@ -281,20 +333,32 @@ static void panel_gemm_any(Tracer *t, hipStream_t s, const char *name, int M, in
                            size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
                            const LorentzArgs *la) {
     const int nkb = A.nkb, KT = nkb / PANEL_KB;
-    uint4 *bp = static_cast<uint4 *>(work);
     const LorentzArgs none{};
-    const int64_t big = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-    const int64_t small = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-    int S = 1;   // k splits of the small tiles, each at least 4 stages
-    // columns whose B panels fit the workspace at once
-    const int64_t fit = (int64_t)(work_bytes / ((size_t)PL * nkb * 16)) / PANEL_LD * PANEL_LD;
-    if (scratch && big < PANEL_BIG && fit >= N)
-        while (S < 16 && small * S < 1024 && KT / (2 * S) >= 4 &&
+    if ((int64_t)((M + 127) / 128) * ((N + 127) / 128) < PANEL_BIG) {
+        // 64x64 tiles, B cut in the kernel; k splits of at least 4 stages
+        const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+        int S = 1;
+        while (scratch && S < 16 && tiles * S < 1024 && KT / (2 * S) >= 4 &&
                (size_t)(2 * S) * M * (size_t)N * sizeof(float) <= scratch_bytes)
             S *= 2;
-    const int kts = (KT + S - 1) / S;
-    S = (KT + kts - 1) / kts;
-    const int chunk = S > 1 ? N : (int)std::min<int64_t>(fit, round_up(N, PANEL_LD));
+        const int kts = (KT + S - 1) / S;
+        S = (KT + kts - 1) / kts;
+        trace_begin(t, name, s);
+        if (S > 1)
+            panel_launch<PL, 64, 64, false, true>(s, M, N, K, S, kts * PANEL_KB, A, B, ldb,
+                                                  static_cast<float *>(scratch), N, 0, none);
+        else if (la)
+            panel_launch<PL, 64, 64, true, true>(s, M, N, K, 1, nkb, A, B, ldb, C, ldc, 0, *la);
+        else
+            panel_launch<PL, 64, 64, false, true>(s, M, N, K, 1, nkb, A, B, ldb, C, ldc, 0, none);
+        trace_end(t, s, flops, bytes);
+        if (S > 1) launch_splitk_reduce_f32(t, s, M, N, S, static_cast<const float *>(scratch), C, ldc, la);
+        return;
+    }
+    // columns whose B panels fit the workspace at once
+    const int64_t fit = (int64_t)(work_bytes / ((size_t)PL * nkb * 16)) / PANEL_LD * PANEL_LD;
+    const int chunk = (int)std::min<int64_t>(fit, round_up(N, PANEL_LD));
+    uint4 *bp = static_cast<uint4 *>(work);
     for (int c0 = 0; c0 < N; c0 += chunk) {
         const int n = std::min(chunk, N - c0), ld = (int)round_up(n, PANEL_LD);
         const double share = (double)n / N;
@@ -302,28 +366,23 @@ static void panel_gemm_any(Tracer *t, hipStream_t s, const char *name, int M, in
         split_any<PL, float>(s, B + c0, K, n, ldb, nkb, ld, bp, (int64_t)nkb * ld);
         trace_end(t, s, 0.0, (4.0 + 2.0 * PL) * (double)K * n);
         trace_begin(t, name, s);
-        if (big >= PANEL_BIG) {
-            if (la) panel_launch<PL, 128, 128, true>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, *la);
-            else panel_launch<PL, 128, 128, false>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, none);
-        } else if (S == 1) {
-            if (la) panel_launch<PL, 64, 64, true>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, *la);
-            else panel_launch<PL, 64, 64, false>(s, M, n, 1, nkb, A, bp, ld, C + c0, ldc, c0, none);
-        } else {
-            panel_launch<PL, 64, 64, false>(s, M, n, S, kts * PANEL_KB, A, bp, ld, static_cast<float *>(scratch), n,
-                                            0, none);
-        }
+        if (la)
+            panel_launch<PL, 128, 128, true, false>(s, M, n, K, 1, nkb, A, bp, ld, C + c0, ldc, c0, *la);
+        else
+            panel_launch<PL, 128, 128, false, false>(s, M, n, K, 1, nkb, A, bp, ld, C + c0, ldc, c0, none);
         trace_end(t, s, flops * share, bytes * share);
-        if (S > 1)
-            launch_splitk_reduce_f32(t, s, M, n, S, static_cast<const float *>(scratch), C, ldc, la);
     }
 }
 
-void launch_panel_gemm_bf16x3(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const PanelDev &A,
-                              const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
-                              size_t scratch_bytes, float *C, int ldc, double flops, double bytes,
-                              const LorentzArgs *la) {
-    panel_gemm_any<2>(t, s, name, M, N, K, A, B, ldb, work, work_bytes, scratch, scratch_bytes, C, ldc, flops, bytes,
-                      la);
+void launch_panel_gemm(Tracer *t, hipStream_t s, const char *name, int planes, int M, int N, int K,
+                       const PanelDev &A, const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
+                       size_t scratch_bytes, float *C, int ldc, double flops, double bytes, const LorentzArgs *la) {
+    if (planes == 2)
+        panel_gemm_any<2>(t, s, name, M, N, K, A, B, ldb, work, work_bytes, scratch, scratch_bytes, C, ldc, flops,
+                          bytes, la);
+    else
+        panel_gemm_any<3>(t, s, name, M, N, K, A, B, ldb, work, work_bytes, scratch, scratch_bytes, C, ldc, flops,
+                          bytes, la);
 }
 
 void launch_to_f32(hipStream_t s, const double *x, float *y, int64_t n) {

@@ -40,3 +40,16 @@ def test_bf16x3(ctx, M, N, K, chunk):
     A, B = A.astype(np.float32).astype(np.float64), B.astype(np.float32).astype(np.float64)
     bound = (3 * 2.0 ** -18 + 3 * K * 2.0 ** -24) * (np.abs(A) @ np.abs(B))
     assert np.all(np.abs(got - A @ B) <= bound)
+
+
+@pytest.mark.parametrize("M,N,K", SIZES)
+@pytest.mark.parametrize("chunk", [0, 1 << 30])
+def test_fp32(ctx, M, N, K, chunk):
+    """Three planes hold an FP32 value whole, |plane i| <= 2^-9i |x|: the dropped products are at most
+    2 2^-27 + 2^-36 of |a b|, and each of its 6 K additions rounds in FP32."""
+    from paper_1005_5340_amd import chi0
+    A, B = _operands(M, N, K, 2)
+    got = ctx.debug_panel_gemm(A, B, chi0.PREC_FP32, chunk)
+    A, B = A.astype(np.float32).astype(np.float64), B.astype(np.float32).astype(np.float64)
+    bound = (3 * 2.0 ** -27 + 6 * K * 2.0 ** -24) * (np.abs(A) @ np.abs(B))
+    assert np.all(np.abs(got - A @ B) <= bound)
