@@ -51,7 +51,9 @@ extern "C" {
 /* Arithmetic of the orbital transforms inside chi0 (Table t:flops steps 2-5).
  * The vertex contractions, the frequency factor, K, Gram-Schmidt, the
  * Hessenberg problem and the true residual are always FP64.
- *   FP64    every transform on FP64 matrix cores.
+ *   FP64    every transform in FP64: on the FP64 matrix cores or, for the two
+ *           dense ones of large systems, on the INT8 ones in residue arithmetic
+ *           (its error is below that of an FP64 sum of the same length).
  *   FP32    transforms on FP32 operands with FP32 accumulation, FP32 intermediates
  *           (dense ones: each operand as three BF16 terms, which hold it whole,
  *           six BF16 products).

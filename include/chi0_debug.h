@@ -61,9 +61,9 @@ int chi0_ws_debug_loss_grad(chi0_ws *ws, int32_t n, const double *omega, const f
 int chi0_debug_lz_passes(const chi0_ctx *ctx, int32_t *passes, double *b_pre, int32_t cap);
 
 /* C [M][N] = A [M][K] B [K][N] (host, row-major) by the panel GEMM that the
- * dense transforms of `precision` use (CHI0_PREC_FP32 or _BF16X3), with at most
- * `work_bytes` of panels for B (so that small sizes also go in chunks of
- * columns).  Needs a device context, no system.  Synchronous. */
+ * dense transforms of `precision` use (FP64: the product on the INT8 matrix
+ * cores, M a multiple of 4), with at most `work_bytes` of workspace for B (so
+ * that small sizes also go in chunks of columns).  Needs a device context, no system.  Synchronous. */
 int chi0_debug_panel_gemm(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N, int32_t K, const double *A,
                           const double *B, int64_t work_bytes, double *C);
 

@@ -116,6 +116,8 @@ struct OpWork {
     float *Tt32 = nullptr, *at32 = nullptr, *Ut32 = nullptr;
     void *panel = nullptr;   // panels of the dense GEMMs' B operand
     size_t panel_bytes = 0;
+    void *crt = nullptr;     // residues of the FP64 dense GEMMs on INT8 (NULL: not used)
+    size_t crt_bytes = 0;
     void release() {
         lpbuf.release();
         buf.release();
@@ -123,8 +125,11 @@ struct OpWork {
         Tt32 = at32 = Ut32 = nullptr;
         panel = nullptr;
         panel_bytes = 0;
+        crt = nullptr;
+        crt_bytes = 0;
     }
 };
+constexpr int kMaxBatch = 256;       // complex columns per operator pass
 constexpr int kLanes = 4;            // most slot lanes of the solver, one stream each
 constexpr int kAutoLanes = 2;        // lanes when the caller leaves the choice to the library
 constexpr int kSets = 2 * kLanes;    // step buffer sets: two steps in flight per lane
@@ -181,6 +186,7 @@ struct chi0_ctx {
     }
     // low-precision operator: operand copies (set_system)
     float *Xo32 = nullptr;
+    CrtDev Xv_crt, Xvt_crt;   // residues of the same for the FP64 operator (data NULL: not used)
     PanelDev Xv_bf, Xvt_bf;   // BF16 panels: rows = atomic orbitals (b3), rows = virtual states (b2)
 
     // partial reorthogonalisation with kernel timing on: per step, whether the
@@ -281,6 +287,20 @@ static int panel_alloc(chi0_ctx *c, DevBuf &buf, PanelDev &p, int rows, int K) {
     double *d = nullptr;
     CHK(dalloc(c, buf, &d, p.plane * PANEL_BF * 2));
     p.data = d;
+    return CHI0_OK;
+}
+
+// Residue planes of an operand with `rows` rows and K reduction entries.
+static int crt_alloc(chi0_ctx *c, DevBuf &buf, CrtDev &p, int rows, int K) {
+    p.p.ld = (int)round_up(rows, CRT_LD);
+    p.p.nkb = (int)round_up((K + 15) / 16, CRT_KB);
+    p.p.plane = (int64_t)p.p.nkb * p.p.ld;
+    double *d = nullptr;
+    CHK(dalloc(c, buf, &d, p.p.plane * CRT_S * 2));
+    p.p.data = d;
+    CHK(dalloc(c, buf, &p.sm, p.p.ld));
+    CHK(dalloc(c, buf, &p.si, p.p.ld));
+    CHK(dalloc(c, buf, &p.se, p.p.ld));
     return CHI0_OK;
 }
 
@@ -670,7 +690,17 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
         CHK(dalloc(c, sb, &c->Xo32, (int64_t)xo.size()));
         CHK(panel_alloc(c, sb, c->Xvt_bf, Nv, N));
         CHK(panel_alloc(c, sb, c->Xv_bf, N, Nv));
+        c->Xvt_crt = c->Xv_crt = CrtDev{};
+        // residues of the orbital matrices where some batch (a multiple of 2 No16 columns) uses them
+        auto some_batch = [&](int M, int K) {
+            const int64_t c1 = 2 * (int64_t)c->No16, most = c1 * kMaxBatch;
+            return crt_pays(M, K, most) || crt_pays(M, K, std::max<int64_t>(c1, std::min<int64_t>(most, 8192 / c1 * c1)));
+        };
+        if (some_batch(c->Nv_pad, N)) CHK(crt_alloc(c, sb, c->Xvt_crt, c->Nv_pad, N));
+        if (some_batch(c->N_pad, Nv)) CHK(crt_alloc(c, sb, c->Xv_crt, c->N_pad, Nv));
         HIPCHK(c, hipDeviceSynchronize());
+        if (c->Xvt_crt.p.data) launch_crt_operand(nullptr, c->Xv, N, c->Nv_pad, c->Nv_pad, c->Xvt_crt);
+        if (c->Xv_crt.p.data) launch_crt_operand(nullptr, c->Xvt, Nv, c->N_pad, c->N_pad, c->Xv_crt);
         launch_to_f32(nullptr, c->Xo, c->Xo32, (int64_t)xo.size());
         launch_panel_bf16(nullptr, c->Xv, N, Nv, c->Nv_pad, &c->Xvt_bf);
         launch_panel_bf16(nullptr, c->Xvt, Nv, N, c->N_pad, &c->Xv_bf);
@@ -725,6 +755,10 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
 }
 
 // ================================================================ operator
+// Most bytes of residues held at once by the FP64 transforms on INT8 (96 MiB
+// is 4-17 % slower from 131 atoms up, 160 MiB to 1 GiB are within 3 %).
+constexpr int64_t kCrtBytes = 512LL << 20;
+
 static int ensure_ws(chi0_ctx *c, OpWork &o, int nc) {
     if (nc <= o.nc_cap) return CHI0_OK;
     for (hipStream_t ls : c->lane_stream)
@@ -748,6 +782,19 @@ static int ensure_ws(chi0_ctx *c, OpWork &o, int nc) {
     // the partial products never exceed 2048 64x64 tiles
     o.gemm_scratch_n = (size_t)2048 * 64 * 64;
     CHK(dalloc(c, w, &o.gemm_scratch, (int64_t)o.gemm_scratch_n));
+    // residues of the FP64 transforms on INT8: every column at once up to kCrtBytes
+    const int64_t ncol = (int64_t)c->No16 * nc;
+    auto crt_bytes = [&](const CrtDev &a, int M, int K) -> int64_t {
+        if (!a.p.data || ncol < 1024) return 0;   // crt_pays for no batch up to this one
+        return std::max(crt_work_bytes(M, K, 1), std::min(kCrtBytes, crt_work_bytes(M, K, ncol)));
+    };
+    const int64_t cb = std::max(crt_bytes(c->Xvt_crt, c->Nv_pad, c->N), crt_bytes(c->Xv_crt, c->N_pad, c->Nv));
+    if (cb > 0) {
+        double *d = nullptr;
+        CHK(dalloc(c, w, &d, cb / 8));
+        o.crt = d;
+        o.crt_bytes = (size_t)(cb / 8 * 8);
+    }
     HIPCHK(c, hipDeviceSynchronize());
     o.nc_cap = nc;
     return CHI0_OK;
@@ -798,14 +845,24 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
     launch_vertex_gather(t, s, c->bm, c->n_blk, o.Zin, o.dV, nc, w);
     if (prec == CHI0_PREC_FP64) {
         launch_occ_transform(t, s, c->bm, c->n_atoms, c->Xo, c->No_pad, o.dV, o.Tt, nc, w);
-        launch_dgemm_lorentz(t, s, c->Nv_pad, ncol, c->N16, c->N_pad, c->Xvt, c->N_pad, o.Tt, (int)mcol,
-                             o.at, (int)mcol, c->Dlt, c->Nv_pad, omega, eps, c->occ, nc,
-                             fl + 6.0 * w.No * w.Nv * nb,
-                             8.0 * (w.N * w.No * nc + w.Nv * w.No * nc + w.N * w.Nv + w.No * w.Nv),
-                             o.gemm_scratch, o.gemm_scratch_n, tu);
-        launch_dgemm(t, s, "virt_back", c->N_pad, ncol, c->Nv16, c->Nv_pad, c->Xv, c->Nv_pad, o.at, (int)mcol,
-                     o.Ut, (int)mcol, fl, 8.0 * (w.Nv * w.No * nc + w.N * w.No * nc + w.N * w.Nv),
-                     o.gemm_scratch, o.gemm_scratch_n, tu);
+        const double f2 = fl + 6.0 * w.No * w.Nv * nb;
+        const double b2 = 8.0 * (w.N * w.No * nc + w.Nv * w.No * nc + w.N * w.Nv + w.No * w.Nv);
+        const double b3 = 8.0 * (w.Nv * w.No * nc + w.N * w.No * nc + w.N * w.Nv);
+        if (o.crt && c->Xvt_crt.p.data && crt_pays(c->Nv_pad, c->N, ncol)) {
+            const LorentzArgs la{c->Dlt, omega, c->Nv_pad, nc, eps, c->occ};
+            launch_crt_gemm(t, s, "virt_transform_crt", c->Nv_pad, ncol, c->N, c->Xvt_crt, o.Tt, mcol, o.crt,
+                            o.crt_bytes, o.at, (int)mcol, CRT_S * fl, b2, &la);
+        } else {
+            launch_dgemm_lorentz(t, s, c->Nv_pad, ncol, c->N16, c->N_pad, c->Xvt, c->N_pad, o.Tt, (int)mcol,
+                                 o.at, (int)mcol, c->Dlt, c->Nv_pad, omega, eps, c->occ, nc, f2, b2, o.gemm_scratch,
+                                 o.gemm_scratch_n, tu);
+        }
+        if (o.crt && c->Xv_crt.p.data && crt_pays(c->N_pad, c->Nv, ncol))
+            launch_crt_gemm(t, s, "virt_back_crt", c->N_pad, ncol, c->Nv, c->Xv_crt, o.at, mcol, o.crt, o.crt_bytes,
+                            o.Ut, (int)mcol, CRT_S * fl, b3, nullptr);
+        else
+            launch_dgemm(t, s, "virt_back", c->N_pad, ncol, c->Nv16, c->Nv_pad, c->Xv, c->Nv_pad, o.at, (int)mcol,
+                         o.Ut, (int)mcol, fl, b3, o.gemm_scratch, o.gemm_scratch_n, tu);
         launch_occ_back(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo, c->No_pad, c->No16, o.Ut, o.W, nc, w);
     } else {
         launch_occ_transform_f32(t, s, c->bm, c->n_atoms, c->Xo32, c->No_pad, o.dV, o.Tt32, nc, w);
@@ -814,10 +871,10 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
         const double by = 4.0 * (w.N * w.No * nc + w.Nv * w.No * nc);
         // FP32: six BF16 products per multiply-add, split BF16 x 3: three
         const bool f32 = prec == CHI0_PREC_FP32;
-        const double fe = (f32 ? 1.0 : 3.0) * fl;   // the record's operations: FP32 ones, or the BF16 ones executed
+        const double fe = (f32 ? 6.0 : 3.0) * fl;   // the record's operations: the BF16 ones executed
         launch_panel_gemm(t, s, f32 ? "virt_transform_lorentz_f32" : "virt_transform_lorentz_bf16x3", f32 ? 3 : 2,
                           c->Nv_pad, ncol, c->N, c->Xvt_bf, o.Tt32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb,
-                          o.at32, (int)mcol, fe + (f32 ? 6.0 * w.No * w.Nv * nb : 0.0), by + 4.0 * w.N * w.Nv, &la);
+                          o.at32, (int)mcol, fe, by + 4.0 * w.N * w.Nv, &la);
         launch_panel_gemm(t, s, f32 ? "virt_back_f32" : "virt_back_bf16x3", f32 ? 3 : 2, c->N_pad, ncol, c->Nv,
                           c->Xv_bf, o.at32, mcol, o.panel, o.panel_bytes, o.gemm_scratch, sb, o.Ut32, (int)mcol, fe,
                           by + 4.0 * w.N * w.Nv, nullptr);
@@ -826,7 +883,6 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
     launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod);
 }
 
-static const int kMaxBatch = 256;   // complex columns per operator pass
 // normwise relative error of one low-precision chi0 application (measured on
 // the test systems: ~3e-7 with FP32 transforms, ~5-7e-6 with split BF16 x 3)
 static const double kOpErrFP32 = 3e-7, kOpErrBF16X3 = 6e-6;
@@ -2070,8 +2126,8 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     if (!c) return CHI0_EINVAL;
     if (c->device < 0) return fail(c, CHI0_ENOSYS, "no device context");
     if (M < 1 || N < 1 || K < 1 || !A || !B || !C) return fail(c, CHI0_EINVAL, "bad sizes or NULL");
-    if (precision != CHI0_PREC_FP32 && precision != CHI0_PREC_BF16X3)
-        return fail(c, CHI0_EINVAL, "no panel GEMM for this precision");
+    if (precision < CHI0_PREC_FP64 || precision > CHI0_PREC_BF16X3) return fail(c, CHI0_EINVAL, "unknown precision");
+    if (precision == CHI0_PREC_FP64 && M % 4) return fail(c, CHI0_EINVAL, "M must be a multiple of 4");
     HIPCHK(c, hipSetDevice(c->device));
     struct Scope {
         DevBuf buf;
@@ -2085,6 +2141,26 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     for (int64_t i = 0; i < kn; ++i) b32[i] = (float)B[i];
     double *a_d = nullptr, *work = nullptr, *scratch = nullptr;
     float *b_d = nullptr, *c_d = nullptr;
+    if (precision == CHI0_PREC_FP64) {
+        double *bd = nullptr, *cd = nullptr;
+        CrtDev a;
+        work_bytes = std::max(work_bytes, crt_work_bytes(M, K, 1));
+        CHK(crt_alloc(c, ws.buf, a, M, K));
+        CHK(dalloc(c, ws.buf, &a_d, mk));
+        CHK(dalloc(c, ws.buf, &work, (work_bytes + 7) / 8));
+        CHK(dalloc(c, ws.buf, &bd, kn));
+        CHK(dalloc(c, ws.buf, &cd, mn));
+        HIPCHK(c, hipMemcpy(a_d, at.data(), mk * 8, hipMemcpyHostToDevice));
+        HIPCHK(c, hipMemcpy(bd, B, kn * 8, hipMemcpyHostToDevice));
+        HIPCHK(c, hipDeviceSynchronize());
+        launch_crt_operand(c->stream, a_d, K, M, M, a);
+        launch_crt_gemm(nullptr, c->stream, "panel", M, N, K, a, bd, N, work, (size_t)work_bytes, cd, N, 0.0, 0.0,
+                        nullptr);
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipMemcpy(C, cd, mn * 8, hipMemcpyDeviceToHost));
+        return CHI0_OK;
+    }
     PanelDev p;
     CHK(panel_alloc(c, ws.buf, p, M, K));
     const int64_t least = (int64_t)p.nkb * PANEL_LD * 16 * PANEL_BF;

@@ -196,6 +196,27 @@ void launch_panel_bf16(hipStream_t s, const double *X, int K, int N, int64_t ldx
 void launch_panel_gemm(Tracer *t, hipStream_t s, const char *name, int planes, int M, int N, int K,
                        const PanelDev &A, const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
                        size_t scratch_bytes, float *C, int ldc, double flops, double bytes, const LorentzArgs *la);
+// FP64 products on the INT8 matrix cores (kernels_crt.hip): an operand as
+// CRT_S planes of residues with a scale 2^se sm per row (column of B).
+constexpr int CRT_S = 14;
+constexpr int CRT_LD = 256;   // rows of an operand: whole GEMM tiles
+constexpr int CRT_KB = 4;     // k-blocks (of 16) of an operand: whole GEMM stages
+struct CrtDev {
+    PanelDev p;
+    double *sm = nullptr, *si = nullptr;   // [ld] sm and 1 / sm
+    int *se = nullptr;                     // [ld]
+};
+// whether a product of these sizes is faster this way than in FP64
+bool crt_pays(int M, int K, int64_t N);
+// residues of X [K][ldx] (N columns = the operand's rows); p's buffers and sizes set
+void launch_crt_operand(hipStream_t s, const double *X, int K, int N, int64_t ldx, CrtDev &p);
+// workspace that takes N columns at once (launch_crt_gemm goes in chunks of
+// columns of at least CRT_LD)
+int64_t crt_work_bytes(int M, int K, int64_t N);
+// C [M][ldc] = A B, B [K][ldb], M % 4 == 0, K < 2^17; la: with the frequency factor
+void launch_crt_gemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const CrtDev &A,
+                     const double *B, int64_t ldb, void *work, size_t work_bytes, double *C, int ldc, double flops,
+                     double bytes, const LorentzArgs *la);
 // C = sum of S FP32 slices of M x N (+ the frequency factor if la)
 void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, const float *part,
                               float *C, int ldc, const LorentzArgs *la);

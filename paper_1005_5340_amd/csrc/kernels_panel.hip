@@ -1,20 +1,6 @@
-// Dense matrix-core products over k-block panels: the virtual-orbital
-// transforms (Sec. 4.2, Table t:flops steps 3 and 4) wherever their operands
-// are cut into pieces of a narrow type.
-//
-// Panel layout.  An operand with R rows (columns of B) and K reduction
-// entries is stored in 16-byte blocks of consecutive k (8 of BF16): block
-// kb of row r is uint4 number kb * ld + r of its plane, ld >= R.  That is
-// what one lane of a 32x32 MFMA supplies (lane l: row l % 32, k-block l / 32
-// of the instruction's two), so a tile is a set of contiguous runs in global
-// memory, goes straight to LDS (16 bytes per lane, consecutive lanes to
-// consecutive addresses) and is read back without bank conflicts and without
-// padding.  A and B use the same k order inside a block, so the order itself
-// does not matter.  D of a 32x32 MFMA: element r of lane l is row
-// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
-#include "common.h"
-
-#include <type_traits>
+// The virtual-orbital transforms (Sec. 4.2, Table t:flops steps 3 and 4) of the
+// low-precision operator, on BF16 panels (panel_core.h).
+#include "panel_core.h"
 
 namespace chi0 {
 
@@ -30,16 +16,6 @@ typedef float flt16 __attribute__((ext_vector_type(16)));
 typedef float flt2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-#define CHI0_GLOBAL __attribute__((address_space(1)))
-#define CHI0_LDS __attribute__((address_space(3)))
-
-// Workgroup id -> tile id, each of the 8 XCDs on one contiguous range of tiles.
-__device__ __forceinline__ int panel_xcd(int wid, int n) {
-    const int q = n / 8, r = n % 8;
-    const int x = wid % 8, local = wid / 8;
-    return x * q + (x < r ? x : r) + local;
-}
 
 // One k-block of 8 values as PL planes: bf16(x), then one BF16 of what the
 // planes before leave (all to nearest even); x is overwritten.
@@ -66,16 +42,8 @@ __device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
 // first: the rest is below 2^-25 of a product, under the rounding of the
 // FP32 accumulation.
 //
-// A workgroup computes a BM x BN tile with WM x WN wavefronts of 32x32 MFMA
-// tiles.  KB k-blocks of both operands make one stage; two stages of LDS are
-// filled in turn by direct-to-LDS loads.  The fragments of a step are read
-// while the MFMAs of the step before run, also across the stage boundary:
-// the last step's fragments are in registers when the workgroup meets at the
-// barrier, so the loads that refill the freed stage and the first fragment
-// reads of the next one are issued ahead of the last step's MFMAs and a load
-// has a whole stage of MFMAs to land.  blockIdx.y selects a k range of
-// nkb_split k-blocks (at least one stage), whose raw sums go to a C slice of
-// their own.
+// blockIdx.y selects a k range of nkb_split k-blocks (at least one stage),
+// whose raw sums go to a C slice of their own.
 //
 // Bound by the matrix cores' sustained rate: 128x128 tiles execute 1.0-1.1
 // PFLOP/s of BF16 (a library product of 8192^3 reaches 1.05 on this card).
@@ -98,144 +66,74 @@ __device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
 // 131 atoms, 24 vectors 611 -> 479 us, 200 atoms, 24 vectors 3.31 -> 2.57 ms,
 // 400 atoms, 8 vectors 19.5 -> 14.0 ms; its error against 64 bits is a tenth
 // smaller (4.3e-7 -> 3.8e-7 of chi0 z).
-template <int PL, int BM, int BN, int WM, int WN, int KB, bool LORENTZ, bool RAW>
-__global__ __launch_bounds__(WM * WN * 64)
+template <int PL_>
+struct FormBF {
+    static constexpr int PL = PL_;
+    typedef flt16 acc;
+    static __device__ __forceinline__ acc mma(const uint4 (&a)[PL], const uint4 (&b)[PL], acc c) {
+        auto mm = [&](int x, int y) {
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[x]),
+                                                        __builtin_bit_cast(bf16x8, b[y]), c, 0, 0, 0);
+        };
+        if constexpr (PL == 3) {
+            mm(2, 0);
+            mm(0, 2);
+            mm(1, 1);
+        }
+        mm(1, 0);
+        mm(0, 1);
+        mm(0, 0);
+        return c;
+    }
+};
+
+// FP32 column of B cut on the way to LDS: thread t takes k-block t / BN of
+// the stage in column t % BN.
+template <class P>
+struct PanelRaw {
+    static constexpr bool on = true;
+    static_assert(P::SB == P::NT, "one k-block of B per thread");
+    const float *src;   // row 0 of the thread's column
+    int64_t ldb;
+    int k_first, K;     // first k of stage 0 for this thread
+    bool ok;
+    float x[8];
+    __device__ __forceinline__ void load(int kt) {
+        const int k0 = k_first + kt * P::KB * 8;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) x[c] = (ok && k0 + c < K) ? src[(int64_t)(k0 + c) * ldb] : 0.f;
+    }
+    __device__ __forceinline__ void store(uint4 *dst) {
+        uint4 w[P::PL];
+        panel_cut<P::PL>(x, w);
+#pragma unroll
+        for (int pl = 0; pl < P::PL; ++pl) dst[pl * P::SB + threadIdx.x] = w[pl];
+    }
+};
+
+template <class P, bool LORENTZ, bool RAW>
+__global__ __launch_bounds__(P::NT)
 void k_panel_gemm(int M, int N, int K, int ntm, int ntn, int nkb, int nkb_split, const uint4 *__restrict__ A,
                   int lda, int64_t apl, const void *__restrict__ Bv, int64_t ldb, int64_t bpl, float *__restrict__ C,
                   int ldc, int col0, LorentzArgs la) {
-    constexpr int NT = WM * WN * 64;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int SA = KB * BM, SB = KB * BN, KS = KB / 2;
-    static_assert(SA % NT == 0 && SB % NT == 0 && KB % 2 == 0, "whole 16-byte chunks per thread");
-    __shared__ uint4 s0[PL * (SA + SB)], s1[PL * (SA + SB)];
+    constexpr int BM = P::BM, BN = P::BN, WM = P::WM, WN = P::WN, TM = P::TM, TN = P::TN;
+    __shared__ uint4 s0[P::STAGE], s1[P::STAGE];
     const int tile = panel_xcd(blockIdx.x, ntm * ntn);
     const int m0 = (tile % ntm) * BM, n0 = (tile / ntm) * BN;
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wv % WM, wn = wv / WM, lr = lane & 31, lk = lane >> 5;
-    const int kb0 = blockIdx.y * nkb_split, KT = min(nkb_split, nkb - kb0) / KB;
+    const int kb0 = blockIdx.y * nkb_split, KT = min(nkb_split, nkb - kb0) / P::KB;
     A += (int64_t)kb0 * lda + m0;
-    const uint4 *B = static_cast<const uint4 *>(Bv) + (int64_t)kb0 * ldb + n0;
-    const float *Braw = static_cast<const float *>(Bv) + n0 + t % BN;   // RAW: this thread's column
-    static_assert(!RAW || SB == NT, "one k-block of B per thread");
-    const bool raw_ok = RAW && n0 + t % BN < N;
-    float rb[8];
     C += (int64_t)blockIdx.y * M * ldc;
-
-    auto load = [&](uint4 *dst, int kt) {
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl) {
-#pragma unroll
-            for (int c = 0; c < SA / NT; ++c) {
-                const int ch = c * NT + t;
-                const uint4 *g = A + pl * apl + (int64_t)(kt * KB + ch / BM) * lda + ch % BM;
-                __builtin_amdgcn_global_load_lds((const CHI0_GLOBAL void *)g,
-                                                 (CHI0_LDS void *)(dst + pl * SA + c * NT + wv * 64), 16, 0, 0);
-            }
-#pragma unroll
-            for (int c = 0; c < (RAW ? 0 : SB / NT); ++c) {
-                const int ch = c * NT + t;
-                const uint4 *g = B + pl * bpl + (int64_t)(kt * KB + ch / BN) * ldb + ch % BN;
-                __builtin_amdgcn_global_load_lds((const CHI0_GLOBAL void *)g,
-                                                 (CHI0_LDS void *)(dst + PL * SA + pl * SB + c * NT + wv * 64), 16,
-                                                 0, 0);
-            }
-        }
-    };
-    auto load_raw = [&](int kt) {
-        const int k0 = (kb0 + kt * KB + t / BN) * 8;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) rb[c] = (raw_ok && k0 + c < K) ? Braw[(int64_t)(k0 + c) * ldb] : 0.f;
-    };
-    auto store_raw = [&](uint4 *dst) {
-        uint4 w[PL];
-        panel_cut<PL>(rb, w);
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl) dst[PL * SA + pl * SB + t] = w[pl];
-    };
-    flt16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    uint4 fa[2][PL][TM], fb[2][PL][TN];   // fragments of two steps
-    auto read = [&](int w, const uint4 *src, int ks) {
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                fb[w][pl][j] = src[PL * SA + pl * SB + (2 * ks + lk) * BN + wn * (BN / WN) + j * 32 + lr];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[w][pl][i] = src[pl * SA + (2 * ks + lk) * BM + wm * (BM / WM) + i * 32 + lr];
-        }
-    };
-    auto mma = [&](int w) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                auto mm = [&](int x, int y) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[w][x][i]),
-                                                                        __builtin_bit_cast(bf16x8, fb[w][y][j]),
-                                                                        acc[i][j], 0, 0, 0);
-                };
-                if constexpr (PL == 3) {
-                    mm(2, 0);
-                    mm(0, 2);
-                    mm(1, 1);
-                }
-                mm(1, 0);
-                mm(0, 1);
-                mm(0, 0);
-            }
-    };
-    // every wavefront's loads have landed and every fragment read is done
-    auto meet = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        __syncthreads();
-    };
-    // Stage kt in `cur`, its first step's fragments already in set W0.  Past the
-    // last stage the fragment read of `nxt` takes what LDS holds and is not used.
-    auto stage = [&](auto W0, uint4 *cur, const uint4 *nxt, int kt) {
-        constexpr int w0 = decltype(W0)::value;
-#pragma unroll
-        for (int ks = 0; ks + 1 < KS; ++ks) {
-            read((w0 + ks + 1) & 1, cur, ks + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma((w0 + ks) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (RAW && kt + 1 < KT) store_raw(const_cast<uint4 *>(nxt));
-        meet();
-        if (kt + 2 < KT) {
-            load(cur, kt + 2);
-            if (RAW) load_raw(kt + 2);
-        }
-        read((w0 + KS) & 1, nxt, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mma((w0 + KS - 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    load(s0, 0);
-    if (RAW) {
-        load_raw(0);
-        store_raw(s0);
+    typename P::Acc acc;
+    if constexpr (RAW) {
+        const int n = n0 + t % BN;
+        PanelRaw<P> raw{static_cast<const float *>(Bv) + n, ldb, (kb0 + t / BN) * 8, K, n < N, {}};
+        panel_product<P>(acc, s0, s1, KT, A, lda, apl, (const uint4 *)nullptr, 0, 0, raw);
+    } else {
+        panel_product<P>(acc, s0, s1, KT, A, lda, apl, static_cast<const uint4 *>(Bv) + (int64_t)kb0 * ldb + n0, ldb,
+                         bpl, PanelNoRaw{});
     }
-    meet();
-    if (KT > 1) {
-        load(s1, 1);
-        if (RAW) load_raw(1);
-    }
-    read(0, s0, 0);
-    int kt = 0;
-    for (; kt + 2 <= KT; kt += 2) {
-        stage(std::integral_constant<int, 0>{}, s0, s1, kt);
-        stage(std::integral_constant<int, KS & 1>{}, s1, s0, kt + 1);
-    }
-    if (kt < KT) stage(std::integral_constant<int, 0>{}, s0, s1, kt);
 
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -322,8 +220,8 @@ template <int PL, int BM, int BN, bool LORENTZ, bool RAW>
 static void panel_launch(hipStream_t s, int M, int N, int K, int S, int nkb_split, const PanelDev &A, const void *B,
                          int64_t ldb, float *C, int ldc, int col0, const LorentzArgs &la) {
     const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
-    hipLaunchKernelGGL((k_panel_gemm<PL, BM, BN, 2, 2, PL * BM <= 256 ? 4 : 2, LORENTZ, RAW>), dim3(ntm * ntn, S),
-                       dim3(256), 0, s, M, N, K, ntm, ntn, A.nkb, nkb_split, reinterpret_cast<const uint4 *>(A.data),
+    typedef PanelShape<FormBF<PL>, BM, BN, 2, 2, PL * BM <= 256 ? 4 : 2> P;
+    hipLaunchKernelGGL((k_panel_gemm<P, LORENTZ, RAW>), dim3(ntm * ntn, S), dim3(P::NT), 0, s, M, N, K, ntm, ntn, A.nkb, nkb_split, reinterpret_cast<const uint4 *>(A.data),
                        A.ld, A.plane, B, ldb, (int64_t)A.nkb * ldb, C, ldc, col0, la);
 }
 
@@ -357,7 +255,7 @@ static void panel_gemm_any(Tracer *t, hipStream_t s, const char *name, int M, in
     }
     // columns whose B panels fit the workspace at once
     const int64_t fit = (int64_t)(work_bytes / ((size_t)PL * nkb * 16)) / PANEL_LD * PANEL_LD;
-    const int chunk = (int)std::min<int64_t>(fit, round_up(N, PANEL_LD));
+    const int nch = (int)((N + fit - 1) / fit), chunk = (int)round_up((N + nch - 1) / nch, PANEL_LD);   // equal chunks
     uint4 *bp = static_cast<uint4 *>(work);
     for (int c0 = 0; c0 < N; c0 += chunk) {
         const int n = std::min(chunk, N - c0), ld = (int)round_up(n, PANEL_LD);
