@@ -692,26 +692,24 @@ void k_kmatvec_lanes(int P_pad, const double *__restrict__ K, const double *__re
         }
 }
 
-constexpr int KMV_RT = 2;   // 16-row tiles per workgroup of the MFMA form
-constexpr int KMV_U = 8;    // column pairs per lane and row tile in flight
-
 // 5..32 real columns on the FP64 matrix cores (CT 16-column tiles).  A
-// workgroup owns 16 RT rows;
-// its four waves split the reduction over nu in interleaved chunks of 8 U
-// columns and add their 16x16 accumulators in a fixed order through LDS at
-// the end.  Each lane streams K as 16-byte loads of two adjacent columns; the
-// two columns feed two 16x16x4 MFMAs whose k slots are the lanes' even and odd
-// columns, with Zin rows taken in the same order.  Zin (P_pad x nc, a few MB)
-// is read through the cache; no barrier in the loop.  With PF the loads of the
-// wave's next chunk are issued before the MFMAs of the current one (one
-// 16-column tile: 4.3-4.4 TB/s against 4.0-4.2 without, on the 12.4k-product
-// kernel, 1.2 GB; with two tiles the doubled registers make it slower).
+// workgroup owns 16 RT rows; its NW waves split the reduction over nu in
+// interleaved chunks of 8 U columns and add their 16x16 accumulators in a
+// fixed order through LDS at the end.  Each lane streams K as 16-byte loads of
+// two adjacent columns; the two columns feed two 16x16x4 MFMAs whose k slots
+// are the lanes' even and odd columns, with Zin rows taken in the same order.
+// Zin (P_pad x nc, a few MB) is read through the cache; no barrier in the
+// loop.  With PF the loads of the wave's next chunk are issued before the
+// MFMAs of the current one.
+// Bound by the loads in flight: by too few workgroups where P_pad / 32 is
+// below the CU count (16 rows per workgroup and 8 waves then), by the reads of
+// Zin, which every workgroup repeats, where P_pad is large (32 rows).
 // (LDS-staged form: 0.25-3.4 TB/s; non-temporal loads of K were 10 % slower.)
-template <int RT, int CT, int U, bool PF>
-__global__ __launch_bounds__(256)
+template <int RT, int CT, int U, bool PF, int NW>
+__global__ __launch_bounds__(NW * 64)
 void k_kmatvec_mfma(int P_pad, const double *__restrict__ K, const double *__restrict__ Zin,
                     double *__restrict__ Zout, int nc) {
-    __shared__ dbl4 red[3][RT][CT][64];
+    __shared__ dbl4 red[NW - 1][RT][CT][64];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int row0 = blockIdx.x * 16 * RT;
     const int lr = lane & 15, lk = lane >> 4;
@@ -754,7 +752,7 @@ void k_kmatvec_mfma(int P_pad, const double *__restrict__ K, const double *__res
     if constexpr (PF) {
         int k0 = wv * KW;
         if (k0 < P_pad) fetch(k0);
-        for (; k0 < P_pad; k0 += 4 * KW) {
+        for (; k0 < P_pad; k0 += NW * KW) {
             double2 ca[U][RT];
             double c0[U][CT], c1[U][CT];
 #pragma unroll
@@ -764,11 +762,11 @@ void k_kmatvec_mfma(int P_pad, const double *__restrict__ K, const double *__res
 #pragma unroll
                 for (int c = 0; c < CT; ++c) { c0[u][c] = b0[u][c]; c1[u][c] = b1[u][c]; }
             }
-            if (k0 + 4 * KW < P_pad) fetch(k0 + 4 * KW);
+            if (k0 + NW * KW < P_pad) fetch(k0 + NW * KW);
             mma(ca, c0, c1);
         }
     } else {
-        for (int k0 = wv * KW; k0 < P_pad; k0 += 4 * KW) {
+        for (int k0 = wv * KW; k0 < P_pad; k0 += NW * KW) {
             fetch(k0);
             mma(a, b0, b1);
         }
@@ -785,15 +783,21 @@ void k_kmatvec_mfma(int P_pad, const double *__restrict__ K, const double *__res
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             dbl4 v = acc[r][c];
-            v += red[0][r][c][lane];
-            v += red[1][r][c][lane];
-            v += red[2][r][c][lane];
+#pragma unroll
+            for (int w = 0; w < NW - 1; ++w) v += red[w][r][c][lane];
             const int col = 16 * c + lr;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (col < nc) Zout[(int64_t)(row0 + 16 * r + 4 * e + lk) * nc + col] = v[e];
         }
 }
+
+// Products below which a workgroup takes 16 rows instead of 32 (us at 8 and 24
+// columns, 32 / 16 rows: P = 448: 8.2 / 5.0, 10.9 / 6.5; 1024: 15.5 / 7.7, 20.9 /
+// 11.2; 3328: 42.5 / 21.0, 67.5 / 30.7; 6400: 84 / 87, 95 / 124; 12416: 288 / 326,
+// 386 / 463).  Eight waves of two k-steps at 32 rows and two column tiles
+// replace four of four (6400: 153 -> 95, 12416: 390 -> 386).
+constexpr int KMV_SMALL = 5120;
 
 void launch_kmatvec_skinny(Tracer *t, hipStream_t s, int P_pad, const double *K,
                            const double *Zin, double *Zout, int nc, double P) {
@@ -806,12 +810,18 @@ void launch_kmatvec_skinny(Tracer *t, hipStream_t s, int P_pad, const double *K,
         hipLaunchKernelGGL((k_kmatvec_lanes<3, 1>), dim3(P_pad / 4), dim3(256), 0, s, P_pad, K, Zin, Zout);
     else if (nc == 4)
         hipLaunchKernelGGL((k_kmatvec_lanes<4, 2>), dim3(P_pad / 8), dim3(256), 0, s, P_pad, K, Zin, Zout);
+    else if (nc <= 16 && P_pad < KMV_SMALL)
+        hipLaunchKernelGGL((k_kmatvec_mfma<1, 1, 4, true, 8>), dim3(P_pad / 16), dim3(512), 0, s, P_pad, K, Zin,
+                           Zout, nc);
     else if (nc <= 16)
-        hipLaunchKernelGGL((k_kmatvec_mfma<KMV_RT, 1, KMV_U, true>), dim3(P_pad / (16 * KMV_RT)), dim3(256), 0, s,
-                           P_pad, K, Zin, Zout, nc);
+        hipLaunchKernelGGL((k_kmatvec_mfma<2, 1, 8, true, 4>), dim3(P_pad / 32), dim3(256), 0, s, P_pad, K, Zin,
+                           Zout, nc);
+    else if (P_pad < KMV_SMALL)
+        hipLaunchKernelGGL((k_kmatvec_mfma<1, 2, 4, false, 8>), dim3(P_pad / 16), dim3(512), 0, s, P_pad, K, Zin,
+                           Zout, nc);
     else
-        hipLaunchKernelGGL((k_kmatvec_mfma<KMV_RT, 2, KMV_U / 2, false>), dim3(P_pad / (16 * KMV_RT)), dim3(256), 0,
-                           s, P_pad, K, Zin, Zout, nc);
+        hipLaunchKernelGGL((k_kmatvec_mfma<2, 2, 2, true, 8>), dim3(P_pad / 32), dim3(512), 0, s, P_pad, K, Zin,
+                           Zout, nc);
     trace_end(t, s, 2.0 * P * P * nc, 8.0 * (P * P + 2.0 * P * nc));
 }
 
