@@ -832,8 +832,9 @@ static int ensure_lp(chi0_ctx *c, OpWork &o) {
 // Y = chi0(omega) Zin for nb column pairs already in Zin; omega: device [nb].
 // prec selects the arithmetic of the orbital transforms (ensure_lp first).
 // t, tu: the tracer and GEMM tuner to use (the context's; NULL for none).
+// out: also the result as complex vectors [nb][P] (NULL: Yout alone).
 static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, int prec,
-                     const double *omega, Tracer *t, GemmTuner *tu) {
+                     const double *omega, Tracer *t, GemmTuner *tu, double *out = nullptr) {
     const int nc = 2 * nb;
     const WorkSizes &w = c->ws;
     const int64_t mcol = (int64_t)c->No_pad * nc;
@@ -880,7 +881,7 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
                           by + 4.0 * w.N * w.Nv, nullptr);
         launch_occ_back_f32(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo32, c->No_pad, c->No16, o.Ut32, o.W, nc, w);
     }
-    launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod);
+    launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod, out);
 }
 
 // normwise relative error of one low-precision chi0 application (measured on
@@ -919,9 +920,8 @@ extern "C" int chi0_apply(chi0_ctx *c, int32_t n_rhs, const double *omega, doubl
             if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-            launch_rows_to_cols(&c->tracer, c->cap_stream, z, n_rhs, c->P, ow.Zin, nc);
-            run_chi0(c, ow, c->cap_stream, n_rhs, eps, precision, ow.omega_dev, &c->tracer, &c->tuner);
-            launch_cols_to_rows(&c->tracer, c->cap_stream, ow.Yout, n_rhs, c->P, nc, out);
+            launch_rows_to_cols(&c->tracer, c->cap_stream, z, n_rhs, c->P, ow.Zin);
+            run_chi0(c, ow, c->cap_stream, n_rhs, eps, precision, ow.omega_dev, &c->tracer, &c->tuner, out);
             HIPCHK(c, hipStreamEndCapture(c->cap_stream, &g));
             const hipError_t e = hipGraphInstantiate(&c->apply_exec, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
@@ -941,9 +941,9 @@ extern "C" int chi0_apply(chi0_ctx *c, int32_t n_rhs, const double *omega, doubl
     for (int r0 = 0; r0 < n_rhs; r0 += cap) {
         const int nb = std::min(cap, n_rhs - r0), nc = 2 * nb;
         HIPCHK(c, hipMemcpyAsync(ow.omega_dev, omega + r0, (size_t)nb * 8, hipMemcpyHostToDevice, s));
-        launch_rows_to_cols(&c->tracer, s, z + (int64_t)r0 * c->P * 2, nb, c->P, ow.Zin, nc);
-        run_chi0(c, ow, s, nb, eps, precision, ow.omega_dev, &c->tracer, &c->tuner);
-        launch_cols_to_rows(&c->tracer, s, ow.Yout, nb, c->P, nc, out + (int64_t)r0 * c->P * 2);
+        launch_rows_to_cols(&c->tracer, s, z + (int64_t)r0 * c->P * 2, nb, c->P, ow.Zin);
+        run_chi0(c, ow, s, nb, eps, precision, ow.omega_dev, &c->tracer, &c->tuner,
+                 out + (int64_t)r0 * c->P * 2);
     }
     HIPCHK(c, hipGetLastError());
     return CHI0_OK;
@@ -1026,9 +1026,8 @@ extern "C" int chi0_apply_noalloc(chi0_ctx *c, int32_t n_rhs, const double *omeg
     // the buffers this call uses, whose padding the GEMMs read as zeros.
     launch_zero(nullptr, s, base, L.gemm);
     HIPCHK(c, hipMemcpyAsync(o.omega_dev, omega, (size_t)n_rhs * 8, hipMemcpyHostToDevice, s));
-    launch_rows_to_cols(nullptr, s, z, n_rhs, c->P, o.Zin, nc);
-    run_chi0(c, o, s, n_rhs, eps, CHI0_PREC_FP64, o.omega_dev, nullptr, nullptr);
-    launch_cols_to_rows(nullptr, s, o.Yout, n_rhs, c->P, nc, out);
+    launch_rows_to_cols(nullptr, s, z, n_rhs, c->P, o.Zin);
+    run_chi0(c, o, s, n_rhs, eps, CHI0_PREC_FP64, o.omega_dev, nullptr, nullptr, out);
     HIPCHK(c, hipGetLastError());
     return CHI0_OK;
 }

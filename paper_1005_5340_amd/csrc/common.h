@@ -127,7 +127,7 @@ void launch_vertex_gather(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n
 // max_nprod = largest number of products covering one block.
 void launch_vertex_contract(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_blk, int P,
                             const double *W, double *part, double *Y, int nc, const WorkSizes &ws,
-                            int max_nprod);
+                            int max_nprod, double *out = nullptr);
 // (b1) Tt = X_occ^T dV (gathered MFMA GEMM over the block pattern).
 void launch_occ_transform(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
                           const double *Xo, int no_pad, const double *dV, double *Tt,
@@ -406,10 +406,7 @@ void launch_bl_step(hipStream_t s, int npts, int P, int k, const double *Yout, c
                     int ldalpha, double *beta, int ldbeta, double *rnorm, int ldrn, int *flag);
 
 // apply: caller rows [r][P] complex <-> operator columns [P_pad][ncp]
-void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P,
-                         double *Zin, int ncp);
-void launch_cols_to_rows(Tracer *t, hipStream_t s, const double *Y, int nb, int P, int ncp,
-                         double *out);
+void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin);
 void launch_zero(Tracer *t, hipStream_t s, double *p, int64_t n);
 
 }  // namespace chi0

@@ -1185,34 +1185,22 @@ void launch_alpha_cross(Tracer *t, hipStream_t s, int n_omega, int n_drive, int 
 }
 
 // ------------------------------------------------------------ apply helpers
+// 32 products by 8 vectors per workgroup, turned through LDS: z in 512-byte
+// runs, Zin in 128-byte ones.
 __global__ __launch_bounds__(256)
-void k_rows_to_cols(const double *__restrict__ z, int P, double *__restrict__ Zin, int nc) {
-    const int r = blockIdx.y, mu = blockIdx.x * 256 + threadIdx.x;
-    if (mu >= P) return;
-    const double2 v = reinterpret_cast<const double2 *>(z + (int64_t)r * P * 2)[mu];
-    Zin[(int64_t)mu * nc + 2 * r] = v.x;
-    Zin[(int64_t)mu * nc + 2 * r + 1] = v.y;
+void k_rows_to_cols(const double *__restrict__ z, int P, double *__restrict__ Zin, int nb) {
+    __shared__ double2 tile[8][33];
+    const int t = threadIdx.x, mu0 = blockIdx.x * 32, r0 = blockIdx.y * 8;
+    const int mi = mu0 + t % 32, ri = r0 + t / 32;
+    if (mi < P && ri < nb) tile[t / 32][t % 32] = reinterpret_cast<const double2 *>(z)[(int64_t)ri * P + mi];
+    __syncthreads();
+    const int mu = mu0 + t / 8, r = r0 + t % 8;
+    if (mu < P && r < nb) reinterpret_cast<double2 *>(Zin)[(int64_t)mu * nb + r] = tile[t % 8][t / 8];
 }
 
-__global__ __launch_bounds__(256)
-void k_cols_to_rows(const double *__restrict__ Y, int P, int nc, double *__restrict__ out) {
-    const int r = blockIdx.y, mu = blockIdx.x * 256 + threadIdx.x;
-    if (mu >= P) return;
-    reinterpret_cast<double2 *>(out + (int64_t)r * P * 2)[mu] =
-        make_double2(Y[(int64_t)mu * nc + 2 * r], Y[(int64_t)mu * nc + 2 * r + 1]);
-}
-
-void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P,
-                         double *Zin, int nc) {
+void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin) {
     trace_begin(t, "rows_to_cols", s);
-    hipLaunchKernelGGL(k_rows_to_cols, dim3((P + 255) / 256, nb), dim3(256), 0, s, z, P, Zin, nc);
-    trace_end(t, s);
-}
-
-void launch_cols_to_rows(Tracer *t, hipStream_t s, const double *Y, int nb, int P, int nc,
-                         double *out) {
-    trace_begin(t, "cols_to_rows", s);
-    hipLaunchKernelGGL(k_cols_to_rows, dim3((P + 255) / 256, nb), dim3(256), 0, s, Y, P, nc, out);
+    hipLaunchKernelGGL(k_rows_to_cols, dim3((P + 31) / 32, (nb + 7) / 8), dim3(256), 0, s, z, P, Zin, nb);
     trace_end(t, s);
 }
 
