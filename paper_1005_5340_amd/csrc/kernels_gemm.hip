@@ -51,6 +51,9 @@ struct Mma16d {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
+    // row R of the tile is element elem(R) of the lanes 16 quarter(R) ... + 15
+    static __device__ __forceinline__ int elem(int R) { return R >> 2; }
+    static __device__ __forceinline__ int quarter(int R) { return R & 3; }
 };
 struct Mma16f {
     typedef flt4 acc;
@@ -61,6 +64,8 @@ struct Mma16f {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+    static __device__ __forceinline__ int elem(int R) { return R & 3; }
+    static __device__ __forceinline__ int quarter(int R) { return R >> 2; }
 };
 
 // four consecutive elements (16 B aligned for float, 2 x 16 B for double)
@@ -242,6 +247,98 @@ void k_splitk_reduce(int M, int N, int S, const T *__restrict__ part, int64_t sl
     }
 }
 
+// C = A B (+ Lorentzian factor) for few columns.  One workgroup: 16 TM x 16 TN
+// outputs; its NW waves take turns over k, 8 KU at a time straight into registers
+// (a lane loads two adjacent k of A; they feed two products whose k slots are the
+// lanes' even and odd k), and their sums are added in wave order through LDS,
+// where the factor is applied.  K % 16 == 0, N even with the factor.
+// The tiled kernel with split K needs a second launch and a pass over the
+// partial products there and waits for a barrier per 16 k.
+template <int TM, int TN, int NW, int KU, bool LORENTZ>
+__global__ __launch_bounds__(NW * 64)
+void k_dgemm_few(int N, int K, const double *__restrict__ A, int lda, const double *__restrict__ B, int ldb,
+                 double *__restrict__ C, int ldc, LorentzArgs la) {
+    __shared__ double red[NW][TM][TN][4][64];
+    const int m0 = blockIdx.x * 16 * TM, n0 = blockIdx.y * 16 * TN;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lk = lane >> 4;
+    dbl4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int k0 = wv * 8 * KU; k0 < K; k0 += NW * 8 * KU) {
+        double2 a[KU][TM];
+        double b0[KU][TN], b1[KU][TN];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const int k = k0 + 8 * u + 2 * lk;
+            const bool ok = k < K;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                a[u][i] = ok ? *reinterpret_cast<const double2 *>(A + (int64_t)(m0 + 16 * i + lr) * lda + k)
+                             : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int n = n0 + 16 * j + lr;
+                b0[u][j] = ok && n < N ? B[(int64_t)k * ldb + n] : 0.0;
+                b1[u][j] = ok && n < N ? B[(int64_t)(k + 1) * ldb + n] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][i].x, b0[u][j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][i].y, b1[u][j], acc[i][j], 0, 0, 0);
+                }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wv][i][j][r][lane] = acc[i][j][r];
+    __syncthreads();
+    for (int q = t; q < 256 * TM * TN; q += NW * 64) {   // whole wavefronts
+        const int row = q / (16 * TN), c = q % (16 * TN), n = n0 + c;
+        const int R = row % 16, l = (R & 3) * 16 + c % 16;
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[w][row / 16][c / 16][R >> 2][l];
+        if (LORENTZ) {
+            const int E = n < N ? n / la.ncp : 0, jj = n < N ? n - E * la.ncp : c & 1;
+            const Lorentz lz(la.omega[jj >> 1], la.eps, la.occ, jj & 1);
+            v = lz.apply(la.Dlt[(int64_t)E * la.nv_pad + m0 + row], v, lane_pair(v));
+        }
+        if (n < N) C[(int64_t)(m0 + row) * ldc + n] = v;
+    }
+}
+
+// Up to 6e8 multiply-adds the split-k form is faster; past that its operand
+// reads (32 x 32 tiles) bound it.  16 x 16 tiles up to 2^17 outputs, where the
+// larger ones would be fewer than 128 workgroups.  us at M x N x K, tiled kernel and
+// its reduction / 16 x 16 / 32 x 32: 64x96x112 8.6 / 2.7 / 3.7; 64x1152x112 9.2 /
+// 3.3 / 3.8; 320x480x544 15.3 / 11.0 / 9.4; 320x1440x544 21.7 / 24.7 / 16.4;
+// 576x2880x304 (5e8) 37.3 / 45.1 / 29.6; 320x5760x544 (1e9) 57.6 / 83.5 / 53.8.
+constexpr int64_t FEW_WORK = 600000000LL, FEW_SMALL = 131072;
+
+template <int TM, int TN, int NW, int KU>
+static void launch_few(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const double *A, int lda,
+                       const double *B, int ldb, double *C, int ldc, double flops, double bytes, bool lorentz,
+                       const LorentzArgs &la) {
+    const dim3 grid(M / (16 * TM), (N + 16 * TN - 1) / (16 * TN));
+    trace_begin(t, name, s);
+    if (lorentz)
+        hipLaunchKernelGGL((k_dgemm_few<TM, TN, NW, KU, true>), grid, dim3(NW * 64), 0, s, N, K, A, lda, B, ldb, C, ldc,
+                           la);
+    else
+        hipLaunchKernelGGL((k_dgemm_few<TM, TN, NW, KU, false>), grid, dim3(NW * 64), 0, s, N, K, A, lda, B, ldb, C,
+                           ldc, la);
+    trace_end(t, s, flops, bytes);
+}
+
 // Number of K splits: enough workgroups to fill 256 CUs a few times over,
 // each split keeping >= 4 K tiles of 16; limited by the scratch capacity.  The
 // splits have equal lengths *ks of whole tiles; S *ks may exceed K (the last
@@ -362,6 +459,13 @@ static void gemm_any(Tracer *t, hipStream_t s, const char *name, int M, int N, i
                      const double *A, int lda, const double *B, int ldb, double *C, int ldc,
                      double flops, double bytes, bool lorentz, const LorentzArgs &la,
                      void *scratch, size_t scratch_bytes, GemmTuner *tu) {
+    if ((int64_t)M * N * K <= FEW_WORK) {   // whatever the tuner's mode: results never depend on it
+        if ((int64_t)M * N <= FEW_SMALL)
+            launch_few<1, 1, 8, 4>(t, s, name, M, N, K, A, lda, B, ldb, C, ldc, flops, bytes, lorentz, la);
+        else
+            launch_few<2, 2, 8, 2>(t, s, name, M, N, K, A, lda, B, ldb, C, ldc, flops, bytes, lorentz, la);
+        return;
+    }
     int ks = K;
     const int S = scratch ? choose_splits(M, N, K, kpad, scratch_bytes / sizeof(double), &ks) : 1;
     const int m_fastest = (M / 64) <= ((N + 63) / 64);
@@ -501,6 +605,168 @@ void k_occ_transform(BlockMapDev bm, const T *__restrict__ Xo, int no_pad,
     }
 }
 
+// Where the launch above leaves most of the chip waiting.  One workgroup: column
+// atom B, 16 TE occupied states, NT tiles of pairs; its NW waves take turns over
+// the gathered rows, 4 KU at a time straight into registers (the kernel above
+// pays two barriers and a memory latency per 16 rows), and their sums are added
+// in wave order through LDS.
+template <class T, int TE, int NT, int NW, int KU>
+__global__ __launch_bounds__(NW * 64)
+void k_occ_transform_few(BlockMapDev bm, const T *__restrict__ Xo, int no_pad,
+                         const double *__restrict__ dV, T *__restrict__ Tt, int nc) {
+    typedef typename OccMma<T>::type MM;
+    const int B = blockIdx.x, e0 = blockIdx.y * 16 * TE, n0 = blockIdx.z * 16 * NT;
+    const int g0 = bm.col_gstart[B], g1 = bm.col_gstart[B + 1];
+    const int boff = bm.atom_off[B], nB = bm.atom_off[B + 1] - boff;
+    const int n1 = min(nB * nc, n0 + 16 * NT);   // this workgroup's pairs: n0 <= n < n1
+    if (n0 >= n1) return;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lk = lane >> 4;
+    __shared__ T red[NW][TE][NT][4][64];
+
+    typename MM::acc acc[TE][NT];
+#pragma unroll
+    for (int e = 0; e < TE; ++e)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[e][i] = MM::zero();
+    for (int gc = g0 + wv * 4 * KU; gc < g1; gc += NW * 4 * KU) {
+        T a[KU][TE][1], b[KU][NT];
+        int32_t xr[KU];
+        int64_t ge[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const int g = gc + 4 * u + lk;
+            xr[u] = g < g1 ? bm.g_xrow[g] : 0;
+            ge[u] = g < g1 ? bm.g_ent[g] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const bool ok = gc + 4 * u + lk < g1;
+#pragma unroll
+            for (int e = 0; e < TE; ++e) a[u][e][0] = ok ? Xo[(int64_t)xr[u] * no_pad + e0 + 16 * e + lr] : T(0);
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                b[u][i] = (ok && n0 + 16 * i + lr < n1) ? (T)dV[ge[u] * nc + n0 + 16 * i + lr] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+#pragma unroll
+            for (int e = 0; e < TE; ++e)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[e][i] = MM::op(a[u][e], b[u][i], acc[e][i]);
+    }
+#pragma unroll
+    for (int e = 0; e < TE; ++e)
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wv][e][i][r][lane] = acc[e][i][r];
+    __syncthreads();
+    // (b, E, j) in the order of memory; a group may begin and end inside one b
+    const int b0 = n0 / nc, nb = (n1 - 1) / nc - b0 + 1, run = 16 * TE * nc;
+    for (int q = t; q < nb * run; q += NW * 64) {
+        const int j = q % nc, E = q / nc % (16 * TE), b = b0 + q / run, n = b * nc + j;
+        if (n < n0 || n >= n1) continue;
+        const int R = E % 16, l = MM::quarter(R) * 16 + (n - n0) % 16;
+        T v = T(0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[w][E / 16][(n - n0) / 16][MM::elem(R)][l];
+        Tt[((int64_t)(boff + b) * no_pad + e0 + E) * nc + j] = v;
+    }
+}
+
+// The same split for the way back: column atom B, 16 of its gathered rows, NT
+// tiles of pairs; the waves take turns over the occupied states, 8 KU at a time.
+// A lane loads two adjacent states of X; they feed two products whose k slots are
+// the lanes' even and odd states.
+template <class T, int NT, int NW, int KU>
+__global__ __launch_bounds__(NW * 64)
+void k_occ_back_few(BlockMapDev bm, const T *__restrict__ Xo, int no_pad, int no_sum,
+                    const T *__restrict__ Ut, double *__restrict__ W, int nc) {
+    typedef typename OccMma<T>::type MM;
+    const int B = blockIdx.x, n0 = blockIdx.z * 16 * NT;
+    const int g1 = bm.col_gstart[B + 1], g0 = bm.col_gstart[B] + blockIdx.y * 16;
+    if (g0 >= g1) return;
+    const int boff = bm.atom_off[B], nB = bm.atom_off[B + 1] - boff;
+    const int n1 = min(nB * nc, n0 + 16 * NT);
+    if (n0 >= n1) return;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lk = lane >> 4;
+    const int64_t ldT = (int64_t)no_pad * nc;
+    __shared__ T red[NW][NT][4][64];
+
+    typename MM::acc acc[NT];
+    const T *up[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        acc[i] = MM::zero();
+        const int n = n0 + 16 * i + lr, b = n / nc;
+        up[i] = n < n1 ? Ut + (boff + b) * ldT + n - b * nc : nullptr;
+    }
+    const T *xp = g0 + lr < g1 ? Xo + (int64_t)bm.g_xrow[g0 + lr] * no_pad : nullptr;
+    for (int E0 = wv * 8 * KU; E0 < no_sum; E0 += NW * 8 * KU) {
+        T a0[KU][1], a1[KU][1], u0[KU][NT], u1[KU][NT];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const int E = E0 + 8 * u + 2 * lk;   // even, as no_sum is
+            const bool ok = E < no_sum;
+            a0[u][0] = ok && xp ? xp[E] : T(0);
+            a1[u][0] = ok && xp ? xp[E + 1] : T(0);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                u0[u][i] = ok && up[i] ? up[i][(int64_t)E * nc] : T(0);
+                u1[u][i] = ok && up[i] ? up[i][(int64_t)(E + 1) * nc] : T(0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                acc[i] = MM::op(a0[u], u0[u][i], acc[i]);
+                acc[i] = MM::op(a1[u], u1[u][i], acc[i]);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wv][i][r][lane] = acc[i][r];
+    __syncthreads();
+    for (int q = t; q < 16 * (n1 - n0); q += NW * 64) {
+        const int row = q / (n1 - n0), p = q - row * (n1 - n0);
+        if (g0 + row >= g1) break;
+        const int r = MM::elem(row), l = MM::quarter(row) * 16 + p % 16;
+        T v = T(0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[w][p / 16][r][l];
+        W[bm.g_ent[g0 + row] * nc + n0 + p] = (double)v;
+    }
+}
+
+// The split kernels' shapes: 2 x 1 tiles of (states, pairs) for the transform,
+// 1 x 2 tiles of (rows, pairs) on the way back, eight wavefronts (four, or twice
+// the tiles or the loads per round, were 5-30 % slower at 60 atoms).
+constexpr int OCCF_TE = 2, OCCF_TT = 1, OCCF_TB = 2, OCCF_NW = 8;
+
+// Their lines.  The transform: up to 4096 workgroups (FP32: 8192, its kernel
+// above is slower), past that the operands read again by each workgroup cost
+// more than the waits.  us, whole / split kernel (with the tracer's ~5 us): 12
+// atoms 9 orbitals, 2 columns 14.3 / 7.2; 60 atoms 9 orbitals, 2 columns 21.7 /
+// 12.1, 16 columns 36.8 / 34.0 (4320 workgroups), 24 columns 38.2 / 48.5 (6720);
+// 131 atoms 7 orbitals, 2 columns 19.7 / 16.3, 6 columns 27.0 / 31.6 (5502); FP32
+// 60 atoms, 18 columns 62.8 / 35.5 (5280), 131 atoms, 10 columns 36.0 / 43.6
+// (9170).  Back: up to 1e9 operations.  12 atoms, 2 columns 9.2 / 6.8; 60 atoms,
+// 2 columns 20.2 / 12.4, 32 columns 46.3 / 43.4 (0.94e9), 48 columns 63.3 / 62.3
+// (1.4e9); 131 atoms, 14 columns 59.9 / 58.5 (0.72e9), 24 columns 80.6 / 89.3
+// (1.2e9); 200 atoms, 2 columns 72.6 / 60.1 (0.75e9), 4 columns 92.1 / 95.1 (1.5e9).
+constexpr int64_t OCCF_GROUPS = 4096;
+constexpr double OCCF_WORK = 1e9;
+
+static inline int occ_few_groups(const BlockMapDev &bm, int nc, int nt) {
+    return (bm.nb_max * nc + 16 * nt - 1) / (16 * nt);
+}
+template <class T> static inline bool occ_transform_few(const BlockMapDev &bm, int n_atoms, int no_pad, int nc) {
+    return (int64_t)n_atoms * (no_pad / (16 * OCCF_TE)) * occ_few_groups(bm, nc, OCCF_TT) <=
+           (sizeof(T) == 4 ? 2 : 1) * OCCF_GROUPS;
+}
+
 static inline int occ_pair_blocks(const BlockMapDev &bm, int nc) {
     return (bm.nb_max * nc + OCC_NW - 1) / OCC_NW;
 }
@@ -509,9 +775,14 @@ template <class T>
 static void occ_transform_any(Tracer *t, hipStream_t s, const char *name, const BlockMapDev &bm,
                               int n_atoms, const T *Xo, int no_pad, const double *dV, T *Tt, int nc,
                               const WorkSizes &ws) {
-    dim3 grid(n_atoms, no_pad / 64, occ_pair_blocks(bm, nc));
     trace_begin(t, name, s);
-    hipLaunchKernelGGL((k_occ_transform<T>), grid, dim3(256), 0, s, bm, Xo, no_pad, dV, Tt, nc);
+    if (occ_transform_few<T>(bm, n_atoms, no_pad, nc))
+        hipLaunchKernelGGL((k_occ_transform_few<T, OCCF_TE, OCCF_TT, OCCF_NW, 2>),
+                           dim3(n_atoms, no_pad / (16 * OCCF_TE), occ_few_groups(bm, nc, OCCF_TT)),
+                           dim3(OCCF_NW * 64), 0, s, bm, Xo, no_pad, dV, Tt, nc);
+    else
+        hipLaunchKernelGGL((k_occ_transform<T>), dim3(n_atoms, no_pad / 64, occ_pair_blocks(bm, nc)), dim3(256), 0, s,
+                           bm, Xo, no_pad, dV, Tt, nc);
     trace_end(t, s, 2.0 * ws.No * ws.nnzB * nc,
               8.0 * ws.nnzB * nc + sizeof(T) * (ws.N * ws.No + ws.N * ws.No * nc));
 }
@@ -617,9 +888,14 @@ template <class T>
 static void occ_back_any(Tracer *t, hipStream_t s, const char *name, const BlockMapDev &bm,
                          int n_atoms, int max_rows, const T *Xo, int no_pad, int no_sum, const T *Ut,
                          double *W, int nc, const WorkSizes &ws) {
-    dim3 grid(n_atoms, (max_rows + 63) / 64, occ_pair_blocks(bm, nc));
     trace_begin(t, name, s);
-    hipLaunchKernelGGL((k_occ_back<T>), grid, dim3(256), 0, s, bm, Xo, no_pad, no_sum, Ut, W, nc);
+    if (2.0 * ws.No * ws.nnzB * nc <= OCCF_WORK)
+        hipLaunchKernelGGL((k_occ_back_few<T, OCCF_TB, OCCF_NW, 1>),
+                           dim3(n_atoms, (max_rows + 15) / 16, occ_few_groups(bm, nc, OCCF_TB)), dim3(OCCF_NW * 64), 0,
+                           s, bm, Xo, no_pad, no_sum, Ut, W, nc);
+    else
+        hipLaunchKernelGGL((k_occ_back<T>), dim3(n_atoms, (max_rows + 63) / 64, occ_pair_blocks(bm, nc)), dim3(256), 0,
+                           s, bm, Xo, no_pad, no_sum, Ut, W, nc);
     trace_end(t, s, 2.0 * ws.No * ws.nnzB * nc,
               sizeof(T) * (ws.N * ws.No * nc + ws.N * ws.No) + 8.0 * ws.nnzB * nc);
 }
