@@ -845,7 +845,7 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
     const double fl = 2.0 * w.N * w.Nv * w.No * nc;
     launch_vertex_gather(t, s, c->bm, c->n_blk, o.Zin, o.dV, nc, w);
     if (prec == CHI0_PREC_FP64) {
-        launch_occ_transform(t, s, c->bm, c->n_atoms, c->Xo, c->No_pad, o.dV, o.Tt, nc, w);
+        launch_occ_transform(t, s, c->bm, c->n_atoms, c->Xo, c->No_pad, c->No16, o.dV, o.Tt, nc, w);
         const double f2 = fl + 6.0 * w.No * w.Nv * nb;
         const double b2 = 8.0 * (w.N * w.No * nc + w.Nv * w.No * nc + w.N * w.Nv + w.No * w.Nv);
         const double b3 = 8.0 * (w.Nv * w.No * nc + w.N * w.No * nc + w.N * w.Nv);
@@ -866,7 +866,7 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
                          o.Ut, (int)mcol, fl, b3, o.gemm_scratch, o.gemm_scratch_n, tu);
         launch_occ_back(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo, c->No_pad, c->No16, o.Ut, o.W, nc, w);
     } else {
-        launch_occ_transform_f32(t, s, c->bm, c->n_atoms, c->Xo32, c->No_pad, o.dV, o.Tt32, nc, w);
+        launch_occ_transform_f32(t, s, c->bm, c->n_atoms, c->Xo32, c->No_pad, c->No16, o.dV, o.Tt32, nc, w);
         LorentzArgs la{c->Dlt, omega, c->Nv_pad, nc, eps, c->occ};
         const size_t sb = o.gemm_scratch_n * sizeof(double);
         const double by = 4.0 * (w.N * w.No * nc + w.Nv * w.No * nc);
@@ -2219,7 +2219,7 @@ void lz_front(chi0_ctx *c, OpWork &o, hipStream_t s, int nc) {
     const WorkSizes &w = c->ws;
     const int64_t mcol = (int64_t)c->No_pad * nc;
     launch_vertex_gather(t, s, c->bm, c->n_blk, o.Zin, o.dV, nc, w);
-    launch_occ_transform(t, s, c->bm, c->n_atoms, c->Xo, c->No_pad, o.dV, o.Tt, nc, w);
+    launch_occ_transform(t, s, c->bm, c->n_atoms, c->Xo, c->No_pad, c->No16, o.dV, o.Tt, nc, w);
     launch_dgemm(t, s, "casida_front", c->Nv_pad, c->No16 * nc, c->N16, c->N_pad, c->Xvt, c->N_pad, o.Tt, (int)mcol, o.at,
                  (int)mcol, 2.0 * w.N * w.Nv * w.No * nc, 8.0 * (w.N * w.No * nc + w.Nv * w.No * nc + w.N * w.Nv),
                  o.gemm_scratch, o.gemm_scratch_n, &c->tuner);

@@ -130,7 +130,7 @@ void launch_vertex_contract(Tracer *t, hipStream_t s, const BlockMapDev &bm, int
                             int max_nprod, double *out = nullptr);
 // (b1) Tt = X_occ^T dV (gathered MFMA GEMM over the block pattern).
 void launch_occ_transform(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
-                          const double *Xo, int no_pad, const double *dV, double *Tt,
+                          const double *Xo, int no_pad, int no16, const double *dV, double *Tt,
                           int nc, const WorkSizes &ws);
 // (b4) W = X_occ Ut restricted to the block pattern; the sum over occupied
 // states runs over E < no_sum (a multiple of 16, at most no_pad).
@@ -172,7 +172,7 @@ void launch_dgemm_lorentz(Tracer *t, hipStream_t s, int M, int N, int K, int kpa
                           size_t scratch_doubles, GemmTuner *tu = nullptr);
 // Low-precision operator: FP32 gathered transforms, dense transforms on BF16 panels.
 void launch_occ_transform_f32(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
-                              const float *Xo, int no_pad, const double *dV, float *Tt,
+                              const float *Xo, int no_pad, int no16, const double *dV, float *Tt,
                               int nc, const WorkSizes &ws);
 void launch_occ_back_f32(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms, int max_rows,
                          const float *Xo, int no_pad, int no_sum, const float *Ut, double *W, int nc,

@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace chi0 {
 
@@ -515,93 +516,148 @@ void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, con
     reduce_splits<float>(t, s, M, N, S, part, C, ldc, la != nullptr, la ? *la : none);
 }
 
-template <class T> struct OccMma;
-template <> struct OccMma<double> { typedef Mma16d type; };
+template <class T> struct OccMma;      // tiles staged in LDS
+template <class T> struct OccFewMma;   // operands straight from memory: one A value per lane
+template <> struct OccFewMma<double> { typedef Mma16d type; };
+template <> struct OccFewMma<float> { typedef Mma16f type; };
+template <> struct OccMma<double> { typedef Mma4 type; };
 template <> struct OccMma<float> { typedef Mma16f type; };
 
 // ------------------------------------------------------- (b1) occupied transform
 // The gathered transforms multiply by one atom's orbitals b at a time, for every
 // column j; their output columns are the packed pairs n = b nc + j of the column
-// atom (nB nc of them), cut into 16-column MFMA tiles, OCC_NT tiles per
-// workgroup.  A few right-hand sides therefore fill the tiles: one complex
-// vector (nc = 2) on a 9-orbital atom is 18 pairs, two tiles, not nine tiles of
-// which 2 columns are used.
-constexpr int OCC_NT = 9;              // 16-column tiles per workgroup
-constexpr int OCC_NW = 16 * OCC_NT;    // packed (b, j) pairs per workgroup
+// atom (nB nc of them), cut into tiles.  A few right-hand sides therefore fill
+// the tiles: one complex vector (nc = 2) on a 9-orbital atom is 18 pairs, two
+// 16-column tiles, not nine of which 2 columns are used.
+//
+// Both large kernels: NW wavefronts of 16 rows (states) each times TN 16-column
+// tiles of pairs.  The reduction comes in chunks of 16 through one LDS buffer,
+// with the next chunk's loads issued before the current chunk's MFMAs; a second
+// buffer was no faster, the workgroups it leaves no room for hide as much.  The
+// order of the workgroups decides what is read at once.  Transform: the tiles of
+// states of one atom's pairs side by side (they share dV).  Back: the tiles of
+// pairs of one row tile, then the atoms, so that few workgroups read the same
+// part of Ut at the same time (row tiles side by side: 195 -> 282 us at 60 atoms,
+// 256 columns).
+// us before (64 rows, 144 pairs, 16x16x4 products) and now, transform + back: 60
+// atoms 9 orbitals, 48 columns 54 + 64 -> 45 + 48, 256 columns 203 + 205 -> 175 +
+// 181 (43 TFLOP/s); 200 atoms, 24 columns 250 + 294 -> 229 + 287; 400 atoms 13
+// orbitals, 32 columns 2677 + 2729 -> 2613 + 2800 (there by the operands' second
+// reads); FP32 60 atoms, 120 columns 109 + 73 -> 65 + 64, 131 atoms, 48 columns 82
+// + 71 -> 56 + 57; 400 atoms, 64 columns 4607 + 3143 -> 2807 + 2867.
+constexpr int OCC_NT = 9;   // most 16-column tiles per workgroup
+// wavefronts per workgroup: FP32 tiles are small enough for 128 rows (60 atoms, 48
+// columns 64 rows 9 % slower), FP64 with 128 rows 5-17 % slower at few rows per atom
+template <class T> constexpr int OCC_WAVES = sizeof(T) == 4 ? 8 : 4;
+
+// pairs (n, n + 1) of one row, n even; PAIR: the row is 16-byte (8 in FP32) aligned
+template <class T, bool PAIR, class S>
+__device__ __forceinline__ void load_pair(const S *p, bool ok0, bool ok1, T &v0, T &v1) {
+    if (PAIR) {
+        typedef S vec2 __attribute__((ext_vector_type(2)));
+        const vec2 v = ok0 ? *reinterpret_cast<const vec2 *>(p) : vec2{S(0), S(0)};
+        v0 = (T)v.x;
+        v1 = (T)v.y;
+    } else {
+        v0 = ok0 ? (T)p[0] : T(0);
+        v1 = ok1 ? (T)p[1] : T(0);
+    }
+}
 
 // Tt[b][E*nc + j] = sum_{A in nbr(B)} sum_{a in A} Xo[a][E] dV[(k(A,B), a, b)][j]
-// One workgroup: column atom B, 64 occupied states, OCC_NW packed pairs.  Wave w
-// owns states 16w..16w+15.  The gathered rows come in chunks of 16; the next
-// chunk's global loads are issued before the current chunk's MFMAs so their
-// latency overlaps the arithmetic.  Row g of dV holds the pairs of B
-// contiguously (dV[(k, a, b)][j] = dV[k_a nc + n]), so a chunk's pairs are one
-// coalesced run per gathered row.  T is the arithmetic type (FP64, or FP32 for
-// the low-precision operator); dV is always FP64 and is rounded to T when staged.
-template <class T>
-__global__ __launch_bounds__(256)
-void k_occ_transform(BlockMapDev bm, const T *__restrict__ Xo, int no_pad,
+// One workgroup: column atom B, 16 NW occupied states, 16 TN packed pairs.  The
+// row numbers of a chunk are loaded one chunk before its operands.  Row g of dV
+// holds the pairs of B contiguously (dV[(k, a, b)][j] = dV[k_a nc + n]), so a
+// chunk's pairs are one coalesced run per gathered row.  T is the arithmetic type
+// (FP64, or FP32 for the low-precision operator); dV is always FP64 and rounded to
+// T when staged.  A wavefront whose states lie past No16 skips its MFMAs (zeros).
+// PAIR: nc is even.
+template <class T, int NW, int TN, bool PAIR>
+__global__ __launch_bounds__(NW * 64)
+void k_occ_transform(BlockMapDev bm, int mtiles, int ntiles, const T *__restrict__ Xo, int no_pad, int no16,
                      const double *__restrict__ dV, T *__restrict__ Tt, int nc) {
     typedef typename OccMma<T>::type MM;
-    const int B = blockIdx.x, e0 = blockIdx.y * 64, n0 = blockIdx.z * OCC_NW;
+    constexpr int BM = 16 * NW, BN = 16 * TN, TR = 4 * NW, ND = (BN + 2 * TR - 1) / (2 * TR);
+    const int B = blockIdx.x / (mtiles * ntiles), e0 = blockIdx.x % mtiles * BM, n0 = blockIdx.x / mtiles % ntiles * BN;
     const int g0 = bm.col_gstart[B], g1 = bm.col_gstart[B + 1];
-    const int boff = bm.atom_off[B], nB = bm.atom_off[B + 1] - boff;
-    const int nn = nB * nc;
+    const int boff = bm.atom_off[B], nn = (bm.atom_off[B + 1] - boff) * nc;
     if (n0 >= nn) return;
-    const int ntile = min(OCC_NT, (nn - n0 + 15) / 16);
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    __shared__ T Xs[16][64 + 1];
-    __shared__ T Ds[16][OCC_NW];
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool live = e0 + 16 * wv < no16;
+    __shared__ T Xs[16][BM];
+    __shared__ T Ds[16][BN];
 
-    typename MM::acc acc[OCC_NT];
+    typename MM::acc acc[TN];
 #pragma unroll
-    for (int i = 0; i < OCC_NT; ++i) acc[i] = MM::zero();
+    for (int i = 0; i < TN; ++i) acc[i] = MM::zero();
 
-    // register staging of one chunk: 4 X values and OCC_NT dV values of one row
-    const int xr = t / 16, xc = (t % 16) * 4;
-    const int dr = t / 16, dn = t % 16;
-    T xv[4], dv[OCC_NT];
-    auto fetch = [&](int gc) {
-        const int gx = gc + xr;
-        xv[0] = xv[1] = xv[2] = xv[3] = T(0);
-        if (gx < g1) load4(Xo + (int64_t)bm.g_xrow[gx] * no_pad + e0 + xc, xv);
-        const int gd = gc + dr;
-        const double *src = dV + (gd < g1 ? (int64_t)bm.g_ent[gd] * nc : 0) + n0 + dn;
-#pragma unroll
-        for (int i = 0; i < OCC_NT; ++i)
-            dv[i] = (gd < g1 && n0 + 16 * i + dn < nn) ? (T)src[16 * i] : T(0);
+    // staging: row t / TR of the chunk, 4 states and ND pairs of columns per thread
+    const int sr = t / TR, xc = (t % TR) * 4, dc = (t % TR) * 2;
+    int32_t xrow = 0;
+    int64_t ent = 0;
+    auto rows = [&](int gc) {
+        const int g = gc + sr;
+        xrow = g < g1 ? bm.g_xrow[g] : -1;
+        ent = g < g1 ? bm.g_ent[g] : 0;
     };
-    fetch(g0);
+    T xv[4], dv[ND][2];
+    auto fetch = [&]() {
+        xv[0] = xv[1] = xv[2] = xv[3] = T(0);
+        if (xrow >= 0 && e0 + xc < no_pad) load4(Xo + (int64_t)xrow * no_pad + e0 + xc, xv);
+        const double *src = dV + ent * nc + n0 + dc;
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int c = 2 * TR * i + dc;
+            load_pair<T, PAIR>(src + 2 * TR * i, xrow >= 0 && c < BN && n0 + c < nn,
+                               xrow >= 0 && c < BN && n0 + c + 1 < nn, dv[i][0], dv[i][1]);
+        }
+    };
+    auto store = [&]() {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) Xs[sr][xc + c] = xv[c];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int c = 2 * TR * i + dc;
+            if (c >= BN) continue;
+            Ds[sr][c] = dv[i][0];
+            Ds[sr][c + 1] = dv[i][1];
+        }
+    };
+    rows(g0);
+    fetch();
+    rows(g0 + 16);
     for (int gc = g0; gc < g1; gc += 16) {
-        Xs[xr][xc] = xv[0]; Xs[xr][xc + 1] = xv[1]; Xs[xr][xc + 2] = xv[2]; Xs[xr][xc + 3] = xv[3];
-#pragma unroll
-        for (int i = 0; i < OCC_NT; ++i) Ds[dr][16 * i + dn] = dv[i];
+        store();
         __syncthreads();
-        if (gc + 16 < g1) fetch(gc + 16);
+        if (gc + 16 < g1) {
+            fetch();
+            rows(gc + 32);
+        }
+        if (live) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int kk = ks * 4 + (lane >> 4);
-            T a[MM::NA];
+            for (int ks = 0; ks < 4; ++ks) {
+                const int kk = ks * 4 + (lane >> 4);
+                T a[MM::NA], b[TN];
 #pragma unroll
-            for (int r = 0; r < MM::NA; ++r) a[r] = Xs[kk][wv * 16 + MM::a_row(lane, r)];
+                for (int r = 0; r < MM::NA; ++r) a[r] = Xs[kk][16 * wv + MM::a_row(lane, r)];
 #pragma unroll
-            for (int i = 0; i < OCC_NT; ++i)
-                if (i < ntile) acc[i] = MM::op(a, Ds[kk][16 * i + (lane & 15)], acc[i]);
+                for (int i = 0; i < TN; ++i) b[i] = Ds[kk][16 * i + (lane & 15)];
+#pragma unroll
+                for (int i = 0; i < TN; ++i) acc[i] = MM::op(a, b[i], acc[i]);
+            }
         }
         __syncthreads();
     }
+    if (e0 + 16 * wv >= no_pad) return;
     const int64_t ldT = (int64_t)no_pad * nc;
 #pragma unroll
-    for (int i = 0; i < OCC_NT; ++i) {
+    for (int i = 0; i < TN; ++i) {
         const int n = n0 + 16 * i + (lane & 15);
-        if (i < ntile && n < nn) {
-            const int b = n / nc, j = n - b * nc;
-            T *dst = Tt + (int64_t)(boff + b) * ldT + j;
+        if (n >= nn) continue;
+        const int b = n / nc, j = n - b * nc;
+        T *dst = Tt + (int64_t)(boff + b) * ldT + (int64_t)(e0 + 16 * wv) * nc + j;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int E = e0 + wv * 16 + MM::row(lane, r);
-                dst[(int64_t)E * nc] = acc[i][r];
-            }
-        }
+        for (int r = 0; r < 4; ++r) dst[(int64_t)MM::row(lane, r) * nc] = acc[i][r];
     }
 }
 
@@ -614,7 +670,7 @@ template <class T, int TE, int NT, int NW, int KU>
 __global__ __launch_bounds__(NW * 64)
 void k_occ_transform_few(BlockMapDev bm, const T *__restrict__ Xo, int no_pad,
                          const double *__restrict__ dV, T *__restrict__ Tt, int nc) {
-    typedef typename OccMma<T>::type MM;
+    typedef typename OccFewMma<T>::type MM;
     const int B = blockIdx.x, e0 = blockIdx.y * 16 * TE, n0 = blockIdx.z * 16 * NT;
     const int g0 = bm.col_gstart[B], g1 = bm.col_gstart[B + 1];
     const int boff = bm.atom_off[B], nB = bm.atom_off[B + 1] - boff;
@@ -682,7 +738,7 @@ template <class T, int NT, int NW, int KU>
 __global__ __launch_bounds__(NW * 64)
 void k_occ_back_few(BlockMapDev bm, const T *__restrict__ Xo, int no_pad, int no_sum,
                     const T *__restrict__ Ut, double *__restrict__ W, int nc) {
-    typedef typename OccMma<T>::type MM;
+    typedef typename OccFewMma<T>::type MM;
     const int B = blockIdx.x, n0 = blockIdx.z * 16 * NT;
     const int g1 = bm.col_gstart[B + 1], g0 = bm.col_gstart[B] + blockIdx.y * 16;
     if (g0 >= g1) return;
@@ -745,126 +801,174 @@ void k_occ_back_few(BlockMapDev bm, const T *__restrict__ Xo, int no_pad, int no
 // the tiles or the loads per round, were 5-30 % slower at 60 atoms).
 constexpr int OCCF_TE = 2, OCCF_TT = 1, OCCF_TB = 2, OCCF_NW = 8;
 
-// Their lines.  The transform: up to 4096 workgroups (FP32: 8192, its kernel
-// above is slower), past that the operands read again by each workgroup cost
-// more than the waits.  us, whole / split kernel (with the tracer's ~5 us): 12
-// atoms 9 orbitals, 2 columns 14.3 / 7.2; 60 atoms 9 orbitals, 2 columns 21.7 /
-// 12.1, 16 columns 36.8 / 34.0 (4320 workgroups), 24 columns 38.2 / 48.5 (6720);
-// 131 atoms 7 orbitals, 2 columns 19.7 / 16.3, 6 columns 27.0 / 31.6 (5502); FP32
-// 60 atoms, 18 columns 62.8 / 35.5 (5280), 131 atoms, 10 columns 36.0 / 43.6
-// (9170).  Back: up to 1e9 operations.  12 atoms, 2 columns 9.2 / 6.8; 60 atoms,
-// 2 columns 20.2 / 12.4, 32 columns 46.3 / 43.4 (0.94e9), 48 columns 63.3 / 62.3
-// (1.4e9); 131 atoms, 14 columns 59.9 / 58.5 (0.72e9), 24 columns 80.6 / 89.3
-// (1.2e9); 200 atoms, 2 columns 72.6 / 60.1 (0.75e9), 4 columns 92.1 / 95.1 (1.5e9).
-constexpr int64_t OCCF_GROUPS = 4096;
-constexpr double OCCF_WORK = 1e9;
+// Their lines.  The transform: up to 1024 workgroups, past that the operands read
+// again by each workgroup cost more than the waits.  us, split / staged kernel
+// (with the tracer's ~5 us): 12 atoms 9 orbitals, 24 columns 8.2 / 9.5 (336), 80
+// columns 14.6 / 11.2 (1080); 24 atoms 13 orbitals, 8 columns 11.5 / 14.6 (672), 16
+// columns 17.7 / 17.2 (1248); 60 atoms 9 orbitals, 2 columns 12.0 / 13.0 (960), 8
+// columns 21.4 / 18.4 (2400); 131 atoms 7 orbitals, 2 columns 16.8 / 14.8 (1834).
+// Back: up to 128 pairs per atom and 4e8 operations.  60 atoms, 2 columns 12.6 /
+// 14.0, 12 columns 21.7 / 23.4 (108 pairs, 3.5e8), 24 columns 33.2 / 30.1 (7e8);
+// 131 atoms, 6 columns 27.7 / 30.1 (3.1e8), 14 columns 58.4 / 39.6 (7.2e8); 24
+// atoms, 8 columns 12.3 / 12.6 (104 pairs), 16 columns 16.5 / 14.5 (208); 400 atoms
+// 4 orbitals, 2 columns 41.7 / 53.2 (2.8e8), 8 columns 65.9 / 54.1 (1.1e9).
+constexpr int64_t OCCF_GROUPS = 1024;
+constexpr double OCCF_WORK = 4e8;
+constexpr int OCCF_PAIRS = 128;
 
 static inline int occ_few_groups(const BlockMapDev &bm, int nc, int nt) {
     return (bm.nb_max * nc + 16 * nt - 1) / (16 * nt);
 }
-template <class T> static inline bool occ_transform_few(const BlockMapDev &bm, int n_atoms, int no_pad, int nc) {
-    return (int64_t)n_atoms * (no_pad / (16 * OCCF_TE)) * occ_few_groups(bm, nc, OCCF_TT) <=
-           (sizeof(T) == 4 ? 2 : 1) * OCCF_GROUPS;
+
+// Pair tiles per workgroup, with `rest` workgroups per tile of pairs: the least
+// time at tn + 3 per workgroup (its own rows or states cost about three tiles of
+// pairs) and 1536 workgroups at once.  (Nine tiles always: 61 -> 48 us for the way
+// back of 60 atoms, 48 columns; the least padding always: 2613 -> 3042 us for the
+// transform of 400 atoms, 32 columns.)
+static inline int occ_pair_tiles(const BlockMapDev &bm, int nc, int64_t rest) {
+    const int n16 = (bm.nb_max * nc + 15) / 16;
+    int best = OCC_NT;
+    double least = 0.0;
+    for (int tn = OCC_NT; tn >= 2; --tn) {
+        const double cost = (tn + 3) * std::max(1.0, (double)(rest * ((n16 + tn - 1) / tn)) / 1536.0);
+        if (tn == OCC_NT || cost < least) {
+            least = cost;
+            best = tn;
+        }
+    }
+    return best;
 }
 
-static inline int occ_pair_blocks(const BlockMapDev &bm, int nc) {
-    return (bm.nb_max * nc + OCC_NW - 1) / OCC_NW;
+// Calls f(std::integral_constant<int, tn>) for 2 <= tn <= OCC_NT.
+template <int TN = OCC_NT, class F> static void with_tiles(int tn, const F &f) {
+    if constexpr (TN > 2) {
+        if (tn < TN) return with_tiles<TN - 1>(tn, f);
+    }
+    f(std::integral_constant<int, TN>{});
 }
 
 template <class T>
 static void occ_transform_any(Tracer *t, hipStream_t s, const char *name, const BlockMapDev &bm,
-                              int n_atoms, const T *Xo, int no_pad, const double *dV, T *Tt, int nc,
+                              int n_atoms, const T *Xo, int no_pad, int no16, const double *dV, T *Tt, int nc,
                               const WorkSizes &ws) {
     trace_begin(t, name, s);
-    if (occ_transform_few<T>(bm, n_atoms, no_pad, nc))
+    if ((int64_t)n_atoms * (no_pad / (16 * OCCF_TE)) * occ_few_groups(bm, nc, OCCF_TT) <= OCCF_GROUPS)
         hipLaunchKernelGGL((k_occ_transform_few<T, OCCF_TE, OCCF_TT, OCCF_NW, 2>),
                            dim3(n_atoms, no_pad / (16 * OCCF_TE), occ_few_groups(bm, nc, OCCF_TT)),
                            dim3(OCCF_NW * 64), 0, s, bm, Xo, no_pad, dV, Tt, nc);
-    else
-        hipLaunchKernelGGL((k_occ_transform<T>), dim3(n_atoms, no_pad / 64, occ_pair_blocks(bm, nc)), dim3(256), 0, s,
-                           bm, Xo, no_pad, dV, Tt, nc);
+    else {
+        constexpr int NW = OCC_WAVES<T>;
+        const int mt = (no_pad + 16 * NW - 1) / (16 * NW), tn = occ_pair_tiles(bm, nc, (int64_t)n_atoms * mt);
+        const int nt = (bm.nb_max * nc + 16 * tn - 1) / (16 * tn);
+        const dim3 grid((unsigned)(n_atoms * mt * nt));
+        with_tiles(tn, [&](auto c) {
+            constexpr int TN = decltype(c)::value;
+            if (nc % 2 == 0)
+                hipLaunchKernelGGL((k_occ_transform<T, NW, TN, true>), grid, dim3(NW * 64), 0, s, bm, mt, nt, Xo,
+                                   no_pad, no16, dV, Tt, nc);
+            else
+                hipLaunchKernelGGL((k_occ_transform<T, NW, TN, false>), grid, dim3(NW * 64), 0, s, bm, mt, nt, Xo,
+                                   no_pad, no16, dV, Tt, nc);
+        });
+    }
     trace_end(t, s, 2.0 * ws.No * ws.nnzB * nc,
               8.0 * ws.nnzB * nc + sizeof(T) * (ws.N * ws.No + ws.N * ws.No * nc));
 }
 
 void launch_occ_transform(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
-                          const double *Xo, int no_pad, const double *dV, double *Tt,
+                          const double *Xo, int no_pad, int no16, const double *dV, double *Tt,
                           int nc, const WorkSizes &ws) {
-    occ_transform_any<double>(t, s, "occ_transform", bm, n_atoms, Xo, no_pad, dV, Tt, nc, ws);
+    occ_transform_any<double>(t, s, "occ_transform", bm, n_atoms, Xo, no_pad, no16, dV, Tt, nc, ws);
 }
 
 void launch_occ_transform_f32(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
-                              const float *Xo, int no_pad, const double *dV, float *Tt,
+                              const float *Xo, int no_pad, int no16, const double *dV, float *Tt,
                               int nc, const WorkSizes &ws) {
-    occ_transform_any<float>(t, s, "occ_transform_f32", bm, n_atoms, Xo, no_pad, dV, Tt, nc, ws);
+    occ_transform_any<float>(t, s, "occ_transform_f32", bm, n_atoms, Xo, no_pad, no16, dV, Tt, nc, ws);
 }
 
 // ------------------------------------------------------ (b4) back to the pattern
 // W[(k(A,B), a, b)][j] = sum_E Xo[a][E] Ut[b][E*nc + j] for (A, B) in the pattern.
-// One workgroup: column atom B, 64 of its gathered rows (A, a), OCC_NW packed
-// pairs n = b nc + j; the occupied states E < no_sum come in chunks of 16 with the next
-// chunk's global loads issued before the current chunk's MFMAs.  A wave whose
-// 16 rows lie past the atom's last gathered row stages its share of the
-// operands and skips the MFMAs.  Accumulation in T; W is FP64.
-template <class T>
-__global__ __launch_bounds__(256)
-void k_occ_back(BlockMapDev bm, const T *__restrict__ Xo, int no_pad, int no_sum,
+// One workgroup: column atom B, 16 NW of its gathered rows (A, a), 16 TN packed
+// pairs n = b nc + j; wave w owns rows 16w..16w+15.  The occupied states E < no_sum
+// come in chunks of 16.  A wave whose rows lie past the atom's last gathered row
+// stages its share of the operands and skips the MFMAs.  Accumulation in T; W is
+// FP64.  PAIR: nc is even.
+template <class T, int NW, int TN, bool PAIR>
+__global__ __launch_bounds__(NW * 64)
+void k_occ_back(BlockMapDev bm, int n_atoms, int ntiles, const T *__restrict__ Xo, int no_pad, int no_sum,
                 const T *__restrict__ Ut, double *__restrict__ W, int nc) {
     typedef typename OccMma<T>::type MM;
-    const int B = blockIdx.x, n0 = blockIdx.z * OCC_NW;
+    constexpr int BM = 16 * NW, BN = 16 * TN, TR = 4 * NW, NP = (BN + 2 * TR - 1) / (2 * TR);
+    const int B = blockIdx.x / ntiles % n_atoms, n0 = blockIdx.x % ntiles * BN, mt = blockIdx.x / (ntiles * n_atoms);
     const int g1 = bm.col_gstart[B + 1];
-    const int g0 = bm.col_gstart[B] + blockIdx.y * 64;
+    const int g0 = bm.col_gstart[B] + mt * BM;
     if (g0 >= g1) return;
-    const int boff = bm.atom_off[B], nB = bm.atom_off[B + 1] - boff;
-    const int nn = nB * nc;
+    const int boff = bm.atom_off[B], nn = (bm.atom_off[B + 1] - boff) * nc;
     if (n0 >= nn) return;
-    const int ntile = min(OCC_NT, (nn - n0 + 15) / 16);
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const bool live = g0 + wv * 16 < g1;
     const int64_t ldT = (int64_t)no_pad * nc;
-    __shared__ T Xs[64][16 + 1];
-    __shared__ T Us[16][OCC_NW];
+    __shared__ T Xs[16][BM + 1];
+    __shared__ T Us[16][BN];
 
-    typename MM::acc acc[OCC_NT];
+    typename MM::acc acc[TN];
 #pragma unroll
-    for (int i = 0; i < OCC_NT; ++i) acc[i] = MM::zero();
+    for (int i = 0; i < TN; ++i) acc[i] = MM::zero();
 
     const int xr = t / 4, xc = (t % 4) * 4, xg = g0 + xr;
     const T *xsrc = (xg < g1) ? Xo + (int64_t)bm.g_xrow[xg] * no_pad + xc : nullptr;
-    // pair i of this thread: n = n0 + 16 i + un, at Ut[(boff + b) ldT + E nc + j]
-    const int ue = t / 16, un = t % 16;
-    int64_t uoff[OCC_NT];
+    // pairs (n, n + 1) of this thread, n = n0 + 2 TR i + un, at Ut[(boff + b) ldT + E nc + j]
+    const int ue = t / TR, un = (t % TR) * 2;
+    const T *up[NP][PAIR ? 1 : 2];
 #pragma unroll
-    for (int i = 0; i < OCC_NT; ++i) {
-        const int n = n0 + 16 * i + un;
-        const int b = n / nc, j = n - b * nc;
-        uoff[i] = n < nn ? (int64_t)(boff + b) * ldT + (int64_t)ue * nc + j : -1;
-    }
-    T xv[4], uv[OCC_NT];
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+            const int n = n0 + 2 * TR * i + un + h, b = n / nc, j = n - b * nc;
+            up[i][h] = n < nn && 2 * TR * i + un < BN ? Ut + (int64_t)(boff + b) * ldT + (int64_t)ue * nc + j : nullptr;
+        }
+    T xv[4], uv[NP][2];
     auto fetch = [&](int E0) {
         xv[0] = xv[1] = xv[2] = xv[3] = T(0);
         if (xsrc) load4(xsrc + E0, xv);
+        const int64_t o = (int64_t)E0 * nc;
 #pragma unroll
-        for (int i = 0; i < OCC_NT; ++i)
-            uv[i] = uoff[i] >= 0 ? Ut[uoff[i] + (int64_t)E0 * nc] : T(0);
+        for (int i = 0; i < NP; ++i) {
+            if (PAIR) {
+                load_pair<T, true>(up[i][0] + o, up[i][0] != nullptr, false, uv[i][0], uv[i][1]);
+            } else {
+                uv[i][0] = up[i][0] ? up[i][0][o] : T(0);
+                uv[i][1] = up[i][PAIR ? 0 : 1] ? up[i][PAIR ? 0 : 1][o] : T(0);
+            }
+        }
+    };
+    auto store = [&]() {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) Xs[xc + c][xr] = xv[c];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            if (2 * TR * i + un >= BN) continue;
+            Us[ue][2 * TR * i + un] = uv[i][0];
+            Us[ue][2 * TR * i + un + 1] = uv[i][1];
+        }
     };
     fetch(0);
     for (int E0 = 0; E0 < no_sum; E0 += 16) {
-        Xs[xr][xc] = xv[0]; Xs[xr][xc + 1] = xv[1]; Xs[xr][xc + 2] = xv[2]; Xs[xr][xc + 3] = xv[3];
-#pragma unroll
-        for (int i = 0; i < OCC_NT; ++i) Us[ue][16 * i + un] = uv[i];
+        store();
         __syncthreads();
         if (E0 + 16 < no_sum) fetch(E0 + 16);
         if (live) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 const int kk = ks * 4 + (lane >> 4);
-                T a[MM::NA];
+                T a[MM::NA], b[TN];
 #pragma unroll
-                for (int r = 0; r < MM::NA; ++r) a[r] = Xs[wv * 16 + MM::a_row(lane, r)][kk];
+                for (int r = 0; r < MM::NA; ++r) a[r] = Xs[kk][wv * 16 + MM::a_row(lane, r)];
 #pragma unroll
-                for (int i = 0; i < OCC_NT; ++i)
-                    if (i < ntile) acc[i] = MM::op(a, Us[kk][16 * i + (lane & 15)], acc[i]);
+                for (int i = 0; i < TN; ++i) b[i] = Us[kk][16 * i + (lane & 15)];
+#pragma unroll
+                for (int i = 0; i < TN; ++i) acc[i] = MM::op(a, b[i], acc[i]);
             }
         }
         __syncthreads();
@@ -876,9 +980,9 @@ void k_occ_back(BlockMapDev bm, const T *__restrict__ Xo, int no_pad, int no_sum
         if (g < g1) {
             double *dst = W + (int64_t)bm.g_ent[g] * nc;   // row (k, a, b) = g_ent[g] + b: column b nc + j
 #pragma unroll
-            for (int i = 0; i < OCC_NT; ++i) {
+            for (int i = 0; i < TN; ++i) {
                 const int n = n0 + 16 * i + (lane & 15);
-                if (i < ntile && n < nn) dst[n] = (double)acc[i][r];
+                if (n < nn) dst[n] = (double)acc[i][r];
             }
         }
     }
@@ -889,13 +993,25 @@ static void occ_back_any(Tracer *t, hipStream_t s, const char *name, const Block
                          int n_atoms, int max_rows, const T *Xo, int no_pad, int no_sum, const T *Ut,
                          double *W, int nc, const WorkSizes &ws) {
     trace_begin(t, name, s);
-    if (2.0 * ws.No * ws.nnzB * nc <= OCCF_WORK)
+    if (bm.nb_max * nc <= OCCF_PAIRS && 2.0 * ws.No * ws.nnzB * nc <= OCCF_WORK)
         hipLaunchKernelGGL((k_occ_back_few<T, OCCF_TB, OCCF_NW, 1>),
                            dim3(n_atoms, (max_rows + 15) / 16, occ_few_groups(bm, nc, OCCF_TB)), dim3(OCCF_NW * 64), 0,
                            s, bm, Xo, no_pad, no_sum, Ut, W, nc);
-    else
-        hipLaunchKernelGGL((k_occ_back<T>), dim3(n_atoms, (max_rows + 63) / 64, occ_pair_blocks(bm, nc)), dim3(256), 0,
-                           s, bm, Xo, no_pad, no_sum, Ut, W, nc);
+    else {
+        constexpr int NW = OCC_WAVES<T>;
+        const int mt = (max_rows + 16 * NW - 1) / (16 * NW), tn = occ_pair_tiles(bm, nc, (int64_t)n_atoms * mt);
+        const int nt = (bm.nb_max * nc + 16 * tn - 1) / (16 * tn);
+        const dim3 grid((unsigned)(n_atoms * mt * nt));
+        with_tiles(tn, [&](auto c) {
+            constexpr int TN = decltype(c)::value;
+            if (nc % 2 == 0)
+                hipLaunchKernelGGL((k_occ_back<T, NW, TN, true>), grid, dim3(NW * 64), 0, s, bm, n_atoms, nt, Xo,
+                                   no_pad, no_sum, Ut, W, nc);
+            else
+                hipLaunchKernelGGL((k_occ_back<T, NW, TN, false>), grid, dim3(NW * 64), 0, s, bm, n_atoms, nt, Xo,
+                                   no_pad, no_sum, Ut, W, nc);
+        });
+    }
     trace_end(t, s, 2.0 * ws.No * ws.nnzB * nc,
               sizeof(T) * (ws.N * ws.No * nc + ws.N * ws.No) + 8.0 * ws.nnzB * nc);
 }
