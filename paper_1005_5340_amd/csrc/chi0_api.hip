@@ -832,9 +832,11 @@ static int ensure_lp(chi0_ctx *c, OpWork &o) {
 // Y = chi0(omega) Zin for nb column pairs already in Zin; omega: device [nb].
 // prec selects the arithmetic of the orbital transforms (ensure_lp first).
 // t, tu: the tracer and GEMM tuner to use (the context's; NULL for none).
-// out: also the result as complex vectors [nb][P] (NULL: Yout alone).
+// out: also the result as complex vectors [nb][P]; step: the columns of a solver
+// step where it wants them (both NULL: Yout alone).
 static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, int prec,
-                     const double *omega, Tracer *t, GemmTuner *tu, double *out = nullptr) {
+                     const double *omega, Tracer *t, GemmTuner *tu, double *out = nullptr,
+                     const StepOut *step = nullptr) {
     const int nc = 2 * nb;
     const WorkSizes &w = c->ws;
     const int64_t mcol = (int64_t)c->No_pad * nc;
@@ -881,7 +883,7 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
                           by + 4.0 * w.N * w.Nv, nullptr);
         launch_occ_back_f32(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo32, c->No_pad, c->No16, o.Ut32, o.W, nc, w);
     }
-    launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod, out);
+    launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod, out, step);
 }
 
 // normwise relative error of one low-precision chi0 application (measured on
@@ -1388,9 +1390,15 @@ static int solve_impl(chi0_ctx *c, int32_t n_omega, const double *omega, double 
                 launch_dgemm(t, s, "kernel_matmul", c->P_pad, nc, c->P_pad, c->P_pad, c->K, c->P_pad, ow.Vb, nc, ow.Zin,
                              nc, 2.0 * P * (double)P * nc, 8.0 * ((double)P * P + 2.0 * P * nc),
                              ow.gemm_scratch, ow.gemm_scratch_n, &c->tuner);
-            launch_put_drive(t, s, jg, gn, drives, c->P_pad, ow.Zin, nc, P);
-            run_chi0(c, ow, s, gn, eps, prec, om_d + g0, t, &c->tuner);
-            launch_post_jobs(t, s, jg, gn, c->slots, ow.Yout, ow.Zin, drives, nc, P, st_d + g0);
+            bool rhs = false, other = false;   // b jobs; b or residual jobs in the group
+            for (int k = g0; k < g0 + gn; ++k) {
+                rhs = rhs || jobs_h[k].type == JOB_RHS;
+                other = other || jobs_h[k].type != JOB_ARNOLDI;
+            }
+            if (rhs) launch_put_drive(t, s, jg, gn, drives, c->P_pad, ow.Zin, nc, P);
+            const StepOut so{jg, c->slots};
+            run_chi0(c, ow, s, gn, eps, prec, om_d + g0, t, &c->tuner, nullptr, &so);
+            if (other) launch_post_jobs(t, s, jg, gn, c->slots, ow.Yout, ow.Zin, drives, nc, P, st_d + g0);
         };
         if (nb64 > 0) run_group(0, nb64, CHI0_PREC_FP64);
         if (nb > nb64) run_group(nb64, nb - nb64, o.precision);

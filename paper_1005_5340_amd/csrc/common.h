@@ -124,10 +124,12 @@ struct BlockMapDev {
 void launch_vertex_gather(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_blk,
                           const double *Z, double *dV, int nc, const WorkSizes &ws);
 // (d) n_mu = <V_mu, W>: per-block partial sums, then the sum over each product's blocks.
-// max_nprod = largest number of products covering one block.
+// max_nprod = largest number of products covering one block.  out: also as the
+// caller's vectors; step: a solver step's columns, see StepOut.
+struct StepOut;
 void launch_vertex_contract(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_blk, int P,
                             const double *W, double *part, double *Y, int nc, const WorkSizes &ws,
-                            int max_nprod, double *out = nullptr);
+                            int max_nprod, double *out = nullptr, const StepOut *step = nullptr);
 // (b1) Tt = X_occ^T dV (gathered MFMA GEMM over the block pattern).
 void launch_occ_transform(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_atoms,
                           const double *Xo, int no_pad, int no16, const double *dV, double *Tt,
@@ -279,10 +281,18 @@ struct EpsDev {
 };
 constexpr int EPS_NS = 10;
 
+// Where the columns of a solver step go: the pair of an Arnoldi job q as
+// w = v_j - Y into basis vector j + 1 of its slot, any other into Y.
+struct StepOut {
+    const Job *jobs;
+    SlotsDev sl;
+};
+
 void launch_gather_jobs(Tracer *t, hipStream_t s, const Job *jobs, int nb, const SlotsDev &sl,
                         double *Vb, int ncp, int P);
 void launch_put_drive(Tracer *t, hipStream_t s, const Job *jobs, int nb, const double *drives,
                       int P_pad, double *Zin, int ncp, int P);
+// For the b and residual jobs (the Arnoldi ones are done: StepOut).
 // Y = chi0 Zin; Zin = K x (residual jobs) or d (b jobs); drives [n_drive][P_pad].
 void launch_post_jobs(Tracer *t, hipStream_t s, const Job *jobs, int nb, const SlotsDev &sl,
                       const double *Y, const double *Zin, const double *drives, int ncp, int P,

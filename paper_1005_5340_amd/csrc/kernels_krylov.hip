@@ -19,26 +19,35 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Sum over a 256-thread workgroup; every thread gets the result.
+// Sum over a workgroup of NT threads (256, 512, 1024); every thread gets the result.
+template <int NT = 256>
 __device__ __forceinline__ double block_sum(double v, double *sh) {
     v = wave_sum(v);
     const int t = threadIdx.x;
     __syncthreads();
     if ((t & 63) == 0) sh[t >> 6] = v;
     __syncthreads();
-    const double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    double r = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; w += 4) r += (sh[w] + sh[w + 1]) + (sh[w + 2] + sh[w + 3]);
     return r;
 }
 
 __device__ __forceinline__ int64_t hoff(int j) { return (int64_t)j * (j + 3) / 2; }
 
-// Streaming load of a basis element: the basis is read once per pass and is
-// far larger than the caches, so the load is marked non-temporal.
+// Load of a basis element; S: streaming, for a basis far larger than the caches.
+// A step whose basis vectors take up to LD_STREAM bytes reads them plainly, so that
+// its second pass over them and the next step find them in the cache (12 atoms, 48
+// points: 56.1 -> 52.3 ms a solve; 60 atoms, 12 points, mostly above: streamed
+// 329 ms, plain 333).
+constexpr double LD_STREAM = 32.0 * (1 << 20);
 typedef double nt_dbl2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ double2 ldnt(const double2 *p) {
-    const nt_dbl2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_dbl2 *>(p));
+template <bool S> __device__ __forceinline__ double2 ldb(const double2 *p) {
+    const nt_dbl2 *q = reinterpret_cast<const nt_dbl2 *>(p);
+    const nt_dbl2 v = S ? __builtin_nontemporal_load(q) : *q;
     return make_double2(v.x, v.y);
 }
+__device__ __forceinline__ double2 ldnt(const double2 *p) { return ldb<true>(p); }
 
 // ------------------------------------------------------------- gather inputs
 // Operator input column pair (2q, 2q+1) <- the job's vector (zeros for b jobs).
@@ -91,7 +100,7 @@ void launch_put_drive(Tracer *t, hipStream_t s, const Job *jobs, int nb, const d
 }
 
 // ----------------------------------------------------------------- post step
-// RHS:     b = Y, x = 0 (kept if warm), r = b.   ARNOLDI: w = v_j - Y -> V[j+1].
+// RHS:     b = Y, x = 0 (kept if warm), r = b.
 // RESID:   r = b - (x - Y).                RHS/RESID: V[0] = r/||r||, g0 = ||r||.
 // RHS/RESID also keep wa = d + K x (Zin = K x for a residual job; d alone
 // after b): the solution of the transposed system A^T wa = d for the exact x,
@@ -105,15 +114,7 @@ void k_post_jobs(const Job *__restrict__ jobs, SlotsDev sl, const double *__rest
     const Job jb = jobs[q];
     const int64_t vlen = (int64_t)sl.P_pad * 2;
     double *V = sl.V + jb.slot * sl.vstride;
-    if (jb.type == JOB_ARNOLDI) {
-        const double2 *v = reinterpret_cast<const double2 *>(V + (int64_t)jb.j * vlen);
-        double2 *w = reinterpret_cast<double2 *>(V + (int64_t)(jb.j + 1) * vlen);
-        for (int mu = t; mu < P; mu += 256) {
-            const double2 a = v[mu];
-            w[mu] = make_double2(a.x - Y[(int64_t)mu * nc + 2 * q], a.y - Y[(int64_t)mu * nc + 2 * q + 1]);
-        }
-        return;
-    }
+    if (jb.type == JOB_ARNOLDI) return;
     double2 *x = reinterpret_cast<double2 *>(sl.x + jb.slot * vlen);
     double2 *b = reinterpret_cast<double2 *>(sl.b + jb.slot * vlen);
     double2 *wa = reinterpret_cast<double2 *>(sl.w + jb.slot * vlen);
@@ -394,6 +395,7 @@ __device__ __forceinline__ void dcgs_store_dots(double *h, int i, int j, double 
     }
 }
 
+template <bool S>
 __global__ __launch_bounds__(256)
 void k_dcgs_dots(const Job *__restrict__ jobs, SlotsDev sl, int P, int ld, double *__restrict__ part) {
     const int q = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -424,7 +426,7 @@ void k_dcgs_dots(const Job *__restrict__ jobs, SlotsDev sl, int P, int ld, doubl
         const double2 b = vt[mu], c = z[mu];
 #pragma unroll
         for (int k = 0; k < DPW; ++k) {
-            const double2 a = ldnt(&vi[off[k] + mu]);
+            const double2 a = ldb<S>(&vi[off[k] + mu]);
             sr[k] += a.x * b.x + a.y * b.y;
             si[k] += a.x * b.y - a.y * b.x;
             tr[k] += a.x * c.x + a.y * c.y;
@@ -526,6 +528,7 @@ constexpr int DCH = 512;
 // The loads of UB basis vectors are issued together before their products, so
 // a thread keeps UB loads in flight.
 constexpr int UB = 8;
+template <bool S>
 __device__ __forceinline__ void dcgs_sums(const cpx *h, int j, const double2 *vb, int64_t vst, bool act,
                                           int i0, int i1, cpx *shs, cpx *shc, double2 &as, double2 &ac) {
     const int t = threadIdx.x;
@@ -543,7 +546,7 @@ __device__ __forceinline__ void dcgs_sums(const cpx *h, int j, const double2 *vb
             for (; k + UB <= n; k += UB) {
                 double2 v[UB];
 #pragma unroll
-                for (int u = 0; u < UB; ++u) v[u] = ldnt(&vp[(int64_t)(k + u) * vst]);
+                for (int u = 0; u < UB; ++u) v[u] = ldb<S>(&vp[(int64_t)(k + u) * vst]);
 #pragma unroll
                 for (int u = 0; u < UB; ++u) {
                     const cpx sv = shs[k + u], cv = shc[k + u];
@@ -554,7 +557,7 @@ __device__ __forceinline__ void dcgs_sums(const cpx *h, int j, const double2 *vb
                 }
             }
             for (; k < n; ++k) {
-                const double2 v = ldnt(&vp[(int64_t)k * vst]);
+                const double2 v = ldb<S>(&vp[(int64_t)k * vst]);
                 const cpx sv = shs[k], cv = shc[k];
                 as.x += v.x * sv.r - v.y * sv.i;
                 as.y += v.x * sv.i + v.y * sv.r;
@@ -579,6 +582,7 @@ __device__ __forceinline__ void dcgs_finish(const cpx *h, int j, double *V, int6
                        z.y * ir - ac.y - (v.x * cj.i + v.y * cj.r));
 }
 
+template <bool S>
 __global__ __launch_bounds__(256)
 void k_dcgs_update(const Job *__restrict__ jobs, SlotsDev sl, int P) {
     __shared__ cpx shs[DCH], shc[DCH];
@@ -593,13 +597,14 @@ void k_dcgs_update(const Job *__restrict__ jobs, SlotsDev sl, int P) {
     double *V = sl.V + jb.slot * sl.vstride;
     const double2 *vb = reinterpret_cast<const double2 *>(V) + (act ? mu : 0);
     double2 as = make_double2(0.0, 0.0), ac = make_double2(0.0, 0.0);
-    dcgs_sums(h, j, vb, vlen / 2, act, 0, j, shs, shc, as, ac);
+    dcgs_sums<S>(h, j, vb, vlen / 2, act, 0, j, shs, shc, as, ac);
     if (act) dcgs_finish(h, j, V, vlen, mu, as, ac);
 }
 
 // Split form for steps with few Arnoldi jobs: workgroup (x, q, g) sums basis
 // vectors [g jc, (g+1) jc) of job q into part[(q G + g) P_pad + mu] (as, ac),
 // then k_dcgs_update_fin adds the G partial sums in order and finishes.
+template <bool S>
 __global__ __launch_bounds__(256)
 void k_dcgs_update_part(const Job *__restrict__ jobs, SlotsDev sl, int P, int jc,
                         double *__restrict__ part) {
@@ -615,7 +620,7 @@ void k_dcgs_update_part(const Job *__restrict__ jobs, SlotsDev sl, int P, int jc
     const double2 *vb = reinterpret_cast<const double2 *>(sl.V + jb.slot * sl.vstride) + (act ? mu : 0);
     double2 as = make_double2(0.0, 0.0), ac = make_double2(0.0, 0.0);
     const int i0 = min(j, g * jc), i1 = min(j, (g + 1) * jc);
-    dcgs_sums(h, j, vb, vlen / 2, act, i0, i1, shs, shc, as, ac);
+    dcgs_sums<S>(h, j, vb, vlen / 2, act, i0, i1, shs, shc, as, ac);
     if (act) {
         double2 *o = reinterpret_cast<double2 *>(part) + ((int64_t)(q * G + g) * sl.P_pad + mu) * 2;
         o[0] = as;
@@ -645,9 +650,12 @@ void k_dcgs_update_fin(const Job *__restrict__ jobs, SlotsDev sl, int P, int G, 
 // With the error estimates on (ed.Z != NULL) also the projections of the
 // vector v_j this step finished: delta_j = d . v_j and xi_j = x0^H v_j, and at
 // j = 0 the start's d . x0 and |x0|^2.
-__global__ __launch_bounds__(256)
+// One workgroup per job and nothing else to do meanwhile: up to 1024 threads (P =
+// 3300: 8.5 us with 256).
+template <int NT>
+__global__ __launch_bounds__(NT)
 void k_dcgs_norm(const Job *__restrict__ jobs, SlotsDev sl, int P, StepStatus *__restrict__ st, EpsDev ed) {
-    __shared__ double sh[4];
+    __shared__ double sh[NT / 64];
     const int q = blockIdx.x, t = threadIdx.x;
     const Job jb = jobs[q];
     if (jb.type != JOB_ARNOLDI) return;
@@ -655,13 +663,13 @@ void k_dcgs_norm(const Job *__restrict__ jobs, SlotsDev sl, int P, StepStatus *_
     const int64_t vlen = (int64_t)sl.P_pad * 2;
     double2 *w = reinterpret_cast<double2 *>(sl.V + jb.slot * sl.vstride + (int64_t)(j + 1) * vlen);
     double ss = 0.0;
-    for (int mu = t; mu < P; mu += 256) {
+    for (int mu = t; mu < P; mu += NT) {
         const double2 a = w[mu];
         ss += a.x * a.x + a.y * a.y;
     }
-    const double hn = sqrt(block_sum(ss, sh));
+    const double hn = sqrt(block_sum<NT>(ss, sh));
     const double sc = hn > 0.0 ? 1.0 / hn : 0.0;
-    for (int mu = t; mu < P; mu += 256) {
+    for (int mu = t; mu < P; mu += NT) {
         const double2 a = w[mu];
         w[mu] = make_double2(a.x * sc, a.y * sc);
     }
@@ -675,7 +683,7 @@ void k_dcgs_norm(const Job *__restrict__ jobs, SlotsDev sl, int P, StepStatus *_
     const double2 *x = reinterpret_cast<const double2 *>(sl.x + jb.slot * vlen);
     const double *d = ed.drives + (int64_t)jb.drive * sl.P_pad;
     double dr = 0.0, di = 0.0, xr = 0.0, xi = 0.0, pr = 0.0, pi = 0.0, xx = 0.0;
-    for (int mu = t; mu < P; mu += 256) {
+    for (int mu = t; mu < P; mu += NT) {
         const double2 a = v[mu], b = x[mu];
         dr += d[mu] * a.x;
         di += d[mu] * a.y;
@@ -687,14 +695,14 @@ void k_dcgs_norm(const Job *__restrict__ jobs, SlotsDev sl, int P, StepStatus *_
             xx += b.x * b.x + b.y * b.y;
         }
     }
-    dr = block_sum(dr, sh);
-    di = block_sum(di, sh);
-    xr = block_sum(xr, sh);
-    xi = block_sum(xi, sh);
+    dr = block_sum<NT>(dr, sh);
+    di = block_sum<NT>(di, sh);
+    xr = block_sum<NT>(xr, sh);
+    xi = block_sum<NT>(xi, sh);
     if (j == 0) {
-        pr = block_sum(pr, sh);
-        pi = block_sum(pi, sh);
-        xx = block_sum(xx, sh);
+        pr = block_sum<NT>(pr, sh);
+        pi = block_sum<NT>(pi, sh);
+        xx = block_sum<NT>(xx, sh);
     }
     if (t == 0) {
         const int64_t o = (int64_t)jb.slot * (sl.m + 1) * 2 + 2 * j;
@@ -847,7 +855,9 @@ void launch_dcgs(Tracer *t, hipStream_t s, const Job *jobs, int nb, int jmax, co
     const int R = scratch ? dots_splits(P, nb, jmax, scratch_doubles) : 1;
     const dim3 gd((jmax + 1 + 4 * DPW - 1) / (4 * DPW), nb, R), gu((P + 255) / 256, nb);
     trace_begin(t, "dcgs_dots", s);
-    hipLaunchKernelGGL(k_dcgs_dots, gd, dim3(256), 0, s, jobs, sl, P, jmax + 1, scratch);
+    const bool stream = 16.0 * P * sum_j1 > LD_STREAM;
+    hipLaunchKernelGGL(stream ? k_dcgs_dots<true> : k_dcgs_dots<false>, gd, dim3(256), 0, s, jobs, sl, P, jmax + 1,
+                       scratch);
     if (R > 1)
         hipLaunchKernelGGL(k_dcgs_dots_fin, dim3((jmax + 1 + 255) / 256, nb), dim3(256), 0, s, jobs, sl, R,
                            jmax + 1, (const double *)scratch);
@@ -858,16 +868,20 @@ void launch_dcgs(Tracer *t, hipStream_t s, const Job *jobs, int nb, int jmax, co
     const int G = scratch ? update_groups(P, nb, jmax, sl.P_pad, scratch_doubles) : 1;
     trace_begin(t, "dcgs_update", s);
     if (G == 1) {
-        hipLaunchKernelGGL(k_dcgs_update, gu, dim3(256), 0, s, jobs, sl, P);
+        hipLaunchKernelGGL(stream ? k_dcgs_update<true> : k_dcgs_update<false>, gu, dim3(256), 0, s, jobs, sl, P);
     } else {
         const int jc = (jmax + G - 1) / G;
-        hipLaunchKernelGGL(k_dcgs_update_part, dim3(gu.x, nb, G), dim3(256), 0, s, jobs, sl, P, jc, scratch);
+        hipLaunchKernelGGL(stream ? k_dcgs_update_part<true> : k_dcgs_update_part<false>, dim3(gu.x, nb, G), dim3(256), 0,
+                           s, jobs, sl, P, jc, scratch);
         hipLaunchKernelGGL(k_dcgs_update_fin, gu, dim3(256), 0, s, jobs, sl, P, G, scratch);
     }
     trace_end(t, s, 16.0 * P * sum_j1, 16.0 * P * (sum_j1 + 3.0 * n_arnoldi));
     EpsDev none{};
     trace_begin(t, "dcgs_norm", s);
-    hipLaunchKernelGGL(k_dcgs_norm, dim3(nb), dim3(256), 0, s, jobs, sl, P, status, eps ? *eps : none);
+    if (P > 512)
+        hipLaunchKernelGGL(k_dcgs_norm<1024>, dim3(nb), dim3(1024), 0, s, jobs, sl, P, status, eps ? *eps : none);
+    else
+        hipLaunchKernelGGL(k_dcgs_norm<256>, dim3(nb), dim3(256), 0, s, jobs, sl, P, status, eps ? *eps : none);
     trace_end(t, s, 4.0 * P * n_arnoldi, 16.0 * P * 2.0 * n_arnoldi);
     if (eps) {
         // partial sums in scratch: nb jobs x G workgroups x 8 (the update's

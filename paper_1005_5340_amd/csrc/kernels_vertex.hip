@@ -28,11 +28,12 @@ __device__ __forceinline__ dbl4 mfma16(double a, double b, dbl4 c) {
 // by the rounds of the longest block: a diagonal block (A, A) carries every
 // product that involves atom A (175 at 60 atoms, where others carry 8).
 //
-// Up to 16 columns eight wavefronts share a block: groups of row blocks times
-// slices of the reduction, which cut the longest block's rounds; the slices'
-// sums are added in a fixed order through LDS.  How a workgroup splits depends
-// on its block alone.  One vector, 60 atoms: gather 18.6 -> 13.9 us,
-// projection 14.7 -> 8.9 us.
+// The split kernels take 16 columns of a block per workgroup of eight
+// wavefronts: groups of row blocks times slices of the reduction, which cut the
+// longest block's rounds; the slices' sums are added in a fixed order through
+// LDS.  How a workgroup splits depends on its block alone.  One vector, 60
+// atoms: gather 18.6 -> 13.9 us, projection 14.7 -> 8.9 us; 12 atoms, 48
+// columns 16.1 -> 12.1, 15.5 -> 7.9 (with the tracer's ~5 us).
 constexpr int VRB = 4;     // 16-row MFMA blocks per wave (rows <= 256 = NB_MAX^2)
 constexpr int PCH = 256;   // product ids staged in LDS per chunk
 
@@ -130,12 +131,12 @@ __device__ __forceinline__ void vertex_sum_slices(dbl4 (&acc)[NR], int KS, int R
     }
 }
 
-// The gather for up to 16 columns and few blocks.
+// The gather for few workgroups (VSPLIT_BLK).
 template <int KU>
 __global__ __launch_bounds__(512)
 void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double *__restrict__ dV, int nc) {
     __shared__ dbl4 red[4][VRB][64];
-    const int k = blockIdx.x;
+    const int k = blockIdx.x, j = blockIdx.y * 16 + (threadIdx.x & 15);   // block, this lane's column
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nAB = bm.blk_na[k] * bm.blk_nb[k];
     const int np = bm.blk_nprod[k];
@@ -170,7 +171,7 @@ void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double 
                 const int row = (rg + RG * r) * 16 + lr;
                 a[u][r] = (kv && row < nAB) ? Vk[(int64_t)kk * nAB + row] : 0.0;
             }
-            b[u] = (kv && lr < nc) ? Z[(int64_t)pz[u] * nc + lr] : 0.0;
+            b[u] = (kv && j < nc) ? Z[(int64_t)pz[u] * nc + j] : 0.0;
         }
 #pragma unroll
         for (int r = 0; r < VRB; ++r) {
@@ -181,23 +182,23 @@ void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double 
         }
     }
     vertex_sum_slices<VRB>(acc, KS, RG, wv, lane, red);
-    if (ks != 0 || lr >= nc) return;
+    if (ks != 0 || j >= nc) return;
 #pragma unroll
     for (int r = 0; r < VRB; ++r) {
         if (rg + RG * r >= nrb) continue;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = (rg + RG * r) * 16 + 4 * e + lk;
-            if (row < nAB) dV[(ent + row) * nc + lr] = acc[r][e];
+            if (row < nAB) dV[(ent + row) * nc + j] = acc[r][e];
         }
     }
 }
 
-// Blocks up to which a gather of <= 16 columns splits: past four workgroups
-// per CU the launch runs in several waves and the idle wavefronts of the short
-// blocks cost more than the long ones gain (us, four waves / eight: 758 blocks
-// 20.3 / 14.8, 780 17.2 / 14.9; 1246 12.7 / 17.0, 1349 12.8 / 18.9, 1954
-// 23.5 / 28.2).
+// Blocks times 16-column groups up to which the kernels split (the projection
+// also any number of blocks of up to 16 columns): past four workgroups per CU the
+// launch runs in several waves and the idle wavefronts of the short blocks cost
+// more than the long ones gain (gather, us, four waves / eight: 758 blocks 20.3 /
+// 14.8, 780 17.2 / 14.9; 1246 12.7 / 17.0, 1349 12.8 / 18.9, 1954 23.5 / 28.2).
 constexpr int VSPLIT_BLK = 1024;
 
 // 16-column MFMA blocks per workgroup for nc columns: 1 up to 16 columns,
@@ -209,8 +210,9 @@ void launch_vertex_gather(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n
     const int vc = vertex_vc(nc);
     dim3 grid(n_blk, (nc + 16 * vc - 1) / (16 * vc));
     trace_begin(t, "vertex_gather", s);
-    if (vc == 1 && n_blk <= VSPLIT_BLK)
-        hipLaunchKernelGGL((k_vertex_gather_split<8>), dim3(n_blk), dim3(512), 0, s, bm, Z, dV, nc);
+    const int c16 = (nc + 15) / 16;
+    if (n_blk * c16 <= VSPLIT_BLK)
+        hipLaunchKernelGGL((k_vertex_gather_split<8>), dim3(n_blk, c16), dim3(512), 0, s, bm, Z, dV, nc);
     else if (vc == 1)
         hipLaunchKernelGGL((k_vertex_gather<1, 8>), grid, dim3(256), 0, s, bm, Z, dV, nc);
     else if (vc == 2)
@@ -308,7 +310,7 @@ void k_vertex_contract(BlockMapDev bm, const double *__restrict__ W, double *__r
     }
 }
 
-// The projection for up to 16 columns: 8 wavefronts, four 16-row blocks of
+// The projection, 16 columns per workgroup: 8 wavefronts, four 16-row blocks of
 // products per workgroup (blockIdx.z) in two slices of ab, or one row block in
 // eight.  Also for many blocks (us, 2 columns: 758 blocks 17.4 -> 12.4, 2908
 // 20.3 -> 18.1, 5476 54.4 -> 41.5).
@@ -316,7 +318,7 @@ template <int KU>
 __global__ __launch_bounds__(512)
 void k_vertex_contract_split(BlockMapDev bm, const double *__restrict__ W, double *__restrict__ part, int nc) {
     __shared__ dbl4 red[4][1][64];
-    const int k = blockIdx.x, rb0 = blockIdx.z * 4;
+    const int k = blockIdx.x, rb0 = blockIdx.z * 4, j = blockIdx.y * 16 + (threadIdx.x & 15);
     const int np = bm.blk_nprod[k], nrb = (np + 15) / 16;
     if (rb0 >= nrb) return;   // uniform over the workgroup
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -338,7 +340,7 @@ void k_vertex_contract_split(BlockMapDev bm, const double *__restrict__ W, doubl
             const int kk = a0 + 4 * KS * u + lk;
             const bool kv = kk < nAB;
             a[u] = (kv && i < np) ? Vk[(int64_t)i * nAB + kk] : 0.0;
-            b[u] = (kv && lr < nc) ? W[(ent + kk) * nc + lr] : 0.0;
+            b[u] = (kv && j < nc) ? W[(ent + kk) * nc + j] : 0.0;
         }
         if (rb0 + rg >= nrb) continue;
 #pragma unroll
@@ -346,11 +348,11 @@ void k_vertex_contract_split(BlockMapDev bm, const double *__restrict__ W, doubl
             if (a0 + 4 * KS * u < nAB) acc[0] = mfma16(a[u], b[u], acc[0]);
     }
     vertex_sum_slices<1>(acc, KS, RG, wv, lane, red);
-    if (ks != 0 || rb0 + rg >= nrb || lr >= nc) return;
+    if (ks != 0 || rb0 + rg >= nrb || j >= nc) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int row = (rb0 + rg) * 16 + 4 * e + lk;
-        if (row < np) part[(p0 + row) * nc + lr] = acc[0][e];
+        if (row < np) part[(p0 + row) * nc + j] = acc[0][e];
     }
 }
 
@@ -392,15 +394,46 @@ void k_vertex_reduce_rows(BlockMapDev bm, int P, const double *__restrict__ part
     if (mo < P && ro < nb) reinterpret_cast<double2 *>(out)[(int64_t)ro * P + mo] = tile[t / 32][t % 32];
 }
 
+// The same sums where a solver step wants them (StepOut), turned through LDS too:
+// one launch and one pass over Y less, and all of the chip instead of one
+// workgroup per job (60 atoms, 12 jobs: 4.3 + 8.3 us before).
+__global__ __launch_bounds__(256)
+void k_vertex_reduce_step(BlockMapDev bm, int P, const double *__restrict__ part, double *__restrict__ Y, int nc,
+                          StepOut so) {
+    __shared__ double2 tile[8][33];
+    const int t = threadIdx.x, mu0 = blockIdx.x * 32, q0 = blockIdx.y * 8, nb = nc / 2;
+    const int mu = mu0 + t / 8, q = q0 + t % 8;
+    if (mu < P && q < nb) {
+        double2 acc = make_double2(0.0, 0.0);
+        for (int64_t s = bm.prod_pstart[mu]; s < bm.prod_pstart[mu + 1]; ++s) {
+            const double2 v = reinterpret_cast<const double2 *>(part)[bm.prod_plist[s] * nb + q];
+            acc.x += v.x;
+            acc.y += v.y;
+        }
+        if (so.jobs[q].type != JOB_ARNOLDI) reinterpret_cast<double2 *>(Y)[(int64_t)mu * nb + q] = acc;
+        tile[t % 8][t / 8] = acc;
+    }
+    __syncthreads();
+    const int mo = mu0 + t % 32, qo = q0 + t / 32;
+    if (mo >= P || qo >= nb) return;
+    const Job jb = so.jobs[qo];
+    if (jb.type != JOB_ARNOLDI) return;
+    const int64_t vlen = (int64_t)so.sl.P_pad * 2;
+    double *V = so.sl.V + jb.slot * so.sl.vstride + (int64_t)jb.j * vlen;
+    const double2 v = reinterpret_cast<const double2 *>(V)[mo], y = tile[t / 32][t % 32];
+    reinterpret_cast<double2 *>(V + vlen)[mo] = make_double2(v.x - y.x, v.y - y.y);
+}
+
 void launch_vertex_contract(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n_blk, int P,
                             const double *W, double *part, double *Y, int nc, const WorkSizes &ws,
-                            int max_nprod, double *out) {
+                            int max_nprod, double *out, const StepOut *step) {
     const int vc = vertex_vc(nc), nrb = (max_nprod + 15) / 16;
     dim3 grid(n_blk, (nc + 16 * vc - 1) / (16 * vc), (nrb + 4 * VRB - 1) / (4 * VRB));
     trace_begin(t, "vertex_contract", s);
-    if (vc == 1)
-        hipLaunchKernelGGL((k_vertex_contract_split<12>), dim3(n_blk, 1, (nrb + 3) / 4), dim3(512), 0, s, bm, W, part,
-                           nc);
+    const int c16 = (nc + 15) / 16;
+    if (vc == 1 || n_blk * c16 <= VSPLIT_BLK)
+        hipLaunchKernelGGL((k_vertex_contract_split<12>), dim3(n_blk, c16, (nrb + 3) / 4), dim3(512), 0, s, bm, W,
+                           part, nc);
     else if (vc == 2)
         hipLaunchKernelGGL((k_vertex_contract<2, 8>), grid, dim3(256), 0, s, bm, W, part, nc);
     else
@@ -408,9 +441,11 @@ void launch_vertex_contract(Tracer *t, hipStream_t s, const BlockMapDev &bm, int
     trace_end(t, s, 2.0 * ws.sum_s2 * nc, 8.0 * (ws.sum_s2 + ws.nnzB * nc + ws.npart * nc));
     const int64_t n = (int64_t)P * nc;
     trace_begin(t, "vertex_reduce", s);
+    const dim3 turned((P + 31) / 32, (nc / 2 + 7) / 8);
     if (out)
-        hipLaunchKernelGGL(k_vertex_reduce_rows, dim3((P + 31) / 32, (nc / 2 + 7) / 8), dim3(256), 0, s, bm, P, part,
-                           Y, nc, out);
+        hipLaunchKernelGGL(k_vertex_reduce_rows, turned, dim3(256), 0, s, bm, P, part, Y, nc, out);
+    else if (step)
+        hipLaunchKernelGGL(k_vertex_reduce_step, turned, dim3(256), 0, s, bm, P, part, Y, nc, *step);
     else
         hipLaunchKernelGGL(k_vertex_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, bm, P, part, Y,
                            nc);
