@@ -558,7 +558,7 @@ int chi0_set_timing_filter(chi0_ctx *ctx, const char *names);
  * call's stream, and keeps the fastest for that class.  All variants accumulate each
  * output element in the same order, so tuning never changes a result, only
  * the time; it does add a synchronisation of the stream on each new class.
- * Products of up to 6e8 multiply-adds run a kernel that has no variants, in
+ * Products of up to 8e8 multiply-adds run a kernel that has no variants, in
  * every mode, and make no entry.
  * chi0_set_autotune(ctx, mode): 1 tunes (default), 0 uses the 64x64 variant
  * everywhere, 100 + v forces variant v wherever it is valid for the shape

@@ -317,13 +317,16 @@ void k_dgemm_few(int N, int K, const double *__restrict__ A, int lda, const doub
     }
 }
 
-// Up to 6e8 multiply-adds the split-k form is faster; past that its operand
+// Up to 8e8 multiply-adds the split-k form is faster; past that its operand
 // reads (32 x 32 tiles) bound it.  16 x 16 tiles up to 2^17 outputs, where the
 // larger ones would be fewer than 128 workgroups.  us at M x N x K, tiled kernel and
 // its reduction / 16 x 16 / 32 x 32: 64x96x112 8.6 / 2.7 / 3.7; 64x1152x112 9.2 /
 // 3.3 / 3.8; 320x480x544 15.3 / 11.0 / 9.4; 320x1440x544 21.7 / 24.7 / 16.4;
-// 576x2880x304 (5e8) 37.3 / 45.1 / 29.6; 320x5760x544 (1e9) 57.6 / 83.5 / 53.8.
-constexpr int64_t FEW_WORK = 600000000LL, FEW_SMALL = 131072;
+// 576x2880x304 (5e8) 37.3 / 45.1 / 29.6.  Against the tiled kernel without split K
+// (choose_splits): 320x3840x544 (6.7e8) 45.4 / 35.5, 576x3840x304 36.7 / 36.9,
+// 320x4800x544 (8.4e8) 44.4 / 42.3, 576x4800x304 36.7 / 44.4, 320x5760x544 (1e9)
+// 46 / 53.9.
+constexpr int64_t FEW_WORK = 800000000LL, FEW_SMALL = 131072;
 
 template <int TM, int TN, int NW, int KU>
 static void launch_few(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const double *A, int lda,
@@ -343,12 +346,15 @@ static void launch_few(Tracer *t, hipStream_t s, const char *name, int M, int N,
 // Number of K splits: enough workgroups to fill 256 CUs a few times over,
 // each split keeping >= 4 K tiles of 16; limited by the scratch capacity.  The
 // splits have equal lengths *ks of whole tiles; S *ks may exceed K (the last
-// split then sums zero padding) but not kpad, the operands' K extent.
+// split then sums zero padding) but not kpad, the operands' K extent.  One tile
+// per CU is enough to go without: the partial sums' way through memory costs more
+// than idle matrix cores (us, split and summed / whole: 320x5760x544 59.8 / 46,
+// 576x5760x304 60.0 / 46, 576x3000x576 53.4 / 48.9, 1280x1600x1008 90.7 / 82.2).
 static int choose_splits(int M, int N, int K, int kpad, size_t scratch_elems, int *ks) {
     const int tiles = (M / 64) * ((N + 63) / 64);
     const int KT = K / 16;
     int S = 1;
-    while (S < 16 && tiles * S < 1024) {
+    while (tiles < 256 && S < 16 && tiles * S < 1024) {
         const int S2 = 2 * S, kt2 = (KT + S2 - 1) / S2;
         if (kt2 < 4 || (int64_t)S2 * kt2 * 16 > kpad || (size_t)S2 * M * (size_t)N > scratch_elems) break;
         S = S2;
