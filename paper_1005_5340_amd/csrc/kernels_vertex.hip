@@ -32,8 +32,8 @@ __device__ __forceinline__ dbl4 mfma16(double a, double b, dbl4 c) {
 // wavefronts: groups of row blocks times slices of the reduction, which cut the
 // longest block's rounds; the slices' sums are added in a fixed order through
 // LDS.  How a workgroup splits depends on its block alone.  One vector, 60
-// atoms: gather 18.6 -> 13.9 us, projection 14.7 -> 8.9 us; 12 atoms, 48
-// columns 16.1 -> 12.1, 15.5 -> 7.9 (with the tracer's ~5 us).
+// atoms: gather 18.6 -> 13.9 us, projection 14.7 -> 8.9 us; projection at 12
+// atoms, 48 columns 15.5 -> 7.9 (with the tracer's ~5 us).
 constexpr int VRB = 4;     // 16-row MFMA blocks per wave (rows <= 256 = NB_MAX^2)
 constexpr int PCH = 256;   // product ids staged in LDS per chunk
 
@@ -131,12 +131,12 @@ __device__ __forceinline__ void vertex_sum_slices(dbl4 (&acc)[NR], int KS, int R
     }
 }
 
-// The gather for few workgroups (VSPLIT_BLK).
+// The gather for up to 16 columns and few blocks.
 template <int KU>
 __global__ __launch_bounds__(512)
 void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double *__restrict__ dV, int nc) {
     __shared__ dbl4 red[4][VRB][64];
-    const int k = blockIdx.x, j = blockIdx.y * 16 + (threadIdx.x & 15);   // block, this lane's column
+    const int k = blockIdx.x, j = threadIdx.x & 15;   // block, this lane's column
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nAB = bm.blk_na[k] * bm.blk_nb[k];
     const int np = bm.blk_nprod[k];
@@ -194,11 +194,12 @@ void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double 
     }
 }
 
-// Blocks times 16-column groups up to which the kernels split (the projection
-// also any number of blocks of up to 16 columns): past four workgroups per CU the
-// launch runs in several waves and the idle wavefronts of the short blocks cost
-// more than the long ones gain (gather, us, four waves / eight: 758 blocks 20.3 /
-// 14.8, 780 17.2 / 14.9; 1246 12.7 / 17.0, 1349 12.8 / 18.9, 1954 23.5 / 28.2).
+// Blocks (times 16-column groups, the projection) up to which the kernels split,
+// the gather for up to 16 columns; the projection of up to 16 columns splits for
+// any number of blocks.  Past four workgroups per CU the launch runs in several
+// waves and the idle wavefronts of the short blocks cost more than the long ones
+// gain (gather, us, four waves / eight: 758 blocks 20.3 / 14.8, 780 17.2 / 14.9;
+// 1246 12.7 / 17.0, 1349 12.8 / 18.9, 1954 23.5 / 28.2).
 constexpr int VSPLIT_BLK = 1024;
 
 // 16-column MFMA blocks per workgroup for nc columns: 1 up to 16 columns,
@@ -210,9 +211,8 @@ void launch_vertex_gather(Tracer *t, hipStream_t s, const BlockMapDev &bm, int n
     const int vc = vertex_vc(nc);
     dim3 grid(n_blk, (nc + 16 * vc - 1) / (16 * vc));
     trace_begin(t, "vertex_gather", s);
-    const int c16 = (nc + 15) / 16;
-    if (n_blk * c16 <= VSPLIT_BLK)
-        hipLaunchKernelGGL((k_vertex_gather_split<8>), dim3(n_blk, c16), dim3(512), 0, s, bm, Z, dV, nc);
+    if (vc == 1 && n_blk <= VSPLIT_BLK)
+        hipLaunchKernelGGL((k_vertex_gather_split<8>), dim3(n_blk), dim3(512), 0, s, bm, Z, dV, nc);
     else if (vc == 1)
         hipLaunchKernelGGL((k_vertex_gather<1, 8>), grid, dim3(256), 0, s, bm, Z, dV, nc);
     else if (vc == 2)
