@@ -886,6 +886,27 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
     launch_vertex_contract(t, s, c->bm, c->n_blk, c->P, o.W, o.part, o.Yout, nc, w, c->max_nprod, out, step);
 }
 
+// z (nb vectors) to the operator's columns and omega (host, [nb]) to the device.
+// Few frequencies travel as kernel arguments: a copy from pageable memory costs
+// the host several times a launch.  A stream being captured keeps the copy, whose
+// node reads the caller's array at each replay.
+static int put_input(chi0_ctx *c, Tracer *t, hipStream_t s, const double *z, const double *omega, int nb, OpWork &o) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (nb <= OMEGA_ARGS && hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;
+    }
+    OmegaArgs oa{};
+    if (nb <= OMEGA_ARGS && cap == hipStreamCaptureStatusNone) {
+        oa.n = nb;
+        std::copy(omega, omega + nb, oa.w);
+    } else {
+        HIPCHK(c, hipMemcpyAsync(o.omega_dev, omega, (size_t)nb * 8, hipMemcpyHostToDevice, s));
+    }
+    launch_rows_to_cols(t, s, z, nb, c->P, o.Zin, oa, o.omega_dev);
+    return CHI0_OK;
+}
+
 // normwise relative error of one low-precision chi0 application (measured on
 // the test systems: ~3e-7 with FP32 transforms, ~5-7e-6 with split BF16 x 3)
 static const double kOpErrFP32 = 3e-7, kOpErrBF16X3 = 6e-6;
@@ -922,7 +943,7 @@ extern "C" int chi0_apply(chi0_ctx *c, int32_t n_rhs, const double *omega, doubl
             if (!c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-            launch_rows_to_cols(&c->tracer, c->cap_stream, z, n_rhs, c->P, ow.Zin);
+            launch_rows_to_cols(&c->tracer, c->cap_stream, z, n_rhs, c->P, ow.Zin, OmegaArgs{}, nullptr);
             run_chi0(c, ow, c->cap_stream, n_rhs, eps, precision, ow.omega_dev, &c->tracer, &c->tuner, out);
             HIPCHK(c, hipStreamEndCapture(c->cap_stream, &g));
             const hipError_t e = hipGraphInstantiate(&c->apply_exec, g, nullptr, nullptr, 0);
@@ -942,8 +963,7 @@ extern "C" int chi0_apply(chi0_ctx *c, int32_t n_rhs, const double *omega, doubl
     }
     for (int r0 = 0; r0 < n_rhs; r0 += cap) {
         const int nb = std::min(cap, n_rhs - r0), nc = 2 * nb;
-        HIPCHK(c, hipMemcpyAsync(ow.omega_dev, omega + r0, (size_t)nb * 8, hipMemcpyHostToDevice, s));
-        launch_rows_to_cols(&c->tracer, s, z + (int64_t)r0 * c->P * 2, nb, c->P, ow.Zin);
+        CHK(put_input(c, &c->tracer, s, z + (int64_t)r0 * c->P * 2, omega + r0, nb, ow));
         run_chi0(c, ow, s, nb, eps, precision, ow.omega_dev, &c->tracer, &c->tuner,
                  out + (int64_t)r0 * c->P * 2);
     }
@@ -1024,11 +1044,13 @@ extern "C" int chi0_apply_noalloc(chi0_ctx *c, int32_t n_rhs, const double *omeg
     o.gemm_scratch = left >= 2 * 64 * 64 ? base + L.gemm : nullptr;
     o.gemm_scratch_n = o.gemm_scratch ? (size_t)left : 0;
     const int nc = 2 * n_rhs;
-    // The scratch keeps the last call's contents (any system, any n_rhs): clear
-    // the buffers this call uses, whose padding the GEMMs read as zeros.
-    launch_zero(nullptr, s, base, L.gemm);
-    HIPCHK(c, hipMemcpyAsync(o.omega_dev, omega, (size_t)n_rhs * 8, hipMemcpyHostToDevice, s));
-    launch_rows_to_cols(nullptr, s, z, n_rhs, c->P, o.Zin);
+    // The scratch keeps the last call's contents (any system, any n_rhs).  All
+    // that this call reads it has written, but for the rows N <= b < N_pad of Tt,
+    // which the first dense product multiplies by X's zero padding: clear those
+    // (all of the buffers: 11.8 us at 60 atoms, 5 vectors).
+    const int64_t mcol = (int64_t)c->No_pad * nc;
+    if (c->N_pad > c->N) launch_zero(nullptr, s, o.Tt + c->N * mcol, (c->N_pad - c->N) * mcol);
+    CHK(put_input(c, nullptr, s, z, omega, n_rhs, o));
     run_chi0(c, o, s, n_rhs, eps, CHI0_PREC_FP64, o.omega_dev, nullptr, nullptr, out);
     HIPCHK(c, hipGetLastError());
     return CHI0_OK;

@@ -416,7 +416,14 @@ void launch_bl_step(hipStream_t s, int npts, int P, int k, const double *Yout, c
                     int ldalpha, double *beta, int ldbeta, double *rnorm, int ldrn, int *flag);
 
 // apply: caller rows [r][P] complex <-> operator columns [P_pad][ncp]
-void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin);
+// om: frequencies that the launch also writes to omega_dev (om.n = 0: none).
+constexpr int OMEGA_ARGS = 64;
+struct OmegaArgs {
+    int n;
+    double w[OMEGA_ARGS];
+};
+void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin, const OmegaArgs &om,
+                         double *omega_dev);
 void launch_zero(Tracer *t, hipStream_t s, double *p, int64_t n);
 
 }  // namespace chi0

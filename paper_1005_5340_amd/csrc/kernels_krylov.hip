@@ -1202,9 +1202,11 @@ void launch_alpha_cross(Tracer *t, hipStream_t s, int n_omega, int n_drive, int 
 // 32 products by 8 vectors per workgroup, turned through LDS: z in 512-byte
 // runs, Zin in 128-byte ones.
 __global__ __launch_bounds__(256)
-void k_rows_to_cols(const double *__restrict__ z, int P, double *__restrict__ Zin, int nb) {
+void k_rows_to_cols(const double *__restrict__ z, int P, double *__restrict__ Zin, int nb, OmegaArgs om,
+                    double *__restrict__ omega_dev) {
     __shared__ double2 tile[8][33];
     const int t = threadIdx.x, mu0 = blockIdx.x * 32, r0 = blockIdx.y * 8;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && t < om.n) omega_dev[t] = om.w[t];
     const int mi = mu0 + t % 32, ri = r0 + t / 32;
     if (mi < P && ri < nb) tile[t / 32][t % 32] = reinterpret_cast<const double2 *>(z)[(int64_t)ri * P + mi];
     __syncthreads();
@@ -1212,9 +1214,11 @@ void k_rows_to_cols(const double *__restrict__ z, int P, double *__restrict__ Zi
     if (mu < P && r < nb) reinterpret_cast<double2 *>(Zin)[(int64_t)mu * nb + r] = tile[t % 8][t / 8];
 }
 
-void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin) {
+void launch_rows_to_cols(Tracer *t, hipStream_t s, const double *z, int nb, int P, double *Zin, const OmegaArgs &om,
+                         double *omega_dev) {
     trace_begin(t, "rows_to_cols", s);
-    hipLaunchKernelGGL(k_rows_to_cols, dim3((P + 31) / 32, (nb + 7) / 8), dim3(256), 0, s, z, P, Zin, nb);
+    hipLaunchKernelGGL(k_rows_to_cols, dim3((P + 31) / 32, (nb + 7) / 8), dim3(256), 0, s, z, P, Zin, nb, om,
+                       omega_dev);
     trace_end(t, s);
 }
 
