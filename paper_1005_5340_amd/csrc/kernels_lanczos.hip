@@ -221,37 +221,46 @@ void k_lz_axpy(LanczosDev L) {
     lz_block_part<NC>(acc, L.part);
 }
 
-// b_j = |w|.  A sequence ends (length j + 1, b_j = 0 and every later
-// coefficient 0) when b_j <= 1e-12 (|a_j| + b_{j-1}): an invariant subspace.
-template <int NC>
-__global__ __launch_bounds__(256)
-void k_lz_beta(LanczosDev L, int nblk, int gated) {
-    if (gated && L.flag && !L.flag[0]) return;   // no pass: b_j of the head stands
-    __shared__ double sh[4];
-    const int j = *L.step - 1;
-    for (int s = 0; s < NC; ++s) {
-        const double v = lz_sum_parts<NC>(L.part, nblk, s, sh);
-        if (threadIdx.x == 0) {
-            const double bj = sqrt(v);
-            const double aj = L.a[(int64_t)j * NC + s];
-            const double bm = j > 0 ? L.b[(int64_t)(j - 1) * NC + s] : 0.0;
-            const bool ended = L.len[s] <= j || !(bj > 1e-12 * (fabs(aj) + bm));
-            if (ended && L.len[s] > j) L.len[s] = j + 1;
-            L.b[(int64_t)j * NC + s] = ended ? 0.0 : bj;
-        }
+// b_j = |w| of sequence s from the nblk partial sums, by a whole workgroup.  A
+// sequence ends (length j + 1, b_j = 0 and every later coefficient 0) when
+// b_j <= 1e-12 (|a_j| + b_{j-1}): an invariant subspace.  store: one workgroup
+// keeps b_j and the length; the others may read either length and decide alike.
+__device__ __forceinline__ double lz_beta(const LanczosDev &L, int nc, int nblk, int j, int s, double *sh, bool store) {
+    const int t = threadIdx.x;
+    double v = 0.0;
+    if (t < 256)
+        for (int b = t; b < nblk; b += 256) v += L.part[(int64_t)b * nc + s];
+    v = lz_wave_sum(v);
+    __syncthreads();
+    if ((t & 63) == 0) sh[t >> 6] = v;
+    __syncthreads();
+    const double bj = sqrt((sh[0] + sh[1]) + (sh[2] + sh[3]));
+    const double aj = L.a[(int64_t)j * nc + s];
+    const double bm = j > 0 ? L.b[(int64_t)(j - 1) * nc + s] : 0.0;
+    const bool ended = L.len[s] <= j || !(bj > 1e-12 * (fabs(aj) + bm));
+    if (store && t == 0) {
+        if (ended && L.len[s] > j) L.len[s] = j + 1;
+        L.b[(int64_t)j * nc + s] = ended ? 0.0 : bj;
     }
+    return ended ? 0.0 : bj;
 }
 
-// q_{j+1} = w / b_j in place (0 for an ended sequence); at = St * q_{j+1}.
+// q_{j+1} = w / b_j in place (0 for an ended sequence); at = St * q_{j+1}.  b_j:
+// LZ_B_KEPT is there already, LZ_B_NEW is |w| now (each workgroup adds the partial
+// sums, a launch of one workgroup to do it once took longer), LZ_B_PASS is new
+// after a reorthogonalisation pass and there already without.
+enum { LZ_B_KEPT = 0, LZ_B_NEW = 1, LZ_B_PASS = 2 };
 template <int NC>
 __global__ __launch_bounds__(256)
-void k_lz_scale(LanczosDev L) {
+void k_lz_scale(LanczosDev L, int nblk, int mode) {
+    __shared__ double sh[4];
     const int j = *L.step - 1;
+    const bool fresh = mode == LZ_B_NEW || (mode == LZ_B_PASS && (!L.flag || L.flag[0]));
     double *w = lz_vec(L, j + 1);
     double inv[NC];
 #pragma unroll
     for (int s = 0; s < NC; ++s) {
-        const double bj = L.b[(int64_t)j * NC + s];
+        const double bj = fresh ? lz_beta(L, NC, nblk, j, s, sh, blockIdx.x == 0) : L.b[(int64_t)j * NC + s];
         inv[s] = bj > 0.0 ? 1.0 / bj : 0.0;
     }
     lz_normalise_to_at<NC>(L, w, inv);
@@ -435,7 +444,7 @@ void k_lz_cfrac(const double *__restrict__ a, const double *__restrict__ b, int 
 // written out sequentially; the maximum does not depend on the order.
 constexpr int LZ_OMEGA_THREADS = 1024;
 __global__ __launch_bounds__(LZ_OMEGA_THREADS)
-void k_lz_omega(LanczosDev L, int j) {
+void k_lz_omega(LanczosDev L, int j, int nblk) {
     const int nc = L.nc, t = threadIdx.x;
     const int64_t rl = (int64_t)L.kmax + 2;
     const double ueps = 2.220446049250313e-16, thresh = 1.4901161193847656e-08;   // sqrt(eps)
@@ -445,10 +454,12 @@ void k_lz_omega(LanczosDev L, int j) {
     if (t == 0) need_s = L.flag[1];
     __syncthreads();
     for (int s = 0; s < nc; ++s) {
+        const double bj = lz_beta(L, nc, nblk, j, s, sh, true);
+        __syncthreads();   // sh is used again
         const double *wc = Wr + ((int64_t)(j % 3) * nc + s) * rl;         // row j
         const double *wp = Wr + ((int64_t)((j + 2) % 3) * nc + s) * rl;   // row j - 1
         double *wn = Wr + ((int64_t)((j + 1) % 3) * nc + s) * rl;         // row j + 1
-        const double aj = L.a[(int64_t)j * nc + s], bj = L.b[(int64_t)j * nc + s];
+        const double aj = L.a[(int64_t)j * nc + s];
         const double bm = j > 0 ? L.b[(int64_t)(j - 1) * nc + s] : 0.0;
         if (!(bj > 0.0)) continue;   // ended sequence (uniform across the workgroup)
         const double an = fmax(L.anorm[s], fabs(aj) + bj + bm);
@@ -707,17 +718,9 @@ void lz_passes(Tracer *t, hipStream_t s, const LanczosDev &L, int j, int npass, 
     }
 }
 
-void lz_beta(Tracer *t, hipStream_t s, const LanczosDev &L, int g, int gated = 0) {
-    trace_begin(t, "lanczos_beta", s);
-#define C(N) hipLaunchKernelGGL(k_lz_beta<N>, dim3(1), dim3(256), 0, s, L, g, gated);
-    LZ_NC_SWITCH(L.nc, C)
-#undef C
-    trace_end(t, s);
-}
-
-void lz_scale(Tracer *t, hipStream_t s, const LanczosDev &L, int g, double ta, double vb) {
+void lz_scale(Tracer *t, hipStream_t s, const LanczosDev &L, int g, int mode, double ta, double vb) {
     trace_begin(t, "lanczos_scale", s);
-#define C(N) hipLaunchKernelGGL(k_lz_scale<N>, dim3(g), dim3(256), 0, s, L);
+#define C(N) hipLaunchKernelGGL(k_lz_scale<N>, dim3(g), dim3(256), 0, s, L, g, mode);
     LZ_NC_SWITCH(L.nc, C)
 #undef C
     trace_end(t, s, 2.0 * ta, 3.0 * vb + 8.0 * L.t_alg);
@@ -731,8 +734,7 @@ void launch_lz_step(Tracer *t, hipStream_t s, const LanczosDev &L, int j, double
     const double ta = (double)L.t_alg * L.nc, vb = 8.0 * ta;
     lz_head(t, s, L, g, ta, vb);
     if (!L.ring) lz_passes(t, s, L, j, L.passes, g, ta, vb, part2, h, part3);
-    lz_beta(t, s, L, g);
-    lz_scale(t, s, L, g, ta, vb);
+    lz_scale(t, s, L, g, LZ_B_NEW, ta, vb);
 }
 
 // head of a step with partial reorthogonalisation: the three-term update, b_j and
@@ -741,34 +743,28 @@ void launch_lz_step_head(Tracer *t, hipStream_t s, const LanczosDev &L, int j) {
     const int g = lz_blocks(L);
     const double ta = (double)L.t_alg * L.nc, vb = 8.0 * ta;
     lz_head(t, s, L, g, ta, vb);
-    lz_beta(t, s, L, g);
     trace_begin(t, "lanczos_omega", s);
-    hipLaunchKernelGGL(k_lz_omega, dim3(1), dim3(LZ_OMEGA_THREADS), 0, s, L, j);
+    hipLaunchKernelGGL(k_lz_omega, dim3(1), dim3(LZ_OMEGA_THREADS), 0, s, L, j, g);
     trace_end(t, s);
 }
 
 // a whole step with partial reorthogonalisation, no host decision: the pass
-// kernels and the second b_j are launched every step and return at once when
-// the flag is clear
+// kernels are launched every step and return at once when the flag is clear
 void launch_lz_step_partial(Tracer *t, hipStream_t s, const LanczosDev &L, int j, double *part2, double *h,
                             double *part3) {
     const int g = lz_blocks(L);
     const double ta = (double)L.t_alg * L.nc, vb = 8.0 * ta;
     launch_lz_step_head(t, s, L, j);
     lz_passes(t, s, L, j, 1, g, ta, vb, part2, h, part3);
-    lz_beta(t, s, L, g, 1);
-    lz_scale(t, s, L, g, ta, vb);
+    lz_scale(t, s, L, g, LZ_B_PASS, ta, vb);
 }
 
 void launch_lz_step_tail(Tracer *t, hipStream_t s, const LanczosDev &L, int j, int npass, double *part2, double *h,
                          double *part3) {
     const int g = lz_blocks(L);
     const double ta = (double)L.t_alg * L.nc, vb = 8.0 * ta;
-    if (npass > 0) {
-        lz_passes(t, s, L, j, npass, g, ta, vb, part2, h, part3);
-        lz_beta(t, s, L, g);
-    }
-    lz_scale(t, s, L, g, ta, vb);
+    if (npass > 0) lz_passes(t, s, L, j, npass, g, ta, vb, part2, h, part3);
+    lz_scale(t, s, L, g, npass > 0 ? LZ_B_NEW : LZ_B_KEPT, ta, vb);
 }
 
 void launch_lz_solution_cols(Tracer *t, hipStream_t s, const LanczosDev &L, int kuse, const int *len,
