@@ -2415,8 +2415,8 @@ extern "C" int chi0_lanczos(chi0_ctx *c, int32_t n_drive, const double *drives, 
     CHK(dalloc(c, ws.buf, &L.b, (int64_t)kmax * nc));
     CHK(dalloc(c, ws.buf, &L.cn2, nc));
     CHK(dalloc(c, ws.buf, &L.len, nc));
-    CHK(dalloc(c, ws.buf, &L.step, 1));
-    CHK(dalloc(c, ws.buf, &L.part, (int64_t)LZ_BLOCKS * nc));
+    CHK(dalloc(c, ws.buf, &L.step, 2));
+    CHK(dalloc(c, ws.buf, &L.part, (int64_t)2 * LZ_BLOCKS * nc));
     if (!ring) {
         CHK(dalloc(c, ws.buf, &part2, (int64_t)64 * (kmax + 1) * nc));
         CHK(dalloc(c, ws.buf, &h, (int64_t)(kmax + 1) * nc));

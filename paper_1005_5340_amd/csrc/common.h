@@ -360,8 +360,8 @@ struct LanczosDev {
     double *a, *b;         // [kmax][nc] recursion coefficients
     double *cn2;           // [nc] |c|^2
     int *len;              // [nc] recursion length (kmax until an invariant subspace ends it)
-    int *step;             // current step (device counter)
-    double *part;          // [LZ_BLOCKS][nc] partial sums
+    int *step;             // device counters: step j for its first kernels, j + 1 for its later ones
+    double *part;          // [2][LZ_BLOCKS][nc] partial sums: of q . w, of |w|^2
     // partial reorthogonalisation (null otherwise): Simon's estimates of q_j . q_i in a
     // ring of three rows [3][nc][kmax + 2], the running |T| estimate [nc], and the step's
     // decision: flag[0] = run the pass, flag[1] = the next step must run it too

@@ -122,7 +122,7 @@ void k_lz_start_fin(LanczosDev L, int nblk) {
             L.len[s] = v > 0.0 ? L.kmax : 0;
         }
     }
-    if (threadIdx.x == 0) *L.step = 0;
+    if (threadIdx.x == 0) L.step[0] = L.step[1] = 0;
 }
 
 // q *= inv (per sequence) in place on the compact rows, and at = St * q on
@@ -163,7 +163,7 @@ void k_lz_start_scale(LanczosDev L) {
 template <int NC>
 __global__ __launch_bounds__(256)
 void k_lz_combine(LanczosDev L) {
-    const int j = *L.step;
+    const int j = L.step[0];
     const double *q = lz_vec(L, j);
     double *w = lz_vec(L, j + 1);
     double acc[NC] = {};
@@ -181,34 +181,27 @@ void k_lz_combine(LanczosDev L) {
     lz_block_part<NC>(acc, L.part);
 }
 
-// a_j = q_j . w; advances the step counter (later kernels of the step read j = step - 1).
+// a_j = q_j . w, which each workgroup adds up from the partial sums of
+// k_lz_combine, and w -= a_j q_j + b_{j-1} q_{j-1}; partial sums of |w|^2 in the
+// second half of L.part.  The first workgroup keeps a_j and hands j + 1 to the
+// step's later kernels in L.step[1]; k_lz_scale, the last one, to the next step in
+// L.step[0], so no kernel writes the counter that it reads.
 template <int NC>
 __global__ __launch_bounds__(256)
-void k_lz_alpha(LanczosDev L, int nblk) {
+void k_lz_axpy(LanczosDev L, int nblk) {
     __shared__ double sh[4];
-    const int j = *L.step;
-    for (int s = 0; s < NC; ++s) {
-        const double v = lz_sum_parts<NC>(L.part, nblk, s, sh);
-        if (threadIdx.x == 0) L.a[(int64_t)j * NC + s] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) *L.step = j + 1;
-}
-
-// w -= a_j q_j + b_{j-1} q_{j-1}; partial sums of |w|^2.
-template <int NC>
-__global__ __launch_bounds__(256)
-void k_lz_axpy(LanczosDev L) {
-    const int j = *L.step - 1;
+    const int j = L.step[0];
     const double *q = lz_vec(L, j);
     const double *qm = lz_vec(L, j > 0 ? j - 1 : 0);
     double *w = lz_vec(L, j + 1);
     double aj[NC], bm[NC];
 #pragma unroll
     for (int s = 0; s < NC; ++s) {
-        aj[s] = L.a[(int64_t)j * NC + s];
+        aj[s] = lz_sum_parts<NC>(L.part, nblk, s, sh);
         bm[s] = j > 0 ? L.b[(int64_t)(j - 1) * NC + s] : 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) L.a[(int64_t)j * NC + s] = aj[s];
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.step[1] = j + 1;
     double acc[NC] = {};
     for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < L.tc; r += (int64_t)gridDim.x * 256) {
 #pragma unroll
@@ -218,7 +211,7 @@ void k_lz_axpy(LanczosDev L) {
             acc[s] += v * v;
         }
     }
-    lz_block_part<NC>(acc, L.part);
+    lz_block_part<NC>(acc, L.part + LZ_BLOCKS * NC);
 }
 
 // b_j = |w| of sequence s from the nblk partial sums, by a whole workgroup.  A
@@ -229,7 +222,7 @@ __device__ __forceinline__ double lz_beta(const LanczosDev &L, int nc, int nblk,
     const int t = threadIdx.x;
     double v = 0.0;
     if (t < 256)
-        for (int b = t; b < nblk; b += 256) v += L.part[(int64_t)b * nc + s];
+        for (int b = t; b < nblk; b += 256) v += L.part[(int64_t)(LZ_BLOCKS + b) * nc + s];
     v = lz_wave_sum(v);
     __syncthreads();
     if ((t & 63) == 0) sh[t >> 6] = v;
@@ -254,7 +247,7 @@ template <int NC>
 __global__ __launch_bounds__(256)
 void k_lz_scale(LanczosDev L, int nblk, int mode) {
     __shared__ double sh[4];
-    const int j = *L.step - 1;
+    const int j = L.step[1] - 1;
     const bool fresh = mode == LZ_B_NEW || (mode == LZ_B_PASS && (!L.flag || L.flag[0]));
     double *w = lz_vec(L, j + 1);
     double inv[NC];
@@ -263,6 +256,7 @@ void k_lz_scale(LanczosDev L, int nblk, int mode) {
         const double bj = fresh ? lz_beta(L, NC, nblk, j, s, sh, blockIdx.x == 0) : L.b[(int64_t)j * NC + s];
         inv[s] = bj > 0.0 ? 1.0 / bj : 0.0;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.step[0] = j + 1;
     lz_normalise_to_at<NC>(L, w, inv);
 }
 
@@ -285,7 +279,7 @@ __global__ __launch_bounds__(256)
 void k_lz_dots(LanczosDev L, int nq, int nsplit, double *part2) {
     if (L.flag && !L.flag[0]) return;   // partial reorthogonalisation: no pass this step
     const int i = blockIdx.y, rs = blockIdx.x;
-    const int j = *L.step - 1;
+    const int j = L.step[1] - 1;
     const double *q = lz_vec(L, i);
     const double *w = lz_vec(L, j + 1);
     double acc[NC] = {};
@@ -385,7 +379,7 @@ template <int NC>
 __global__ __launch_bounds__(256)
 void k_lz_update_fin(LanczosDev L, int ngroup, const double *__restrict__ part3) {
     if (L.flag && !L.flag[0]) return;
-    const int j = *L.step - 1;
+    const int j = L.step[1] - 1;
     double *w = lz_vec(L, j + 1);
     double acc[NC] = {};
     for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < L.tc; r += (int64_t)gridDim.x * 256) {
@@ -398,7 +392,7 @@ void k_lz_update_fin(LanczosDev L, int ngroup, const double *__restrict__ part3)
             acc[s] += v * v;
         }
     }
-    lz_block_part<NC>(acc, L.part);
+    lz_block_part<NC>(acc, L.part + LZ_BLOCKS * NC);
 }
 
 // alpha_k(w) = |c|^2 / g_0 with g_{k-1} = a_{k-1} - z, g_i = a_i - z - b_i^2 / g_{i+1},
@@ -679,14 +673,12 @@ namespace {
 // combine (w = Om2 q_j), a_j, the three-term update
 void lz_head(Tracer *t, hipStream_t s, const LanczosDev &L, int g, double ta, double vb) {
     trace_begin(t, "lanczos_combine", s);
-#define C(N)                                                                   \
-    hipLaunchKernelGGL(k_lz_combine<N>, dim3(g), dim3(256), 0, s, L);          \
-    hipLaunchKernelGGL(k_lz_alpha<N>, dim3(1), dim3(256), 0, s, L, g);
+#define C(N) hipLaunchKernelGGL(k_lz_combine<N>, dim3(g), dim3(256), 0, s, L);
     LZ_NC_SWITCH(L.nc, C)
 #undef C
     trace_end(t, s, 4.0 * ta, 3.0 * vb + 16.0 * L.t_alg);
     trace_begin(t, "lanczos_axpy", s);
-#define C(N) hipLaunchKernelGGL(k_lz_axpy<N>, dim3(g), dim3(256), 0, s, L);
+#define C(N) hipLaunchKernelGGL(k_lz_axpy<N>, dim3(g), dim3(256), 0, s, L, g);
     LZ_NC_SWITCH(L.nc, C)
 #undef C
     trace_end(t, s, 6.0 * ta, 4.0 * vb);
