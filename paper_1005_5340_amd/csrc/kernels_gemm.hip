@@ -39,10 +39,9 @@ struct Mma4 {
     }
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
 };
-// The gathered occupied transforms keep the single 16x16x4 FP64 product per
-// tile (A[l % 16][l / 16]): with a dozen accumulators per wave they are not
-// bound by the MFMA issue rate, and the four A fragments of the 4-block form
-// made them slower.
+// The kernels for few columns take the single 16x16x4 FP64 product per tile
+// (A[l % 16][l / 16]): they wait on memory, not on the MFMA rate, and load one
+// value of A per lane and k step instead of four.
 struct Mma16d {
     typedef dbl4 acc;
     static constexpr int NA = 1;
