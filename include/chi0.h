@@ -52,8 +52,11 @@ extern "C" {
  * The vertex contractions, the frequency factor, K, Gram-Schmidt, the
  * Hessenberg problem and the true residual are always FP64.
  *   FP64    every transform in FP64: on the FP64 matrix cores or, for the two
- *           dense ones of large systems, on the INT8 ones in residue arithmetic
- *           (its error is below that of an FP64 sum of the same length).
+ *           dense ones of large systems, on the INT8 ones in residue arithmetic.
+ *           Its error is bounded by the norms of the operands' rows and columns;
+ *           where that may exceed the bound of an FP64 sum for any element (its
+ *           own terms are small against the norms) the tile is computed in FP64,
+ *           so that every element keeps K 2^-53 sum_k |a_k| |b_k| either way.
  *   FP32    transforms on FP32 operands with FP32 accumulation, FP32 intermediates
  *           (dense ones: each operand as three BF16 terms, which hold it whole,
  *           six BF16 products).

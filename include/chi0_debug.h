@@ -62,10 +62,20 @@ int chi0_debug_lz_passes(const chi0_ctx *ctx, int32_t *passes, double *b_pre, in
 
 /* C [M][N] = A [M][K] B [K][N] (host, row-major) by the panel GEMM that the
  * dense transforms of `precision` use (FP64: the product on the INT8 matrix
- * cores, M a multiple of 4), with at most `work_bytes` of workspace for B (so
- * that small sizes also go in chunks of columns).  Needs a device context, no system.  Synchronous. */
+ * cores alone, without the check of its operands, M a multiple of 4, K < 2^17),
+ * with at most `work_bytes` of workspace for B (so that small sizes also go in
+ * chunks of columns).  Needs a device context, no system.  Synchronous. */
 int chi0_debug_panel_gemm(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N, int32_t K, const double *A,
                           const double *B, int64_t work_bytes, double *C);
+
+/* The same as the operator runs it (M a multiple of 64): in FP64 with the check of
+ * the operands, *fp64_tiles (may be NULL) the number of 64 x 128 tiles that went to
+ * the FP64 matrix cores for it.  n_omega > 0: with the frequency factor, columns
+ * (E, r, Re / Im) as in the operator (N a multiple of 2 n_omega), D [E][M] the
+ * transition energies.  */
+int chi0_debug_dense_transform(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N, int32_t K, const double *A,
+                               const double *B, int64_t work_bytes, int32_t n_omega, const double *omega, double eps,
+                               double occ, const double *D, double *C, int32_t *fp64_tiles);
 
 /* Host eigen-decomposition of a Hermitian n x n matrix (row-major interleaved
  * complex): eigenvalues descending in w[n], eigenvectors as columns of V. */

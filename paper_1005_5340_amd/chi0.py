@@ -159,6 +159,9 @@ def lib():
     L.chi0_debug_panel_gemm.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _dp, _dp,
                                         C.c_int64, _dp]
     L.chi0_debug_panel_gemm.restype = C.c_int
+    L.chi0_debug_dense_transform.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _dp, _dp,
+                                             C.c_int64, C.c_int32, _dp, C.c_double, C.c_double, _dp, _dp, _i32p]
+    L.chi0_debug_dense_transform.restype = C.c_int
     L.chi0_debug_eigh.argtypes = [C.c_int32, _dp, _dp, _dp]
     L.chi0_debug_eigh.restype = C.c_int
     L.chi0_lanczos_opts_default.argtypes = [C.POINTER(LanczosOpts)]
@@ -461,6 +464,20 @@ class Context:
         self._check(self._L.chi0_debug_panel_gemm(self._h, int(precision), M, N, K, _ptr(A), _ptr(B),
                                                   int(work_bytes), _ptr(out)))
         return out
+
+    def debug_dense_transform(self, A, B, precision: int, work_bytes: int = 1 << 30, omega=None, eps: float = 0.0,
+                              occ: float = 2.0, D=None):
+        """Test hook: A @ B as the operator runs it, times the frequency factor if omega is given
+        (chi0_debug_dense_transform); also the number of tiles that went to the FP64 matrix cores."""
+        A, B = _f64(A), _f64(B)
+        (M, K), N = A.shape, B.shape[1]
+        om = None if omega is None else _f64(omega)
+        Dh = None if D is None else _f64(D)
+        out, tiles = np.zeros((M, N)), np.zeros(1, np.int32)
+        self._check(self._L.chi0_debug_dense_transform(
+            self._h, int(precision), M, N, K, _ptr(A), _ptr(B), int(work_bytes), 0 if om is None else om.size, _ptr(om),
+            float(eps), float(occ), _ptr(Dh), _ptr(out), _ptr(tiles, _i32p)))
+        return out, int(tiles[0])
 
     def set_graphs(self, enable: bool):
         """Replay repeated chi0_apply calls from a HIP graph (chi0_set_graphs)."""

@@ -296,11 +296,13 @@ static int crt_alloc(chi0_ctx *c, DevBuf &buf, CrtDev &p, int rows, int K) {
     p.p.nkb = (int)round_up((K + 15) / 16, CRT_KB);
     p.p.plane = (int64_t)p.p.nkb * p.p.ld;
     double *d = nullptr;
-    CHK(dalloc(c, buf, &d, p.p.plane * CRT_S * 2));
+    CHK(dalloc(c, buf, &d, p.p.plane * CRT_P * 2));
     p.p.data = d;
-    CHK(dalloc(c, buf, &p.sm, p.p.ld));
-    CHK(dalloc(c, buf, &p.si, p.p.ld));
-    CHK(dalloc(c, buf, &p.se, p.p.ld));
+    CHK(dalloc(c, buf, &p.sc.sm, p.p.ld));
+    CHK(dalloc(c, buf, &p.sc.si, p.p.ld));
+    CHK(dalloc(c, buf, &p.sc.se, p.p.ld));
+    CHK(dalloc(c, buf, &p.sc.nrm, p.p.ld));
+    CHK(dalloc(c, buf, &p.sc.rnz, p.p.ld));
     return CHI0_OK;
 }
 
@@ -694,7 +696,7 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
         // residues of the orbital matrices where some batch (a multiple of 2 No16 columns) uses them
         auto some_batch = [&](int M, int K) {
             const int64_t c1 = 2 * (int64_t)c->No16, most = c1 * kMaxBatch;
-            return crt_pays(M, K, most) || crt_pays(M, K, std::max<int64_t>(c1, std::min<int64_t>(most, 8192 / c1 * c1)));
+            return crt_pays(M, K, most) || crt_pays(M, K, std::max<int64_t>(c1, std::min<int64_t>(most, CRT_FEW / c1 * c1)));
         };
         if (some_batch(c->Nv_pad, N)) CHK(crt_alloc(c, sb, c->Xvt_crt, c->Nv_pad, N));
         if (some_batch(c->N_pad, Nv)) CHK(crt_alloc(c, sb, c->Xv_crt, c->N_pad, Nv));
@@ -853,19 +855,22 @@ static void run_chi0(chi0_ctx *c, OpWork &o, hipStream_t s, int nb, double eps, 
         const double b3 = 8.0 * (w.Nv * w.No * nc + w.N * w.No * nc + w.N * w.Nv);
         if (o.crt && c->Xvt_crt.p.data && crt_pays(c->Nv_pad, c->N, ncol)) {
             const LorentzArgs la{c->Dlt, omega, c->Nv_pad, nc, eps, c->occ};
+            const CrtExact x{c->Xvt, c->N_pad, c->N16};
             launch_crt_gemm(t, s, "virt_transform_crt", c->Nv_pad, ncol, c->N, c->Xvt_crt, o.Tt, mcol, o.crt,
-                            o.crt_bytes, o.at, (int)mcol, CRT_S * fl, b2, &la);
+                            o.crt_bytes, o.at, (int)mcol, CRT_S * fl, b2, &la, &x);
         } else {
             launch_dgemm_lorentz(t, s, c->Nv_pad, ncol, c->N16, c->N_pad, c->Xvt, c->N_pad, o.Tt, (int)mcol,
                                  o.at, (int)mcol, c->Dlt, c->Nv_pad, omega, eps, c->occ, nc, f2, b2, o.gemm_scratch,
                                  o.gemm_scratch_n, tu);
         }
-        if (o.crt && c->Xv_crt.p.data && crt_pays(c->N_pad, c->Nv, ncol))
+        if (o.crt && c->Xv_crt.p.data && crt_pays(c->N_pad, c->Nv, ncol)) {
+            const CrtExact x{c->Xv, c->Nv_pad, c->Nv16};
             launch_crt_gemm(t, s, "virt_back_crt", c->N_pad, ncol, c->Nv, c->Xv_crt, o.at, mcol, o.crt, o.crt_bytes,
-                            o.Ut, (int)mcol, CRT_S * fl, b3, nullptr);
-        else
+                            o.Ut, (int)mcol, CRT_S * fl, b3, nullptr, &x);
+        } else {
             launch_dgemm(t, s, "virt_back", c->N_pad, ncol, c->Nv16, c->Nv_pad, c->Xv, c->Nv_pad, o.at, (int)mcol,
                          o.Ut, (int)mcol, fl, b3, o.gemm_scratch, o.gemm_scratch_n, tu);
+        }
         launch_occ_back(t, s, c->bm, c->n_atoms, c->max_rows, c->Xo, c->No_pad, c->No16, o.Ut, o.W, nc, w);
     } else {
         launch_occ_transform_f32(t, s, c->bm, c->n_atoms, c->Xo32, c->No_pad, c->No16, o.dV, o.Tt32, nc, w);
@@ -2156,7 +2161,8 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     if (c->device < 0) return fail(c, CHI0_ENOSYS, "no device context");
     if (M < 1 || N < 1 || K < 1 || !A || !B || !C) return fail(c, CHI0_EINVAL, "bad sizes or NULL");
     if (precision < CHI0_PREC_FP64 || precision > CHI0_PREC_BF16X3) return fail(c, CHI0_EINVAL, "unknown precision");
-    if (precision == CHI0_PREC_FP64 && M % 4) return fail(c, CHI0_EINVAL, "M must be a multiple of 4");
+    if (precision == CHI0_PREC_FP64 && (M % 4 || K >= (1 << 17)))
+        return fail(c, CHI0_EINVAL, "M must be a multiple of 4 and K below 2^17");
     HIPCHK(c, hipSetDevice(c->device));
     struct Scope {
         DevBuf buf;
@@ -2184,7 +2190,7 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
         HIPCHK(c, hipDeviceSynchronize());
         launch_crt_operand(c->stream, a_d, K, M, M, a);
         launch_crt_gemm(nullptr, c->stream, "panel", M, N, K, a, bd, N, work, (size_t)work_bytes, cd, N, 0.0, 0.0,
-                        nullptr);
+                        nullptr, nullptr);
         HIPCHK(c, hipStreamSynchronize(c->stream));
         HIPCHK(c, hipGetLastError());
         HIPCHK(c, hipMemcpy(C, cd, mn * 8, hipMemcpyDeviceToHost));
@@ -2210,6 +2216,89 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpy(c32.data(), c_d, mn * 4, hipMemcpyDeviceToHost));
     for (int64_t i = 0; i < mn; ++i) C[i] = c32[i];
+    return CHI0_OK;
+}
+
+extern "C" int chi0_debug_dense_transform(chi0_ctx *c, int32_t precision, int32_t M, int32_t N, int32_t K,
+                                          const double *A, const double *B, int64_t work_bytes, int32_t n_omega,
+                                          const double *omega, double eps, double occ, const double *D, double *C,
+                                          int32_t *fp64_tiles) {
+    if (!c) return CHI0_EINVAL;
+    if (c->device < 0) return fail(c, CHI0_ENOSYS, "no device context");
+    if (M < 64 || M % 64 || N < 1 || K < 1 || K >= (1 << 17) || !A || !B || !C)
+        return fail(c, CHI0_EINVAL, "bad sizes or NULL");
+    if (precision < CHI0_PREC_FP64 || precision > CHI0_PREC_BF16X3) return fail(c, CHI0_EINVAL, "unknown precision");
+    if (n_omega < 0 || (n_omega > 0 && (!omega || !D || N % (2 * n_omega)))) return fail(c, CHI0_EINVAL, "bad factor");
+    HIPCHK(c, hipSetDevice(c->device));
+    struct Scope {
+        DevBuf buf;
+        ~Scope() { buf.release(); }
+    } ws;
+    const int K16 = (int)round_up(K, 16);
+    const int64_t ldb = round_up(N, 4), kb = (int64_t)K16 * ldb, mn = (int64_t)M * N;
+    std::vector<double> at((size_t)K * M), a16((size_t)M * K16, 0.0), b((size_t)kb, 0.0);
+    for (int i = 0; i < M; ++i)
+        for (int k = 0; k < K; ++k) a16[(size_t)i * K16 + k] = at[(size_t)k * M + i] = A[(size_t)i * K + k];
+    for (int k = 0; k < K; ++k) std::copy(B + (size_t)k * N, B + (size_t)(k + 1) * N, b.begin() + (size_t)k * ldb);
+    double *at_d = nullptr, *work = nullptr, *om_d = nullptr, *D_d = nullptr;
+    int *tiles_d = nullptr;
+    CHK(dalloc(c, ws.buf, &at_d, (int64_t)K * M));
+    CHK(dalloc(c, ws.buf, &om_d, n_omega));
+    const int64_t nd = n_omega > 0 ? mn / (2 * n_omega) : 0;
+    CHK(dalloc(c, ws.buf, &D_d, nd));
+    CHK(dalloc(c, ws.buf, &tiles_d, 1));
+    HIPCHK(c, hipMemcpy(at_d, at.data(), at.size() * 8, hipMemcpyHostToDevice));
+    if (n_omega > 0) {
+        HIPCHK(c, hipMemcpy(om_d, omega, (size_t)n_omega * 8, hipMemcpyHostToDevice));
+        HIPCHK(c, hipMemcpy(D_d, D, (size_t)nd * 8, hipMemcpyHostToDevice));
+    }
+    const LorentzArgs la{D_d, om_d, M, 2 * n_omega, eps, occ};
+    const LorentzArgs *lap = n_omega > 0 ? &la : nullptr;
+    int tiles = 0;
+    if (precision == CHI0_PREC_FP64) {
+        double *a_d = nullptr, *b_d = nullptr, *c_d = nullptr;
+        CrtDev a;
+        work_bytes = std::max(work_bytes, crt_work_bytes(M, K, 1));
+        CHK(crt_alloc(c, ws.buf, a, M, K));
+        CHK(dalloc(c, ws.buf, &a_d, (int64_t)M * K16));
+        CHK(dalloc(c, ws.buf, &b_d, kb));
+        CHK(dalloc(c, ws.buf, &c_d, mn));
+        CHK(dalloc(c, ws.buf, &work, (work_bytes + 7) / 8));
+        HIPCHK(c, hipMemcpy(a_d, a16.data(), a16.size() * 8, hipMemcpyHostToDevice));
+        HIPCHK(c, hipMemcpy(b_d, b.data(), b.size() * 8, hipMemcpyHostToDevice));
+        HIPCHK(c, hipDeviceSynchronize());
+        launch_crt_operand(c->stream, at_d, K, M, M, a);
+        const CrtExact x{a_d, K16, K16};
+        launch_crt_gemm(nullptr, c->stream, "panel", M, N, K, a, b_d, ldb, work, (size_t)work_bytes, c_d, N, 0.0, 0.0,
+                        lap, &x, tiles_d);
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipMemcpy(C, c_d, mn * 8, hipMemcpyDeviceToHost));
+        HIPCHK(c, hipMemcpy(&tiles, tiles_d, sizeof(int), hipMemcpyDeviceToHost));
+    } else {
+        std::vector<float> f((size_t)std::max(kb, mn));
+        float *b_d = nullptr, *c_d = nullptr;
+        double *scratch = nullptr;
+        PanelDev p;
+        CHK(panel_alloc(c, ws.buf, p, M, K));
+        work_bytes = std::max(work_bytes, (int64_t)p.nkb * PANEL_LD * 16 * PANEL_BF) / 8 * 8;
+        const size_t scratch_n = (size_t)2048 * 64 * 64;
+        CHK(dalloc(c, ws.buf, &work, work_bytes / 8));
+        CHK(dalloc(c, ws.buf, &scratch, (int64_t)scratch_n));
+        CHK(dalloc(c, ws.buf, &b_d, kb));
+        CHK(dalloc(c, ws.buf, &c_d, mn));
+        std::copy(b.begin(), b.end(), f.begin());
+        HIPCHK(c, hipMemcpy(b_d, f.data(), (size_t)kb * 4, hipMemcpyHostToDevice));
+        launch_panel_bf16(c->stream, at_d, K, M, M, &p);
+        HIPCHK(c, hipDeviceSynchronize());   // the copies above are on the default stream
+        launch_panel_gemm(nullptr, c->stream, "panel", precision == CHI0_PREC_FP32 ? 3 : 2, M, N, K, p, b_d, ldb, work,
+                          (size_t)work_bytes, scratch, scratch_n * sizeof(double), c_d, N, 0.0, 0.0, lap);
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipMemcpy(f.data(), c_d, (size_t)mn * 4, hipMemcpyDeviceToHost));
+        std::copy(f.begin(), f.begin() + mn, C);
+    }
+    if (fp64_tiles) *fp64_tiles = tiles;
     return CHI0_OK;
 }
 

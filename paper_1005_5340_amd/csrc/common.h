@@ -199,26 +199,53 @@ void launch_panel_gemm(Tracer *t, hipStream_t s, const char *name, int planes, i
                        const PanelDev &A, const float *B, int64_t ldb, void *work, size_t work_bytes, void *scratch,
                        size_t scratch_bytes, float *C, int ldc, double flops, double bytes, const LorentzArgs *la);
 // FP64 products on the INT8 matrix cores (kernels_crt.hip): an operand as
-// CRT_S planes of residues with a scale 2^se sm per row (column of B).
+// CRT_S planes of residues and one of magnitudes, with a scale 2^se sm per row
+// (column of B).
 constexpr int CRT_S = 14;
-constexpr int CRT_LD = 256;   // rows of an operand: whole GEMM tiles
-constexpr int CRT_KB = 4;     // k-blocks (of 16) of an operand: whole GEMM stages
+constexpr int CRT_P = CRT_S + 1;
+constexpr int CRT_LD = 256;    // rows of an operand: whole GEMM tiles
+constexpr int CRT_KB = 4;      // k-blocks (of 16) of an operand: whole GEMM stages
+constexpr int CRT_FM = 64, CRT_FN = 128;   // rows and columns of a tile that goes to FP64 as one
+struct CrtScales {             // all [ld]
+    double *sm = nullptr, *si = nullptr;       // sm and 1 / sm
+    int *se = nullptr;
+    float *nrm = nullptr, *rnz = nullptr;      // norm of the scaled row, root of its non-zero entries
+    __device__ __forceinline__ void put(int n, double m, int e, float norm, double nz) const {
+        sm[n] = m;
+        si[n] = 1.0 / m;
+        se[n] = e;
+        nrm[n] = norm;
+        rnz[n] = sqrtf((float)nz);
+    }
+};
 struct CrtDev {
     PanelDev p;
-    double *sm = nullptr, *si = nullptr;   // [ld] sm and 1 / sm
-    int *se = nullptr;                     // [ld]
+    CrtScales sc;
+};
+// A itself, row-major, for the tiles that go to FP64: K a multiple of 16, M of 64
+struct CrtExact {
+    const double *A;
+    int lda, K;
 };
 // whether a product of these sizes is faster this way than in FP64
+constexpr int CRT_FEW = 12288;
 bool crt_pays(int M, int K, int64_t N);
 // residues of X [K][ldx] (N columns = the operand's rows); p's buffers and sizes set
 void launch_crt_operand(hipStream_t s, const double *X, int K, int N, int64_t ldx, CrtDev &p);
 // workspace that takes N columns at once (launch_crt_gemm goes in chunks of
 // columns of at least CRT_LD)
 int64_t crt_work_bytes(int M, int K, int64_t N);
-// C [M][ldc] = A B, B [K][ldb], M % 4 == 0, K < 2^17; la: with the frequency factor
+// C [M][ldc] = A B, B [K][ldb], M % 4 == 0, K < 2^17; la: with the frequency factor.
+// exact: tiles whose operands do not bear the rounding go to the FP64 GEMM (B has
+// exact->K rows then, ldb even); NULL (test hook alone): none do.  flagged (device,
+// may be NULL): += the number of such tiles.
 void launch_crt_gemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const CrtDev &A,
                      const double *B, int64_t ldb, void *work, size_t work_bytes, double *C, int ldc, double flops,
-                     double bytes, const LorentzArgs *la);
+                     double bytes, const LorentzArgs *la, const CrtExact *exact, int *flagged = nullptr);
+// C = A B (+ frequency factor, columns from col0 on) in the flagged tiles:
+// flag[row / CRT_FM][column / CRT_FN], fn flags per row of them.
+void launch_dgemm_flagged(hipStream_t s, int M, int N, int K, const double *A, int lda, const double *B, int ldb,
+                          double *C, int ldc, int col0, const LorentzArgs *la, const uint8_t *flag, int fn);
 // C = sum of S FP32 slices of M x N (+ the frequency factor if la)
 void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, const float *part,
                               float *C, int ldc, const LorentzArgs *la);

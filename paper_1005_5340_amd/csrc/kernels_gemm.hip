@@ -97,14 +97,10 @@ __device__ __forceinline__ int xcd_remap(int wid, int n) {
 // The tile shape (BM x BN, WM x WN wavefronts) changes only which workgroup
 // computes an element, never the order of its k accumulation, so every tile
 // variant gives bit-identical results and the autotuner may pick any of them.
-template <int BM, int BN, int WM, int WN, bool LORENTZ, int BK = 16>
-__global__ __launch_bounds__(WM * WN * 64)
-void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
-             const double *__restrict__ B, int ldb, double *__restrict__ C, int ldc,
-             int m_fastest, LorentzArgs la) {
-    A += (int64_t)blockIdx.y * K;
-    B += (int64_t)blockIdx.y * K * ldb;
-    C += (int64_t)blockIdx.y * M * ldc;
+template <int BM, int BN, int WM, int WN, bool LORENTZ, int BK>
+__device__ __forceinline__ void dgemm_tile(int m0, int n0, int N, int K, const double *__restrict__ A, int lda,
+                                           const double *__restrict__ B, int ldb, double *__restrict__ C, int ldc,
+                                           int col0, const LorentzArgs &la) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM / 16;
     constexpr int TN = BN / WN / 16;
@@ -115,11 +111,6 @@ void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
     __shared__ double As[2][BK][BM + 1];
     __shared__ double Bs[2][BK][BN];
 
-    const int ntm = M / BM, ntn = (N + BN - 1) / BN;
-    const int tile = xcd_remap(blockIdx.x, ntm * ntn);
-    const int tm = m_fastest ? tile % ntm : tile / ntn;
-    const int tn = m_fastest ? tile / ntm : tile % ntn;
-    const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int wm = wv % WM, wn = wv / WM;
 
@@ -201,7 +192,7 @@ void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
     for (int j = 0; j < TN; ++j) {
         const int col = n0 + wn * (BN / WN) + j * 16 + (lane & 15);
         const bool ok = col < N;
-        const int cc = ok ? col : 0, E = LORENTZ ? cc / la.ncp : 0, jj = LORENTZ ? cc - E * la.ncp : 0;
+        const int cc = ok ? col0 + col : 0, E = LORENTZ ? cc / la.ncp : 0, jj = LORENTZ ? cc - E * la.ncp : 0;
         const Lorentz lz(LORENTZ ? la.omega[jj >> 1] : 0.0, la.eps, la.occ, jj & 1);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -216,6 +207,31 @@ void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
             }
         }
     }
+}
+
+template <int BM, int BN, int WM, int WN, bool LORENTZ, int BK = 16>
+__global__ __launch_bounds__(WM * WN * 64)
+void k_dgemm(int M, int N, int K, const double *__restrict__ A, int lda,
+             const double *__restrict__ B, int ldb, double *__restrict__ C, int ldc,
+             int m_fastest, LorentzArgs la) {
+    const int ntm = M / BM, ntn = (N + BN - 1) / BN;
+    const int tile = xcd_remap(blockIdx.x, ntm * ntn);
+    const int tm = m_fastest ? tile % ntm : tile / ntn;
+    const int tn = m_fastest ? tile / ntm : tile % ntn;
+    dgemm_tile<BM, BN, WM, WN, LORENTZ, BK>(tm * BM, tn * BN, N, K, A + (int64_t)blockIdx.y * K, lda,
+                                            B + (int64_t)blockIdx.y * K * ldb, ldb,
+                                            C + (int64_t)blockIdx.y * M * ldc, ldc, 0, la);
+}
+
+// The 64 x 64 tiles of a product that lie in a flagged tile; row tiles fastest.
+template <bool LORENTZ>
+__global__ __launch_bounds__(256)
+void k_dgemm_flagged(int ntm, int N, int K, const double *__restrict__ A, int lda, const double *__restrict__ B,
+                     int ldb, double *__restrict__ C, int ldc, int col0, LorentzArgs la,
+                     const uint8_t *__restrict__ flag, int fn) {
+    const int m0 = blockIdx.x % ntm * 64, n0 = blockIdx.x / ntm * 64;
+    if (!flag[m0 / CRT_FM * fn + n0 / CRT_FN]) return;
+    dgemm_tile<64, 64, 2, 2, LORENTZ, 16>(m0, n0, N, K, A, lda, B, ldb, C, ldc, col0, la);
 }
 
 // C = sum over splits of the partial products; optional Lorentzian epilogue.
@@ -513,6 +529,15 @@ void launch_dgemm_lorentz(Tracer *t, hipStream_t s, int M, int N, int K, int kpa
     LorentzArgs la{Dlt, omega, nv_pad, ncp, eps, occ};
     gemm_any(t, s, "virt_transform_lorentz", M, N, K, kpad, A, lda, B, ldb, C, ldc, flops, bytes,
                      true, la, scratch, scratch_doubles * sizeof(double), tu);
+}
+
+void launch_dgemm_flagged(hipStream_t s, int M, int N, int K, const double *A, int lda, const double *B, int ldb,
+                          double *C, int ldc, int col0, const LorentzArgs *la, const uint8_t *flag, int fn) {
+    const int ntm = M / 64;
+    const dim3 grid((unsigned)((int64_t)ntm * ((N + 63) / 64)));
+    LorentzArgs none{};
+    hipLaunchKernelGGL(la ? k_dgemm_flagged<true> : k_dgemm_flagged<false>, grid, dim3(256), 0, s, ntm, N, K, A, lda, B,
+                       ldb, C, ldc, col0, la ? *la : none, flag, fn);
 }
 
 void launch_splitk_reduce_f32(Tracer *t, hipStream_t s, int M, int N, int S, const float *part,
