@@ -77,6 +77,11 @@ int chi0_debug_dense_transform(chi0_ctx *ctx, int32_t precision, int32_t M, int3
                                const double *B, int64_t work_bytes, int32_t n_omega, const double *omega, double eps,
                                double occ, const double *D, double *C, int32_t *fp64_tiles);
 
+/* Device memory of the context: *held the bytes in all its buffers, *optional those
+ * of them that give way to another allocation (either may be NULL).  From this call
+ * on allocations past `limit` bytes in all fail as on a full device (-1: no limit). */
+int chi0_debug_memory(chi0_ctx *ctx, int64_t limit, int64_t *held, int64_t *optional);
+
 /* Host eigen-decomposition of a Hermitian n x n matrix (row-major interleaved
  * complex): eigenvalues descending in w[n], eigenvectors as columns of V. */
 int chi0_debug_eigh(int32_t n, const double *A, double *w, double *V);

@@ -162,6 +162,8 @@ def lib():
     L.chi0_debug_dense_transform.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _dp, _dp,
                                              C.c_int64, C.c_int32, _dp, C.c_double, C.c_double, _dp, _dp, _i32p]
     L.chi0_debug_dense_transform.restype = C.c_int
+    L.chi0_debug_memory.argtypes = [C.c_void_p, C.c_int64, _i64p, _i64p]
+    L.chi0_debug_memory.restype = C.c_int
     L.chi0_debug_eigh.argtypes = [C.c_int32, _dp, _dp, _dp]
     L.chi0_debug_eigh.restype = C.c_int
     L.chi0_lanczos_opts_default.argtypes = [C.POINTER(LanczosOpts)]
@@ -478,6 +480,13 @@ class Context:
             self._h, int(precision), M, N, K, _ptr(A), _ptr(B), int(work_bytes), 0 if om is None else om.size, _ptr(om),
             float(eps), float(occ), _ptr(Dh), _ptr(out), _ptr(tiles, _i32p)))
         return out, int(tiles[0])
+
+    def debug_memory(self, limit: int = -1):
+        """Test hook: (bytes held, optional ones of them); allocations past `limit` fail from now on
+        (chi0_debug_memory)."""
+        v = np.zeros(2, np.int64)
+        self._check(self._L.chi0_debug_memory(self._h, int(limit), _ptr(v, _i64p), _ptr(v[1:], _i64p)))
+        return int(v[0]), int(v[1])
 
     def set_graphs(self, enable: bool):
         """Replay repeated chi0_apply calls from a HIP graph (chi0_set_graphs)."""

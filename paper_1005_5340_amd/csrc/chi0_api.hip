@@ -95,11 +95,22 @@ void chi0::trace_end(Tracer *t, hipStream_t s, double flops, double bytes) {
 }
 
 // ================================================================== context
+// Device memory of a context: bytes held in all its buffers, and the most it may
+// hold (-1: as much as the device gives; a test hook sets it).  Shared with the
+// buffers, which may outlive the context.
+struct MemCount {
+    int64_t held = 0, limit = -1;
+};
+
 struct DevBuf {
     std::vector<void *> ptrs;
+    int64_t bytes = 0;
+    std::shared_ptr<MemCount> count;
     void release() {
         for (void *p : ptrs) (void)hipFree(p);
         ptrs.clear();
+        if (count) count->held -= bytes;
+        bytes = 0;
     }
 };
 
@@ -107,7 +118,7 @@ struct DevBuf {
 // intermediates for the low-precision operator, allocated on first use).
 // chi0_apply uses op[0]; the solver gives each lane of slots its own.
 struct OpWork {
-    DevBuf buf, lpbuf;
+    DevBuf buf, lpbuf, crtbuf;   // crtbuf: gives way to other allocations (drop_optional)
     int nc_cap = 0, lp_cap = 0;
     double *Vb = nullptr, *Zin = nullptr, *Yout = nullptr, *dV = nullptr, *W = nullptr;
     double *Tt = nullptr, *at = nullptr, *Ut = nullptr, *part = nullptr, *omega_dev = nullptr;
@@ -118,6 +129,11 @@ struct OpWork {
     size_t panel_bytes = 0;
     void *crt = nullptr;     // residues of the FP64 dense GEMMs on INT8 (NULL: not used)
     size_t crt_bytes = 0;
+    void release_crt() {
+        crtbuf.release();
+        crt = nullptr;
+        crt_bytes = 0;
+    }
     void release() {
         lpbuf.release();
         buf.release();
@@ -125,8 +141,7 @@ struct OpWork {
         Tt32 = at32 = Ut32 = nullptr;
         panel = nullptr;
         panel_bytes = 0;
-        crt = nullptr;
-        crt_bytes = 0;
+        release_crt();
     }
 };
 constexpr int kMaxBatch = 256;       // complex columns per operator pass
@@ -141,6 +156,7 @@ struct chi0_ctx {
     std::string err;
     Tracer tracer;
     GemmTuner tuner;
+    std::shared_ptr<MemCount> mem = std::make_shared<MemCount>();
 
     // system
     bool has_system = false;
@@ -153,7 +169,7 @@ struct chi0_ctx {
     int n_blk = 0, n_g = 0, max_rows = 0, max_nprod = 0;
     int64_t nnzB = 0, npart = 0;
     WorkSizes ws{};
-    DevBuf sysbuf;
+    DevBuf sysbuf, crtbuf[2];   // crtbuf: Xv_crt, Xvt_crt
     double *Xo = nullptr, *Xv = nullptr, *Xvt = nullptr, *Dlt = nullptr, *K = nullptr;
     BlockMapDev bm{};
 
@@ -224,6 +240,7 @@ struct chi0_ctx {
                 if (ls) (void)hipStreamSynchronize(ls);
         slotbuf.release();
         for (OpWork &o : op) o.release();
+        for (DevBuf &b : crtbuf) b.release();
         sysbuf.release();
         if (arena_h) (void)hipHostFree(arena_h);
         if (fin_h) (void)hipHostFree(fin_h);
@@ -254,15 +271,53 @@ static int fail(chi0_ctx *c, int code, const std::string &msg) {
                         std::string(#call) + ": " + hipGetErrorString(e_));                \
     } while (0)
 
+// Bytes that a failing allocation takes back: the INT8 route's workspaces and
+// residues, without which the FP64 transforms run on the FP64 matrix cores.
+static int64_t optional_bytes(const chi0_ctx *c) {
+    int64_t b = 0;
+    for (const OpWork &o : c->op) b += o.crtbuf.bytes;
+    for (const DevBuf &r : c->crtbuf) b += r.bytes;
+    return b;
+}
+
+// Frees them, the workspaces first (they come back when a workspace grows), then
+// the residues (with the next system).  False: there were none.
+static bool drop_optional(chi0_ctx *c) {
+    if (optional_bytes(c) == 0) return false;
+    (void)hipDeviceSynchronize();
+    c->drop_apply_graph();
+    bool ws = false;
+    for (OpWork &o : c->op) {
+        ws = ws || o.crt;
+        o.release_crt();
+    }
+    if (!ws) {
+        for (DevBuf &r : c->crtbuf) r.release();
+        c->Xv_crt = c->Xvt_crt = CrtDev{};
+    }
+    return true;
+}
+
+// optional: takes nothing from the other optional buffers, and a failure is not an
+// error of the call.
 template <class T>
-static int dalloc(chi0_ctx *c, DevBuf &buf, T **p, int64_t n) {
+static int dalloc(chi0_ctx *c, DevBuf &buf, T **p, int64_t n, bool optional = false) {
     void *q = nullptr;
     const size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(T);
-    hipError_t e = hipMalloc(&q, bytes);
+    buf.count = c->mem;
+    hipError_t e;
+    do {
+        e = c->mem->limit >= 0 && c->mem->held + (int64_t)bytes > c->mem->limit ? hipErrorOutOfMemory
+                                                                               : hipMalloc(&q, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+    } while (e != hipSuccess && !optional && drop_optional(c));
+    if (e != hipSuccess && optional) return CHI0_ENOMEM;
     if (e != hipSuccess)
         return fail(c, CHI0_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " +
                                         hipGetErrorString(e));
     buf.ptrs.push_back(q);
+    buf.bytes += (int64_t)bytes;
+    c->mem->held += (int64_t)bytes;
     // The zero fill runs on the null stream, which is not ordered with the
     // context's non-blocking streams: wait for it, so that work enqueued on
     // those streams after dalloc returns never races with the fill.
@@ -291,19 +346,44 @@ static int panel_alloc(chi0_ctx *c, DevBuf &buf, PanelDev &p, int rows, int K) {
 }
 
 // Residue planes of an operand with `rows` rows and K reduction entries.
-static int crt_alloc(chi0_ctx *c, DevBuf &buf, CrtDev &p, int rows, int K) {
-    p.p.ld = (int)round_up(rows, CRT_LD);
-    p.p.nkb = (int)round_up((K + 15) / 16, CRT_KB);
-    p.p.plane = (int64_t)p.p.nkb * p.p.ld;
+// optional: without the memory for them p.p.data stays NULL.
+static int crt_alloc(chi0_ctx *c, DevBuf &buf, CrtDev &p, int rows, int K, bool optional) {
+    CrtDev q;
+    q.p.ld = (int)round_up(rows, CRT_LD);
+    q.p.nkb = (int)round_up((K + 15) / 16, CRT_KB);
+    q.p.plane = (int64_t)q.p.nkb * q.p.ld;
     double *d = nullptr;
-    CHK(dalloc(c, buf, &d, p.p.plane * CRT_P * 2));
-    p.p.data = d;
-    CHK(dalloc(c, buf, &p.sc.sm, p.p.ld));
-    CHK(dalloc(c, buf, &p.sc.si, p.p.ld));
-    CHK(dalloc(c, buf, &p.sc.se, p.p.ld));
-    CHK(dalloc(c, buf, &p.sc.nrm, p.p.ld));
-    CHK(dalloc(c, buf, &p.sc.rnz, p.p.ld));
-    return CHI0_OK;
+    int r = dalloc(c, buf, &d, q.p.plane * CRT_P * 2, optional);
+    if (r == CHI0_OK) r = dalloc(c, buf, &q.sc.sm, q.p.ld, optional);
+    if (r == CHI0_OK) r = dalloc(c, buf, &q.sc.si, q.p.ld, optional);
+    if (r == CHI0_OK) r = dalloc(c, buf, &q.sc.se, q.p.ld, optional);
+    if (r == CHI0_OK) r = dalloc(c, buf, &q.sc.nrm, q.p.ld, optional);
+    if (r == CHI0_OK) r = dalloc(c, buf, &q.sc.rnz, q.p.ld, optional);
+    if (r == CHI0_OK) {
+        q.p.data = d;
+        p = q;
+    } else if (optional) {
+        buf.release();
+    }
+    return r == CHI0_ENOMEM && optional ? CHI0_OK : r;
+}
+
+// A workspace that may be smaller: `want` bytes, else half as many, down to `least`.
+// required: `least` or an error; otherwise none (*got = 0) is fine too.
+static int shrinking_alloc(chi0_ctx *c, DevBuf &buf, void **p, int64_t want, int64_t least, bool required, size_t *got) {
+    double *d = nullptr;
+    *p = nullptr;
+    *got = 0;
+    for (int64_t b = std::max(want, least);; b = std::max(b / 2, least)) {
+        const int r = dalloc(c, buf, &d, b / 8, !required || b > least);
+        if (r == CHI0_OK) {
+            *p = d;
+            *got = (size_t)(b / 8 * 8);
+            return CHI0_OK;
+        }
+        if (r != CHI0_ENOMEM) return r;
+        if (b <= least) return required ? r : CHI0_OK;
+    }
 }
 
 // ============================================================ static scratch
@@ -493,6 +573,8 @@ static void drop_system(chi0_ctx *c) {
     c->slot_n = c->slot_m = 0;
     c->drop_apply_graph();
     for (OpWork &o : c->op) o.release();
+    for (DevBuf &b : c->crtbuf) b.release();
+    c->Xv_crt = c->Xvt_crt = CrtDev{};
     c->sysbuf.release();
     c->has_system = false;
 }
@@ -692,14 +774,13 @@ extern "C" int chi0_set_system(chi0_ctx *c, int32_t n_atoms, const double *posit
         CHK(dalloc(c, sb, &c->Xo32, (int64_t)xo.size()));
         CHK(panel_alloc(c, sb, c->Xvt_bf, Nv, N));
         CHK(panel_alloc(c, sb, c->Xv_bf, N, Nv));
-        c->Xvt_crt = c->Xv_crt = CrtDev{};
         // residues of the orbital matrices where some batch (a multiple of 2 No16 columns) uses them
         auto some_batch = [&](int M, int K) {
             const int64_t c1 = 2 * (int64_t)c->No16, most = c1 * kMaxBatch;
             return crt_pays(M, K, most) || crt_pays(M, K, std::max<int64_t>(c1, std::min<int64_t>(most, CRT_FEW / c1 * c1)));
         };
-        if (some_batch(c->Nv_pad, N)) CHK(crt_alloc(c, sb, c->Xvt_crt, c->Nv_pad, N));
-        if (some_batch(c->N_pad, Nv)) CHK(crt_alloc(c, sb, c->Xv_crt, c->N_pad, Nv));
+        if (some_batch(c->N_pad, Nv)) CHK(crt_alloc(c, c->crtbuf[0], c->Xv_crt, c->N_pad, Nv, true));
+        if (some_batch(c->Nv_pad, N)) CHK(crt_alloc(c, c->crtbuf[1], c->Xvt_crt, c->Nv_pad, N, true));
         HIPCHK(c, hipDeviceSynchronize());
         if (c->Xvt_crt.p.data) launch_crt_operand(nullptr, c->Xv, N, c->Nv_pad, c->Nv_pad, c->Xvt_crt);
         if (c->Xv_crt.p.data) launch_crt_operand(nullptr, c->Xvt, Nv, c->N_pad, c->N_pad, c->Xv_crt);
@@ -784,19 +865,18 @@ static int ensure_ws(chi0_ctx *c, OpWork &o, int nc) {
     // the partial products never exceed 2048 64x64 tiles
     o.gemm_scratch_n = (size_t)2048 * 64 * 64;
     CHK(dalloc(c, w, &o.gemm_scratch, (int64_t)o.gemm_scratch_n));
-    // residues of the FP64 transforms on INT8: every column at once up to kCrtBytes
+    // residues of the FP64 transforms on INT8: every column at once up to kCrtBytes, as
+    // many as there is memory for otherwise
     const int64_t ncol = (int64_t)c->No16 * nc;
-    auto crt_bytes = [&](const CrtDev &a, int M, int K) -> int64_t {
-        if (!a.p.data || ncol < 1024) return 0;   // crt_pays for no batch up to this one
-        return std::max(crt_work_bytes(M, K, 1), std::min(kCrtBytes, crt_work_bytes(M, K, ncol)));
+    int64_t want = 0, least = 0;
+    auto crt_bytes = [&](const CrtDev &a, int M, int K) {
+        if (!a.p.data || ncol < 1024) return;   // crt_pays for no batch up to this one
+        want = std::max(want, std::min(kCrtBytes, crt_work_bytes(M, K, ncol)));
+        least = std::max(least, crt_work_bytes(M, K, 1));
     };
-    const int64_t cb = std::max(crt_bytes(c->Xvt_crt, c->Nv_pad, c->N), crt_bytes(c->Xv_crt, c->N_pad, c->Nv));
-    if (cb > 0) {
-        double *d = nullptr;
-        CHK(dalloc(c, w, &d, cb / 8));
-        o.crt = d;
-        o.crt_bytes = (size_t)(cb / 8 * 8);
-    }
+    crt_bytes(c->Xvt_crt, c->Nv_pad, c->N);
+    crt_bytes(c->Xv_crt, c->N_pad, c->Nv);
+    if (least > 0) CHK(shrinking_alloc(c, o.crtbuf, &o.crt, want, least, false, &o.crt_bytes));
     HIPCHK(c, hipDeviceSynchronize());
     o.nc_cap = nc;
     return CHI0_OK;
@@ -822,10 +902,7 @@ static int ensure_lp(chi0_ctx *c, OpWork &o) {
     const int64_t nkb = std::max(c->Xvt_bf.nkb, c->Xv_bf.nkb);
     const int64_t full = nkb * round_up(mcol, PANEL_LD) * 16 * PANEL_BF;
     const int64_t least = nkb * PANEL_LD * 16 * PANEL_BF;
-    o.panel_bytes = (size_t)std::max(least, std::min(full, kPanelBytes));
-    double *pd = nullptr;
-    CHK(dalloc(c, o.lpbuf, &pd, (int64_t)(o.panel_bytes / 8)));
-    o.panel = pd;
+    CHK(shrinking_alloc(c, o.lpbuf, &o.panel, std::min(full, kPanelBytes), least, true, &o.panel_bytes));
     HIPCHK(c, hipDeviceSynchronize());
     o.lp_cap = o.nc_cap;
     return CHI0_OK;
@@ -1295,6 +1372,7 @@ static int solve_impl(chi0_ctx *c, int32_t n_omega, const double *omega, double 
                                 (o.stop != CHI0_STOP_RESIDUAL ? 8.0 * ((double)m * (m + 1) + 8.0 * m + 16.0) : 0.0);
         size_t free_b = 0, total_b = 0;
         HIPCHK(c, hipMemGetInfo(&free_b, &total_b));
+        free_b += (size_t)optional_bytes(c);   // ensure_slots takes them if it must
         const double held = (double)c->slot_n * (c->slot_m > 0 ? 8.0 * (2.0 * (c->slot_m + 1) * c->P_pad +
                                                                         (double)c->slot_m * (c->slot_m + 3)) : 0.0);
         const double avail = (double)free_b + held - 0.05 * (double)total_b - 4e9;
@@ -2180,7 +2258,7 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
         double *bd = nullptr, *cd = nullptr;
         CrtDev a;
         work_bytes = std::max(work_bytes, crt_work_bytes(M, K, 1));
-        CHK(crt_alloc(c, ws.buf, a, M, K));
+        CHK(crt_alloc(c, ws.buf, a, M, K, false));
         CHK(dalloc(c, ws.buf, &a_d, mk));
         CHK(dalloc(c, ws.buf, &work, (work_bytes + 7) / 8));
         CHK(dalloc(c, ws.buf, &bd, kn));
@@ -2216,6 +2294,14 @@ extern "C" int chi0_debug_panel_gemm(chi0_ctx *c, int32_t precision, int32_t M, 
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpy(c32.data(), c_d, mn * 4, hipMemcpyDeviceToHost));
     for (int64_t i = 0; i < mn; ++i) C[i] = c32[i];
+    return CHI0_OK;
+}
+
+extern "C" int chi0_debug_memory(chi0_ctx *c, int64_t limit, int64_t *held, int64_t *optional) {
+    if (!c) return CHI0_EINVAL;
+    c->mem->limit = limit;
+    if (held) *held = c->mem->held;
+    if (optional) *optional = optional_bytes(c);
     return CHI0_OK;
 }
 
@@ -2259,7 +2345,7 @@ extern "C" int chi0_debug_dense_transform(chi0_ctx *c, int32_t precision, int32_
         double *a_d = nullptr, *b_d = nullptr, *c_d = nullptr;
         CrtDev a;
         work_bytes = std::max(work_bytes, crt_work_bytes(M, K, 1));
-        CHK(crt_alloc(c, ws.buf, a, M, K));
+        CHK(crt_alloc(c, ws.buf, a, M, K, false));
         CHK(dalloc(c, ws.buf, &a_d, (int64_t)M * K16));
         CHK(dalloc(c, ws.buf, &b_d, kb));
         CHK(dalloc(c, ws.buf, &c_d, mn));
@@ -2486,6 +2572,7 @@ extern "C" int chi0_lanczos(chi0_ctx *c, int32_t n_drive, const double *drives, 
     {
         size_t fr = 0, tot = 0;
         HIPCHK(c, hipMemGetInfo(&fr, &tot));
+        fr += (size_t)optional_bytes(c);   // taken back where an allocation needs them
         const double need =
             8.0 * (double)(nvec * n + 2 * tc + 69 * ((int64_t)kmax + 2) * nc + (ring ? 0 : LZ_GROUPS * n) +
                            (o.n_x > 0 ? (int64_t)kmax * LZ_XCOL * 6 + (int64_t)P * (nc + 2 * LZ_XCOL) : 0));
@@ -2828,6 +2915,7 @@ extern "C" int chi0_solve_bilanczos(chi0_ctx *c, int32_t n_omega, const double *
     {
         size_t fr = 0, tot = 0;
         HIPCHK(c, hipMemGetInfo(&fr, &tot));
+        fr += (size_t)optional_bytes(c);   // taken back where an allocation needs them
         const double need = 8.0 * ((double)P_pad * 2 * NB * 7 + (double)n_drive * P_pad + 5.0 * NB * (ms + 1));
         if (need > 0.9 * (double)fr) return fail(c, CHI0_ENOMEM, "the recursion's workspace does not fit (max_steps?)");
     }
