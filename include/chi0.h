@@ -59,7 +59,7 @@ extern "C" {
  *           so that every element keeps K 2^-53 sum_k |a_k| |b_k| either way.
  *   FP32    transforms on FP32 operands with FP32 accumulation, FP32 intermediates
  *           (dense ones: each operand as three BF16 terms, which hold it whole,
- *           six BF16 products).
+ *           below 2^-110 to 2^-134; six BF16 products).
  *   BF16X3  the two dense virtual-orbital transforms as split BF16 x 3 (each
  *           operand x = bf16 hi + bf16 lo, three BF16 products, FP32
  *           accumulation); the block-sparse occupied transforms in FP32. */

@@ -17,8 +17,13 @@ typedef float flt2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
+constexpr float BF16_MAX = 0x1.FEp127f;
+
 // One k-block of 8 values as PL planes: bf16(x), then one BF16 of what the
-// planes before leave (all to nearest even); x is overwritten.
+// planes before leave (all to nearest even); x is overwritten.  With three planes
+// the first one stops at the largest finite BF16, so that FP32 values which would
+// round past it (above 3.39e38) are held too.  An infinity gives NaN: its
+// remainder has none.
 template <int PL>
 __device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
 #pragma unroll
@@ -26,7 +31,10 @@ __device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
         uint32_t w[4];
 #pragma unroll
         for (int c = 0; c < 8; c += 2) {
-            const bf16x2 h = __builtin_convertvector((flt2{x[c], x[c + 1]}), bf16x2);
+            flt2 v{x[c], x[c + 1]};
+            if (PL == 3 && pl == 0)
+                v = flt2{__builtin_amdgcn_fmed3f(v.x, -BF16_MAX, BF16_MAX), __builtin_amdgcn_fmed3f(v.y, -BF16_MAX, BF16_MAX)};
+            const bf16x2 h = __builtin_convertvector(v, bf16x2);
             w[c / 2] = __builtin_bit_cast(uint32_t, h);
             x[c] -= __uint_as_float(w[c / 2] << 16);
             x[c + 1] -= __uint_as_float(w[c / 2] & 0xFFFF0000u);
@@ -38,9 +46,9 @@ __device__ __forceinline__ void panel_cut(float (&x)[8], uint4 (&out)[PL]) {
 // C [M][ldc] (FP32) = A B, A and B as PL planes of BF16 (hi, then the
 // rounded remainders).  PL = 2 (split BF16 x 3) sums lo hi + hi lo + hi hi,
 // which drops parts of 2^-17 of a product.  PL = 3 holds an FP32 value whole
-// (3 x 8 bits) and sums the six products of planes x + y <= 2, smallest
-// first: the rest is below 2^-25 of a product, under the rounding of the
-// FP32 accumulation.
+// (3 x 8 bits; one below 2^-110 to 2^-134, half of the least BF16 subnormal) and
+// sums the six products of planes x + y <= 2, smallest first: the rest is below
+// 2^-25 of a product, under the rounding of the FP32 accumulation.
 //
 // blockIdx.y selects a k range of nkb_split k-blocks (at least one stage),
 // whose raw sums go to a C slice of their own.
