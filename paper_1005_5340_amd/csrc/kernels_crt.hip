@@ -360,8 +360,6 @@ void k_crt_cut_long(const double *__restrict__ X, int K, int N, int64_t ldx, con
 //   m_ij >= (4 K + err 2^(53 - 2 MAG_SHIFT) / (K - 8)) (1 + K 2^-22)
 // is enough for err <= (K - 8) 2^-53 S_ij.  m_ij = 0: every product is exactly zero.
 // A NaN (a column with an infinity or NaN has a NaN norm) fails the test.
-// Workgroups of 128 x 128 or, where those are few, 64 x 128 (fewer waits side by
-// side; more LDS reads per product).
 template <class P>
 __global__ __launch_bounds__(P::NT)
 void k_crt_check(int ntm, int ntn, int nkb, int K, int N, const uint4 *__restrict__ A, int lda,
@@ -576,9 +574,6 @@ int64_t crt_work_bytes(int M, int K, int64_t N) {
     return crt_column_bytes((int)round_up(M, CRT_LD), (int)round_up((K + 15) / 16, CRT_KB)) * round_up(N, CRT_LD);
 }
 
-// Tiles of 128 x 128 from which k_crt_check takes those.
-constexpr int CHECK_BIG = 512;
-
 template <class P>
 static void crt_gemm_launch(hipStream_t s, int rows, const CrtDev &A, const CrtDev &B, uint32_t *res,
                             const uint8_t *flag, int fm) {
@@ -588,10 +583,12 @@ static void crt_gemm_launch(hipStream_t s, int rows, const CrtDev &A, const CrtD
                        reinterpret_cast<const uint4 *>(B.p.data), B.p.ld, B.p.plane, res, flag, fm, B.p.ld / CRT_FN);
 }
 
-template <int BM, int KB>
+// Stages of KB k-blocks of either half: nkb % (2 KB) == 0.  (64 x 128 tiles by two
+// wavefronts: 150-400 atoms, 1-12 vectors 26-652 us for both transforms, 25-814.)
+template <int KB>
 static void crt_check_launch(hipStream_t s, int K, int N, const CrtDev &A, const CrtDev &B, uint8_t *flag, int fm) {
-    typedef PanelShape<FormMag, BM, CRT_FN, 2, 2, KB> P;
-    const int ntm = (fm * CRT_FM + BM - 1) / BM, fn = B.p.ld / CRT_FN;
+    typedef PanelShape<FormMag, 128, CRT_FN, 2, 2, KB> P;
+    const int ntm = (fm * CRT_FM + P::BM - 1) / P::BM, fn = B.p.ld / CRT_FN;
     hipLaunchKernelGGL((k_crt_check<P>), dim3(ntm * fn), dim3(P::NT), 0, s, ntm, fn, A.p.nkb, K, N,
                        reinterpret_cast<const uint4 *>(A.p.data) + CRT_S * A.p.plane, A.p.ld, (const float *)A.sc.nrm,
                        (const float *)A.sc.rnz, reinterpret_cast<const uint4 *>(B.p.data) + CRT_S * B.p.plane, B.p.ld,
@@ -599,12 +596,11 @@ static void crt_check_launch(hipStream_t s, int K, int N, const CrtDev &A, const
 }
 
 static void crt_check(hipStream_t s, int K, int N, const CrtDev &A, const CrtDev &B, uint8_t *flag, int fm) {
-    if ((int64_t)((fm + 1) / 2) * (B.p.ld / CRT_FN) < CHECK_BIG)
-        crt_check_launch<64, 4>(s, K, N, A, B, flag, fm);
-    else if (A.p.nkb % 8 == 0)
-        crt_check_launch<128, 4>(s, K, N, A, B, flag, fm);
+    static_assert(CRT_KB % 4 == 0, "whole stages of two k-blocks in either half");
+    if (A.p.nkb % 8 == 0)
+        crt_check_launch<4>(s, K, N, A, B, flag, fm);
     else
-        crt_check_launch<128, 2>(s, K, N, A, B, flag, fm);
+        crt_check_launch<2>(s, K, N, A, B, flag, fm);
 }
 
 void launch_crt_gemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const CrtDev &A,

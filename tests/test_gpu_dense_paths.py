@@ -1,7 +1,7 @@
 """Branches of the dense products that ordinary small systems do not reach.
 
-The INT8 route's ways to cut a column by its length, its largest tiles and
-those of its check; chunks of columns with the frequency factor; the FP64
+The INT8 route's ways to cut a column by its length, its largest tiles, its
+check; chunks of columns with the frequency factor; the FP64
 split-K reduction with the factor; the tile variants of the FP64 GEMM, split
 and whole.  References in extended precision or the FP64 oracle.
 """
@@ -59,7 +59,7 @@ def test_int8_route_by_length(ctx, M, N, K):
 
 @pytest.mark.parametrize("K", [64, 128])
 def test_check_of_large_products(ctx, K):
-    """From 512 tiles of 128 x 128 the check takes those, with stages of 2 or 4 blocks per half."""
+    """Many tiles, of which one goes to FP64; the check's stages of 2 or 4 blocks per half."""
     from paper_1005_5340_amd import chi0
     M, N = 1024, 8192
     A, B = _operands(M, N, K, 23)

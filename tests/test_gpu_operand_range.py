@@ -163,3 +163,20 @@ def test_small_part_of_a_response_next_to_a_large_one():
             e = np.linalg.norm(out[k, part] - ref[part]) / np.linalg.norm(ref[part])
             print(f"[range] omega {w} {'coupling' if part is small else 'other'} products: {e:.2e}", flush=True)
             assert e <= 1e-12
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 64, 900), (64, 64, 1000), (128, 200, 460), (1024, 8192, 100), (1024, 8192, 120)])
+def test_operands_that_meet_in_one_block_only(ctx, M, N, K):
+    """One row and one column of ordinary matrices share a single block of 16 terms, 2^-40 of their others,
+    which meet zeros: the check has to look at every block."""
+    from paper_1005_5340_amd import chi0
+    r = np.random.default_rng(13)
+    blk = np.arange(K) // 16
+    A0, B0 = r.standard_normal((M, K)), r.standard_normal((K, N))
+    for b in range(-(-K // 16)):
+        A, B = A0.copy(), B0.copy()
+        A[3] *= np.where(blk == b, 2.0 ** -40, blk % 2 == 0)
+        B[:, 5] *= np.where(blk == b, 2.0 ** -40, blk % 2 == 1)
+        got, tiles = ctx.debug_dense_transform(A, B, chi0.PREC_FP64)
+        ref, S = _product_longdouble(A[3:4], B), _product_longdouble(np.abs(A[3:4]), np.abs(B))
+        assert tiles > 0 and np.all(np.abs(got[3] - ref) <= K * np.longdouble(2.0) ** -53 * S), b
