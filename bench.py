@@ -38,15 +38,16 @@ sys.path.insert(0, ROOT)
 
 import numpy as np  # noqa: E402
 
-# MI355X dense peaks: FP64 / FP32 / BF16 / INT8 matrix cores, HBM3E
+# MI355X dense peaks: FP64 / FP32 / BF16 / INT8 / FP8 matrix cores, HBM3E
 PEAK = {"mfma": (78.6e12, "TFLOP/s"), "mfma_f32": (157.3e12, "TFLOP/s"),
-        "mfma_bf16": (2.5e15, "TFLOP/s"), "mfma_i8": (5.0e15, "TOP/s"), "hbm": (8.0e12, "GB/s")}
+        "mfma_bf16": (2.5e15, "TFLOP/s"), "mfma_i8": (5.0e15, "TOP/s"),
+        "mfma_f8": (5.0e15, "TFLOP/s"), "hbm": (8.0e12, "GB/s")}
 
 CHI0_KERNELS = ("vertex_gather", "occ_transform", "virt_transform_lorentz", "virt_back",
                 "occ_back", "vertex_contract", "vertex_reduce", "occ_transform_f32",
                 "virt_transform_lorentz_f32", "virt_back_f32", "occ_back_f32",
                 "virt_transform_lorentz_bf16x3", "virt_back_bf16x3",
-                "virt_transform_crt", "virt_back_crt", "crt_cut", "crt_join")
+                "virt_transform_crt", "virt_back_crt", "crt_cut", "crt_check", "crt_join", "crt_fp64_tiles")
 MFMA_KERNELS = ("virt_transform_lorentz", "virt_back", "occ_transform", "occ_back", "kernel_matmul",
                 "casida_front")
 MFMA_F32 = ("occ_transform_f32", "occ_back_f32")
@@ -64,13 +65,16 @@ def bound_of(kernel):
         return "mfma_bf16"
     if kernel in MFMA_I8:
         return "mfma_i8"
+    if kernel == "crt_check":
+        return "mfma_f8"
     return "hbm"
 
 
 KERNEL_SOURCES = {  # kernel -> source file that defines it (for the counter-staleness check)
     "virt_transform_lorentz": "kernels_gemm.hip", "virt_back": "kernels_gemm.hip",
     "virt_transform_crt": "kernels_crt.hip", "virt_back_crt": "kernels_crt.hip",
-    "crt_cut": "kernels_crt.hip", "crt_join": "kernels_crt.hip",
+    "crt_cut": "kernels_crt.hip", "crt_check": "kernels_crt.hip", "crt_join": "kernels_crt.hip",
+    "crt_fp64_tiles": "kernels_gemm.hip",
     "kernel_matmul": "kernels_gemm.hip", "kernel_matvec": "kernels_gemm.hip",
     "occ_transform": "kernels_gemm.hip", "occ_back": "kernels_gemm.hip",
     "vertex_gather": "kernels_vertex.hip", "vertex_contract": "kernels_vertex.hip",

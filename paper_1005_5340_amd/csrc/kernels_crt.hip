@@ -32,8 +32,14 @@
 //      and computed by the FP64 GEMM (launch_dgemm_flagged).
 //
 // Every element therefore keeps the bound of an FP64 sum.  The check and the empty
-// launch for the FP64 tiles take 2.5 + 0.2 ms of 43 (400 atoms, 16 vectors), 0.14 +
-// 0.01 of 2.4 (200 atoms, 12 vectors).
+// launch for the FP64 tiles take 2.4 + 0.1 ms of 43 (400 atoms, 16 vectors), 0.14 +
+// 0.01 of 2.4 (200 atoms, 12 vectors).  How many tiles leave depends on the
+// vectors and the broadening, chi0 z in us (FP64 kernels alone / this way):
+//                              200 atoms, 12   150 atoms, 5   400 atoms, 4
+//   random or graded vectors     3016 / 2470     822 /  674   19100 / 11060
+//   unit vectors                 3018 / 2647     821 /  736   19080 / 10680
+//   eps 1e-4 (else 1e-2)         3013 / 3112     822 /  880   19110 / 12510
+//   eps 1e-8                     3003 / 3055     826 /  864   19230 / 17160
 //
 // Relative error of the transforms of dense orbitals (sampled against extended
 // precision, two seeds), this way and by the FP64 GEMM, in 1e-16:

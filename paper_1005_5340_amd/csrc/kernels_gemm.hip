@@ -854,7 +854,10 @@ static inline int occ_few_groups(const BlockMapDev &bm, int nc, int nt) {
 // time at tn + 3 per workgroup (its own rows or states cost about three tiles of
 // pairs) and 1536 workgroups at once.  (Nine tiles always: 61 -> 48 us for the way
 // back of 60 atoms, 48 columns; the least padding always: 2613 -> 3042 us for the
-// transform of 400 atoms, 32 columns.)
+// transform of 400 atoms, 32 columns.  Both transforms over 30 sizes, 24 to 200
+// atoms and 8 to 256 columns in FP64 and FP32, against these constants: tn + 1 0.2 %
+// slower on average (one size by 5 %), tn + 6 1.6 % (10 %), 768 workgroups 1.8 % (18
+// %), 3072 0.9 % (10 %; 8 % faster at best).)
 static inline int occ_pair_tiles(const BlockMapDev &bm, int nc, int64_t rest) {
     const int n16 = (bm.nb_max * nc + 15) / 16;
     int best = OCC_NT;

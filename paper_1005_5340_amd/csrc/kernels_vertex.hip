@@ -196,7 +196,11 @@ void k_vertex_gather_split(BlockMapDev bm, const double *__restrict__ Z, double 
 
 // Blocks (times 16-column groups, the projection) up to which the kernels split,
 // the gather for up to 16 columns; the projection of up to 16 columns splits for
-// any number of blocks.  Past four workgroups per CU the launch runs in several
+// any number of blocks.  The gather's limit of 16 columns is not one of speed (12
+// atoms, 48 columns: 16.1 us with four waves, 12.1 with eight): the two-sided
+// Lanczos recursion stops at a step that follows the rounding (4950-6130 steps over
+// summation orders at 12 atoms), and the order of the split sums takes it out of
+// the band around the oracle's count that its test allows.  Past four workgroups per CU the launch runs in several
 // waves and the idle wavefronts of the short blocks cost more than the long ones
 // gain (gather, us, four waves / eight: 758 blocks 20.3 / 14.8, 780 17.2 / 14.9;
 // 1246 12.7 / 17.0, 1349 12.8 / 18.9, 1954 23.5 / 28.2).
