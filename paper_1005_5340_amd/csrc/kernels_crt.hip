@@ -367,7 +367,7 @@ void k_crt_cut_long(const double *__restrict__ X, int K, int N, int64_t ldx, con
 // is enough for err <= (K - 8) 2^-53 S_ij.  m_ij = 0: every product is exactly zero.
 // A NaN (a column with an infinity or NaN has a NaN norm) fails the test.
 template <class P>
-__global__ __launch_bounds__(P::NT)
+__global__ __launch_bounds__(P::NT, 3)
 void k_crt_check(int ntm, int ntn, int nkb, int K, int N, const uint4 *__restrict__ A, int lda,
                  const float *__restrict__ an, const float *__restrict__ aq, const uint4 *__restrict__ B, int ldb,
                  const float *__restrict__ bn, const float *__restrict__ bq, uint8_t *__restrict__ flag, int fm, int fn) {
@@ -589,24 +589,18 @@ static void crt_gemm_launch(hipStream_t s, int rows, const CrtDev &A, const CrtD
                        reinterpret_cast<const uint4 *>(B.p.data), B.p.ld, B.p.plane, res, flag, fm, B.p.ld / CRT_FN);
 }
 
-// Stages of KB k-blocks of either half: nkb % (2 KB) == 0.  (64 x 128 tiles by two
-// wavefronts: 150-400 atoms, 1-12 vectors 26-652 us for both transforms, 25-814.)
-template <int KB>
-static void crt_check_launch(hipStream_t s, int K, int N, const CrtDev &A, const CrtDev &B, uint8_t *flag, int fm) {
-    typedef PanelShape<FormMag, 128, CRT_FN, 2, 2, KB> P;
+// Stages of two k-blocks of either half, which any operand has whole ones of.  us for
+// both transforms, 200 atoms, 12 vectors / 400 atoms, 4: 120 / 677; stages of four
+// where the blocks are a multiple of 8, 125 / 652; two workgroups per CU instead of
+// three 154 / 655; 64 x 128 tiles 157 / 814, 256 x 128 209 / 855, 256 x 256 154 / 685.
+static void crt_check(hipStream_t s, int K, int N, const CrtDev &A, const CrtDev &B, uint8_t *flag, int fm) {
+    typedef PanelShape<FormMag, 128, CRT_FN, 2, 2, 2> P;
+    static_assert(CRT_KB % (2 * P::KB) == 0, "whole stages in either half");
     const int ntm = (fm * CRT_FM + P::BM - 1) / P::BM, fn = B.p.ld / CRT_FN;
     hipLaunchKernelGGL((k_crt_check<P>), dim3(ntm * fn), dim3(P::NT), 0, s, ntm, fn, A.p.nkb, K, N,
                        reinterpret_cast<const uint4 *>(A.p.data) + CRT_S * A.p.plane, A.p.ld, (const float *)A.sc.nrm,
                        (const float *)A.sc.rnz, reinterpret_cast<const uint4 *>(B.p.data) + CRT_S * B.p.plane, B.p.ld,
                        (const float *)B.sc.nrm, (const float *)B.sc.rnz, flag, fm, fn);
-}
-
-static void crt_check(hipStream_t s, int K, int N, const CrtDev &A, const CrtDev &B, uint8_t *flag, int fm) {
-    static_assert(CRT_KB % 4 == 0, "whole stages of two k-blocks in either half");
-    if (A.p.nkb % 8 == 0)
-        crt_check_launch<4>(s, K, N, A, B, flag, fm);
-    else
-        crt_check_launch<2>(s, K, N, A, B, flag, fm);
 }
 
 void launch_crt_gemm(Tracer *t, hipStream_t s, const char *name, int M, int N, int K, const CrtDev &A,

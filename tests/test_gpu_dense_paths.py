@@ -59,7 +59,7 @@ def test_int8_route_by_length(ctx, M, N, K):
 
 @pytest.mark.parametrize("K", [64, 128])
 def test_check_of_large_products(ctx, K):
-    """Many tiles, of which one goes to FP64; the check's stages of 2 or 4 blocks per half."""
+    """Many tiles, of which one goes to FP64."""
     from paper_1005_5340_amd import chi0
     M, N = 1024, 8192
     A, B = _operands(M, N, K, 23)
