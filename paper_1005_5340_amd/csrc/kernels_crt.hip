@@ -32,8 +32,8 @@
 //      and computed by the FP64 GEMM (launch_dgemm_flagged).
 //
 // Every element therefore keeps the bound of an FP64 sum.  The check and the empty
-// launch for the FP64 tiles take 2.4 + 0.1 ms of 43 (400 atoms, 16 vectors), 0.14 +
-// 0.01 of 2.4 (200 atoms, 12 vectors).  How many tiles leave depends on the
+// launches for the FP64 tiles take 2.5 + 0.1 ms of 43 (400 atoms, 16 vectors), 0.11 +
+// 0.02 of 2.45 (200 atoms, 12 vectors).  How many tiles leave depends on the
 // vectors and the broadening, chi0 z in us (FP64 kernels alone / this way):
 //                              200 atoms, 12   150 atoms, 5   400 atoms, 4
 //   random or graded vectors     3016 / 2470     822 /  674   19100 / 11060
@@ -366,6 +366,8 @@ void k_crt_cut_long(const double *__restrict__ X, int K, int N, int64_t ldx, con
 //   m_ij >= (4 K + err 2^(53 - 2 MAG_SHIFT) / (K - 8)) (1 + K 2^-22)
 // is enough for err <= (K - 8) 2^-53 S_ij.  m_ij = 0: every product is exactly zero.
 // A NaN (a column with an infinity or NaN has a NaN norm) fails the test.
+// Bound by the wait of a tile of few stages: 1.1 PFLOP/s and matrix cores busy 23 %
+// of the cycles at K = 1000-1800, 1.7 and 33 % at 3200-5200.
 template <class P>
 __global__ __launch_bounds__(P::NT, 3)
 void k_crt_check(int ntm, int ntn, int nkb, int K, int N, const uint4 *__restrict__ A, int lda,
@@ -414,9 +416,11 @@ void k_crt_check(int ntm, int ntn, int nkb, int K, int N, const uint4 *__restric
 }
 
 // Residues of the products: work id = (modulus, column tile, row tile), row
-// tiles fastest.  Bound by the INT8 matrix cores' sustained rate: 1.7-2.15
-// POP/s at K >= 1000 (a library product of 8192^3 reaches 2.11 on this card).  out[modulus][row / 4][ld] holds four consecutive rows of a
-// column per word.
+// tiles fastest.  Bound by the INT8 matrix cores' sustained rate: 1.6-2.15
+// POP/s at K >= 1000 (a library product of 8192^3 reaches 2.11 on this card);
+// they are busy 55 % of the cycles at K = 3200 and 5200, 40-43 % at 1800 and 1000,
+// where a tile's start and end weigh more.  out[modulus][row / 4][ld] holds four
+// consecutive rows of a column per word.
 template <class P>
 __global__ __launch_bounds__(P::NT)
 void k_crt_gemm(int ntm, int ntn, int nkb, const uint4 *__restrict__ A, int lda, int64_t apl,
