@@ -70,3 +70,30 @@ def test_other_allocations_take_it_back(case):
         assert e.value.code == -3
         c.debug_memory(-1)
         assert _same(c.apply(om, s.eps, z), out)
+
+
+def test_solver_lanes_share_what_is_left(case):
+    """Two lanes, each with a workspace of its own, where only part of the INT8 route's memory is there:
+    the solutions meet the same tolerance."""
+    from paper_1005_5340_amd import chi0
+    s, om, z, out, _, _, _, _ = case
+    d = s.drives("z")
+    grid = np.linspace(0.4, 1.2, 16)
+
+    def solve(limit):
+        with chi0.Context(0) as c:
+            c.debug_memory(limit)
+            c.set_system_from(s)
+            a, st, rc = c.solve_response(grid, s.eps, d, restart=200, tol=1e-10, batch=16, lanes=2)
+            assert rc == 0
+            return a, c.debug_memory(limit)
+
+    ref, (held, optional) = solve(-1)
+    assert optional > 0
+    call = 1 << 20   # more than what a call takes and gives back
+    for part in (0.0, 0.3, 0.8):
+        got, (h, o) = solve(held - optional + call + int(part * optional))
+        print(f"[memory] lanes, part {part}: held {h}, optional {o}", flush=True)
+        assert h <= held - (1.0 - part) * optional + call
+        # both meet a residual of 1e-10; the polarizability is second-order accurate in it
+        assert np.max(np.abs(got - ref)) <= 1e-9 * np.max(np.abs(ref))
