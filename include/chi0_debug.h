@@ -72,7 +72,7 @@ int chi0_debug_panel_gemm(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N
  * the operands, *fp64_tiles (may be NULL) the number of 64 x 128 tiles that went to
  * the FP64 matrix cores for it.  n_omega > 0: with the frequency factor, columns
  * (E, r, Re / Im) as in the operator (N a multiple of 2 n_omega), D [E][M] the
- * transition energies.  */
+ * transition energies. */
 int chi0_debug_dense_transform(chi0_ctx *ctx, int32_t precision, int32_t M, int32_t N, int32_t K, const double *A,
                                const double *B, int64_t work_bytes, int32_t n_omega, const double *omega, double eps,
                                double occ, const double *D, double *C, int32_t *fp64_tiles);
